@@ -34,6 +34,7 @@
 
 #include "conv_plan.hpp"
 #include "fastdiv.hpp"
+#include "mfma_conv.hpp"
 #include "tuning.hpp"
 
 namespace ds {
@@ -817,6 +818,14 @@ static void plan_splits(const ConvGeom &g, const Variant &v, int &tiles_p, int &
     splits = (nchunks + cps - 1) / cps;
 }
 
+// Whether a shift problem runs on the matrix cores (variant 64 forces them
+// wherever a layout exists, any other forced variant the vector kernels).
+static bool use_mfma(const ConvGeom &g, const MfmaLayout &l)
+{
+    const int fv = forced_variant();
+    return l.fits && (fv == 64 || (fv < 0 && mfma_prefer(g, l)));
+}
+
 static bool use_direct(const ConvGeom &g, const Variant &v)
 {
     const int64_t x_bytes = int64_t(g.n) * g.c * g.h * g.w * 4;
@@ -861,17 +870,22 @@ void describe_conv(const ConvGeom &g0, char *buf, size_t len)
     size_t lds = 0;
     const Variant v = choose_variant(g, Padded(), plane, lds);
     if (use_direct(g, v)) {
-        snprintf(buf, len, "direct");
+        snprintf(buf, len, "direct%s", use_mfma(g0, mfma_layout(g0)) ? "; matrix cores" : "");
         return;
     }
     int tiles_p, tiles_k, nchunks, splits, cps;
     plan_splits(g, v, tiles_p, tiles_k, nchunks, splits, cps);
+    // Problems that the matrix cores run are named by their tiled instance too (the
+    // one that takes them under another variant or a small workspace).
+    const MfmaLayout l = mfma_layout(g0);
+    char mfma[32] = "";
+    if (use_mfma(g0, l)) snprintf(mfma, sizeof mfma, "; matrix cores, parts %d", l.splits);
     if (v.mode == MODE_POINT)
-        snprintf(buf, len, "tiled point%s tm%d cc%d splits%d", rowmajor ? " transposed" : "", v.tm,
-                 v.cc, splits);
+        snprintf(buf, len, "tiled point%s tm%d cc%d splits%d%s", rowmajor ? " transposed" : "", v.tm,
+                 v.cc, splits, mfma);
     else
-        snprintf(buf, len, "tiled window tm%d cc%d s%d gw%d splits%d", v.tm, v.cc, v.sk, v.gw,
-                 splits);
+        snprintf(buf, len, "tiled window tm%d cc%d s%d gw%d splits%d%s", v.tm, v.cc, v.sk, v.gw,
+                 splits, mfma);
 }
 
 // The epilogue as its own pass over y (see epilogue_kernel).
@@ -1331,6 +1345,18 @@ hipError_t run_conv(const ConvGeom &g0, const int32_t *x, const uint32_t *wp, co
                     const OutMap &map, const Padded &pad, const Workspace &ws)
 {
     if (rows_path(g0, map, pad)) return run_rows(g0, x, wp, wi, bias, y, op, st, epi);
+    if (op == Inner::Shift && !(epi.any() && !map.dense())) {
+        const MfmaLayout l = mfma_layout(g0);
+        if (use_mfma(g0, l) && (!ws.ptr || l.bytes() <= ws.bytes)) {
+            void *scratch = ws.ptr;
+            hipError_t e = scratch ? hipSuccess : scratch_alloc(&scratch, l.bytes(), st);
+            if (e != hipSuccess) return e;
+            e = run_mfma(g0, l, x, wp, bias, y, st, epi, map, scratch);
+            if (ws.ptr) return e;
+            const hipError_t ef = hipFreeAsync(scratch, st);
+            return e != hipSuccess ? e : ef;
+        }
+    }
     const ConvLayout L = conv_layout(g0, map, pad);
     const ConvGeom &g = L.g;
     const bool mapped = L.mapped, rowmajor = L.rowmajor;

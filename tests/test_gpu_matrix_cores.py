@@ -1,0 +1,115 @@
+"""GPU parity of the matrix-core kernels, bit for bit against the oracle: the edges
+of their tiles (256 pixels, 64 channels, 32-channel blocks, chunks of two blocks,
+odd block counts, tap columns folded into channels), inputs inside the one-digit
+range, at its edges, beyond it in some blocks only and over all of int32, sums
+that reach the exact range of the accumulators, split reductions, both output
+layouts, the fused epilogue and 2-5-bit codes. Variant 64 forces the kernels
+where the problem is too small for them to be the automatic choice."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_1905_13298_amd import ops
+from paper_1905_13298_amd.workloads import random_codes
+
+pytestmark = pytest.mark.gpu
+DEV = torch.device("cuda:0")
+
+
+def to_dev(a):
+    return None if a is None else torch.from_numpy(np.ascontiguousarray(a)).to(DEV)
+
+
+def inputs(rng, mode, shape):
+    if mode == "digit":       # |x| < 2^20: one digit above the low 16 bits
+        x = rng.integers(-(2 ** 20), 2 ** 20, shape)
+    elif mode == "edges":     # either side of that range, and the type's ends
+        x = rng.choice([-(2 ** 31), 2 ** 31 - 1, -(2 ** 20) - 1, -(2 ** 20), 2 ** 20 - 1, 2 ** 20, -1, 0, 1], shape)
+    elif mode == "one":       # a single value beyond it
+        x = rng.integers(0, 2 ** 18, shape)
+        x[-1, -1, -1, -1] = -(2 ** 31)
+    else:                     # "full": all of int32
+        x = rng.integers(-(2 ** 31), 2 ** 31, shape, dtype=np.int64)
+    return x.astype(np.int32)
+
+
+CASES = [
+    # n, c, h, w, k, r, s, stride, pad, inputs
+    (1, 1, 1, 257, 1, 1, 1, 1, 0, "full"),        # one channel, one pixel past a tile
+    (1, 32, 16, 16, 64, 1, 1, 1, 0, "digit"),     # exactly one tile, one block
+    (1, 64, 16, 16, 65, 1, 1, 1, 0, "edges"),     # one channel past a row tile
+    (3, 40, 9, 9, 65, 1, 1, 2, 0, "one"),         # strided 1 x 1: a packed copy of the sampled pixels
+    (2, 96, 14, 14, 70, 3, 3, 2, 1, "edges"),     # odd number of blocks: a chunk spans two taps
+    (2, 33, 13, 17, 70, 3, 2, 2, 1, "full"),      # ragged channels, window and rows
+    (1, 3, 40, 41, 64, 7, 7, 2, 3, "digit"),      # folded tap columns
+    (2, 10, 11, 12, 33, 5, 3, 1, 2, "full"),      # folded, padding beyond the window's half
+    (2, 64, 7, 7, 128, 3, 3, 1, 1, "digit"),      # small images: a tile spans several
+    (300, 256, 1, 1, 128, 1, 1, 1, 0, "digit"),   # LinearShift: y in rows of channels
+    (261, 250, 1, 1, 130, 1, 1, 1, 0, "full"),    # unaligned rows
+]
+
+
+@pytest.mark.parametrize("case", CASES, ids=[f"{i}_{c[-1]}" for i, c in enumerate(CASES)])
+def test_matrix_core_convolutions_match_oracle(case, knob):
+    n, c, h, w, k, r, s, stride, pad, mode = case
+    rng = np.random.default_rng(100 + CASES.index(case))
+    x = inputs(rng, mode, (n, c, h, w))
+    codes = random_codes(rng, (k, c * r * s), zero_frac=0.1)
+    bias = rng.integers(-(2 ** 31), 2 ** 31, k, dtype=np.int64).astype(np.int32)
+    knob("DS_FORCE_VARIANT", 64)
+    assert "matrix cores" in ops.describe_conv2d(n, c, h, w, k, (r, s), stride, pad)
+    print(case, ops.describe_conv2d(n, c, h, w, k, (r, s), stride, pad), flush=True)
+    want = oracle.conv2d_shift(x, codes, bias, r=r, s=s, stride=stride, pad=pad)
+    size = want.size
+    big = torch.full((size + 512,), 0x5A5A5A5A, dtype=torch.int32, device=DEV)   # canaries around y
+    y = ops.conv2d_shift(to_dev(x), to_dev(ops.pack_shift_weights(codes).view(np.int32)), to_dev(bias), (r, s),
+                         stride, pad, out=big[256:256 + size].view(want.shape))
+    np.testing.assert_array_equal(y.cpu().numpy(), want)
+    edge = big.cpu().numpy()
+    assert np.all(edge[:256] == 0x5A5A5A5A) and np.all(edge[256 + size:] == 0x5A5A5A5A)
+
+
+@pytest.mark.parametrize("value,shift", [(2 ** 20 - 1, 6), (-(2 ** 20), 6), (2 ** 20 - 1, 0), (2 ** 31 - 1, 0)])
+def test_sums_past_the_accumulators_exact_range(value, shift, knob):
+    """1056 equal terms of the largest size an accumulator meets (shift 6 in one, shift
+    0 in the other): a tile that walked them in one go would pass 2^24 units. The grid
+    is large enough that the reduction is not split."""
+    n, c, k = 300, 1056, 16
+    knob("DS_FORCE_VARIANT", 64)
+    assert ops.describe_conv2d(n, c, 16, 16, k, 1).endswith("parts 1")
+    x = torch.full((n, c, 16, 16), value, dtype=torch.int32, device=DEV)
+    codes = np.full((k, c), shift, dtype=np.uint8)
+    codes[1::2] |= 16
+    y = ops.conv2d_shift(x, to_dev(ops.pack_shift_weights(codes).view(np.int32)), None, 1)
+    total = c * (value >> shift)
+    wrap = lambda v: (v + 2 ** 31) % 2 ** 32 - 2 ** 31
+    assert torch.all(y[:, 0::2] == wrap(total)) and torch.all(y[:, 1::2] == wrap(-total))
+
+
+@pytest.mark.parametrize("mode", ["digit", "edges"])
+@pytest.mark.parametrize("shape", [(96, 64, 16, 64, 1), (2, 128, 14, 100, 3), (260, 64, 1, 72, 1)],
+                         ids=["whole", "split", "linear"])
+def test_matrix_core_epilogue_matches_oracle(shape, mode, knob):
+    n, c, h, k, r = shape
+    rng = np.random.default_rng(n + c)
+    x = inputs(rng, mode, (n, c, h, h))
+    codes = random_codes(rng, (k, c * r * r), zero_frac=0.1)
+    bias, mul, add = (rng.integers(-(2 ** 18), 2 ** 18, k).astype(np.int32) for _ in range(3))
+    res = rng.integers(-(2 ** 31), 2 ** 31, (n, k, h, h), dtype=np.int64).astype(np.int32)
+    knob("DS_FORCE_VARIANT", 64)
+    y = ops.conv2d_shift_fused(to_dev(x), to_dev(ops.pack_shift_weights(codes).view(np.int32)), to_dev(bias), r, 1,
+                               r // 2, mul=to_dev(mul), add=to_dev(add), mul_shift=13, residual=to_dev(res), relu=True)
+    want = oracle.epilogue(oracle.conv2d_shift(x, codes, bias, r=r, stride=1, pad=r // 2), mul, add, 13, res, True)
+    np.testing.assert_array_equal(y.cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("bits", [2, 3, 4])
+def test_matrix_core_short_codes_match_oracle(bits, knob):
+    rng = np.random.default_rng(bits)
+    x = inputs(rng, "digit", (2, 64, 9, 9))
+    codes = random_codes(rng, (70, 64 * 9), zero_frac=0.2, max_shift=(1 << (bits - 1)) - 2)
+    knob("DS_FORCE_VARIANT", 64)
+    y = ops.conv2d_shift(to_dev(x), to_dev(ops.pack_shift_weights(codes, bits).view(np.int32)), None, 3, 1, 1,
+                         code_bits=bits)
+    np.testing.assert_array_equal(y.cpu().numpy(), oracle.conv2d_shift(x, codes, None, r=3, stride=1, pad=1))
