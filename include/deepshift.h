@@ -247,6 +247,32 @@ ds_status ds_conv2d_shift_fused(const int32_t *x, const uint32_t *w_packed, cons
                                 int32_t stride_h, int32_t stride_w, int32_t pad_h, int32_t pad_w,
                                 int32_t frac_bits, uint32_t flags, void *stream);
 
+/* The same two operators with scratch of the caller's: device memory of at least
+ * ds_conv2d_shift_scratch_bytes (ds_conv2d_shift_backward_data_scratch_bytes)
+ * bytes for the shape, 256-byte aligned, apart from the other buffers and not
+ * used by anything else until the call's work on `stream` is done. A call with
+ * less, or with NULL, takes its scratch from the device's memory pool as the
+ * calls above do. ds_conv2d_shift and ds_linear_shift are the fused operator
+ * without mul, add and residual (a LinearShift with h = w = r = s = 1). The
+ * byte counts are -1 for an invalid shape; they hold for every code width. */
+int64_t ds_conv2d_shift_scratch_bytes(int64_t n, int64_t c, int64_t h, int64_t w, int64_t k, int64_t r,
+                                      int64_t s, int32_t stride_h, int32_t stride_w, int32_t pad_h,
+                                      int32_t pad_w);
+ds_status ds_conv2d_shift_fused_ws(const int32_t *x, const uint32_t *w_packed, const int32_t *bias,
+                                   const int32_t *mul, const int32_t *add, int32_t mul_shift,
+                                   const int32_t *residual, int32_t *y, int64_t n, int64_t c, int64_t h,
+                                   int64_t w, int64_t k, int64_t r, int64_t s, int32_t stride_h,
+                                   int32_t stride_w, int32_t pad_h, int32_t pad_w, int32_t frac_bits,
+                                   uint32_t flags, void *scratch, int64_t scratch_bytes, void *stream);
+int64_t ds_conv2d_shift_backward_data_scratch_bytes(int64_t n, int64_t c, int64_t h, int64_t w, int64_t k,
+                                                    int64_t r, int64_t s, int32_t stride_h,
+                                                    int32_t stride_w, int32_t pad_h, int32_t pad_w);
+ds_status ds_conv2d_shift_backward_data_ws(const int32_t *dy, const uint32_t *w_packed, int32_t *dx,
+                                           int64_t n, int64_t c, int64_t h, int64_t w, int64_t k, int64_t r,
+                                           int64_t s, int32_t stride_h, int32_t stride_w, int32_t pad_h,
+                                           int32_t pad_w, int32_t frac_bits, uint32_t flags, void *scratch,
+                                           int64_t scratch_bytes, void *stream);
+
 /* Max pooling of int32 x [n][c][h][w] into y [n][c][oh][ow] (oh, ow as for
  * ConvShift); window positions in the padding are ignored, so pad_h <= r/2 and
  * pad_w <= s/2 are required (every window then holds an input). The max pool
@@ -433,6 +459,12 @@ ds_status ds_jit_conv_image(const uint32_t *w_packed, const int32_t *bias, const
                             int64_t *size);
 ds_status ds_jit_conv_query(const ds_jit_conv *plan, int64_t *code_bytes, int32_t *segments,
                             int32_t *splits);
+/* Whether a plan runs on the matrix cores (1) or generated code (0). Large layers
+ * do, when splits is 0 and no plan knob below is set: the plan then holds the
+ * expanded weight matrices and a packed copy of x in place of code, and query
+ * and layout describe those (code_bytes: the matrices; 64 channels a segment,
+ * 256 pixels a tile). */
+int32_t ds_jit_conv_matrix_cores(const ds_jit_conv *plan);
 ds_status ds_jit_conv_layout(const ds_jit_conv *plan, int32_t *channels, int32_t *wsplit,
                              int32_t *pixel_groups, int32_t *pixel_tiles, int32_t *transposed);
 

@@ -23,10 +23,12 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cstring>
 #include <vector>
 
 #include "common.hpp"
 #include "conv_plan.hpp"
+#include "mfma_conv.hpp"
 
 namespace ds {
 namespace {
@@ -87,6 +89,31 @@ std::vector<GradPhase> grad_phases(const ConvGeom &g)
             out.push_back(p);
         }
     return out;
+}
+
+bool mfma_gradient_tasks(const ConvGeom &g, std::vector<MfmaTask> &tasks, bool &zeros, int64_t &terms)
+{
+    tasks.clear();
+    zeros = false;
+    terms = 0;
+    const std::vector<GradPhase> phases = grad_phases(g);
+    int live = 0;
+    for (const GradPhase &ph : phases) live += ph.g.r > 0 && ph.g.s > 0;
+    for (const GradPhase &ph : phases) {
+        if (ph.g.r == 0 || ph.g.s == 0) {
+            zeros = true;
+            continue;
+        }
+        terms += int64_t(ph.g.n) * ph.g.oh * ph.g.ow * ph.g.k * ph.g.crs;
+        MfmaTask t;
+        t.g = ph.g;
+        t.map = ph.map;
+        t.l = mfma_layout(ph.g, live > 1, std::min(live, kMfmaTasks));
+        t.w = mfma_phase_weights(g, ph);
+        if (!t.l.fits) return false;
+        tasks.push_back(t);
+    }
+    return !tasks.empty();
 }
 
 namespace {
@@ -194,9 +221,66 @@ bool plan_phases(const ConvGeom &g, std::vector<PhasePlan> &out, size_t &words)
     return true;
 }
 
-hipError_t run_backward_data(const ConvGeom &g, const int32_t *dy, const uint32_t *wp, int32_t *dx,
-                             hipStream_t st)
+// Whether the input gradient of g runs on the matrix cores, and its tasks there.
+bool matrix_phases(const ConvGeom &g, std::vector<MfmaTask> &tasks, bool &zeros)
 {
+    const int fv = forced_variant();
+    if (fv >= 0 && fv != 64) return false;
+    // The small-batch LinearShift kernel keeps its rows.
+    if (fv < 0 && g.h == 1 && g.w == 1 && g.r == 1 && g.s == 1 && g.ph == 0 && g.pw == 0 && g.n < 256) return false;
+    int64_t terms = 0;
+    return mfma_gradient_tasks(g, tasks, zeros, terms) && (fv == 64 || mfma_prefer(tasks[0].g, terms));
+}
+
+size_t matrix_phase_bytes(const std::vector<MfmaTask> &tasks)
+{
+    size_t bytes = tasks[0].l.input_bytes();
+    for (const MfmaTask &t : tasks) bytes += t.l.weight_bytes();
+    return bytes;
+}
+
+hipError_t run_matrix_phases(std::vector<MfmaTask> &tasks, bool zeros, const ConvGeom &g, const int32_t *dy,
+                             const uint32_t *wp, int32_t *dx, unsigned char *scratch, hipStream_t st)
+{
+    size_t at = tasks[0].l.input_bytes();
+    for (MfmaTask &t : tasks) {
+        t.weights = scratch + at;
+        at += t.l.weight_bytes();
+    }
+    hipError_t e = zeros ? run_fill_zero(dx, int64_t(g.n) * g.c * g.h * g.w, st) : hipSuccess;
+    for (size_t i = 0; i < tasks.size() && e == hipSuccess; i += kMfmaTasks) {
+        const int n = int(std::min<size_t>(kMfmaTasks, tasks.size() - i));
+        e = mfma_prepare(&tasks[i], n, i ? nullptr : dy, 4, wp, scratch, nullptr, dx, st);
+        // Later groups read the copy the first one packed.
+        if (e == hipSuccess) e = mfma_multiply(&tasks[i], n, scratch, nullptr, dx, Epilogue(), st);
+    }
+    return e;
+}
+
+size_t backward_workspace_bytes(const ConvGeom &g)
+{
+    std::vector<MfmaTask> tasks;
+    bool zeros = false;
+    return matrix_phases(g, tasks, zeros) ? matrix_phase_bytes(tasks) : 0;
+}
+
+hipError_t run_backward_data(const ConvGeom &g, const int32_t *dy, const uint32_t *wp, int32_t *dx,
+                             hipStream_t st, const Workspace &ws = Workspace())
+{
+    {
+        std::vector<MfmaTask> tasks;
+        bool zeros = false;
+        if (matrix_phases(g, tasks, zeros)) {
+            const size_t bytes = matrix_phase_bytes(tasks);
+            void *scratch = ws.ptr && ws.bytes >= bytes ? ws.ptr : nullptr;
+            const bool own = !scratch;
+            hipError_t e = own ? scratch_alloc(&scratch, bytes, st) : hipSuccess;
+            if (e != hipSuccess) return e;
+            e = run_matrix_phases(tasks, zeros, g, dy, wp, dx, static_cast<unsigned char *>(scratch), st);
+            const hipError_t ef = own ? hipFreeAsync(scratch, st) : hipSuccess;
+            return e != hipSuccess ? e : ef;
+        }
+    }
     std::vector<PhasePlan> phases;
     size_t words = 0;
     const int wpr = int(row_words_bits(g.crs, g.bits));
@@ -240,9 +324,12 @@ hipError_t run_backward_data(const ConvGeom &g, const int32_t *dy, const uint32_
 void describe_backward(const ConvGeom &g, char *buf, size_t len)
 {
     std::vector<PhasePlan> phases;
+    std::vector<MfmaTask> tasks;
     size_t words = 0;
+    bool zeros = false;
+    const bool mfma = matrix_phases(g, tasks, zeros);
     if (!plan_phases(g, phases, words) || forced_variant() == 0) {
-        snprintf(buf, len, "direct");
+        snprintf(buf, len, "direct%s", mfma ? "; matrix cores" : "");
         return;
     }
     size_t used = size_t(snprintf(buf, len, "phases%zu", phases.size()));
@@ -254,28 +341,24 @@ void describe_backward(const ConvGeom &g, char *buf, size_t len)
             snprintf(sub, sizeof sub, "zero");
         else
             describe_conv(q, sub, sizeof sub);
+        // (the phases are named by their tiled instances)
+        if (char *cut = strstr(sub, "; matrix cores")) *cut = 0;
         used += size_t(snprintf(buf + used, len - used, "%s%dx%d %s", used ? "; " : "", q.r,
                                 q.s, sub));
     }
+    if (mfma && used < len) snprintf(buf + used, len - used, "; matrix cores");
 }
 
-// Validates a backward problem given by its forward geometry.
-ds_status check_backward(const void *dy, const void *wp, const void *dx, int64_t n, int64_t c,
-                         int64_t h, int64_t w, int64_t k, int64_t r, int64_t s, int32_t sh,
-                         int32_t sw, int32_t ph, int32_t pw, int32_t frac_bits, uint32_t flags,
-                         ConvGeom &g)
+// Validates the sizes of a backward problem given by its forward geometry.
+ds_status backward_shape(int64_t n, int64_t c, int64_t h, int64_t w, int64_t k, int64_t r, int64_t s, int32_t sh,
+                         int32_t sw, int32_t ph, int32_t pw, int bits, ConvGeom &g)
 {
-    if (!dy || !wp || !dx) return fail(DS_ERR_NULL_POINTER, "dy, w_packed and dx must not be NULL");
     if (n <= 0 || c <= 0 || h <= 0 || w <= 0 || k <= 0 || r <= 0 || s <= 0)
         return fail(DS_ERR_INVALID_SHAPE, "all sizes must be > 0");
     if (sh < 1 || sw < 1) return fail(DS_ERR_INVALID_ARG, "stride must be >= 1");
     if (ph < 0 || pw < 0) return fail(DS_ERR_INVALID_ARG, "padding must be >= 0");
     if (h + 2 * int64_t(ph) < r || w + 2 * int64_t(pw) < s)
         return fail(DS_ERR_INVALID_SHAPE, "kernel larger than the padded input");
-    if (frac_bits < 0 || frac_bits > 31) return fail(DS_ERR_INVALID_ARG, "frac_bits must be in [0, 31]");
-    const int bits = flags_code_bits(flags);
-    if ((flags & ~0xF00u) != 0 || bits < 0)
-        return fail(DS_ERR_INVALID_ARG, "flags must be 0 apart from DS_CODE_BITS(2..5)");
     const int64_t oh = (h + 2 * int64_t(ph) - r) / sh + 1;
     const int64_t ow = (w + 2 * int64_t(pw) - s) / sw + 1;
     const int64_t crs = prod({c, r, s});
@@ -286,6 +369,27 @@ ds_status check_backward(const void *dy, const void *wp, const void *dx, int64_t
         return fail(DS_ERR_UNSUPPORTED, "tensors with 2^31 or more elements are not supported");
     g = ConvGeom{int(n), int(c), int(h), int(w), int(k), int(r), int(s), sh, sw, ph, pw,
                  int(oh), int(ow), int(crs), bits};
+    return DS_SUCCESS;
+}
+
+// Validates a backward problem given by its forward geometry.
+ds_status check_backward(const void *dy, const void *wp, const void *dx, int64_t n, int64_t c,
+                         int64_t h, int64_t w, int64_t k, int64_t r, int64_t s, int32_t sh,
+                         int32_t sw, int32_t ph, int32_t pw, int32_t frac_bits, uint32_t flags,
+                         ConvGeom &g)
+{
+    if (!dy || !wp || !dx) return fail(DS_ERR_NULL_POINTER, "dy, w_packed and dx must not be NULL");
+    const int bits = flags_code_bits(flags);
+    if (n > 0 && c > 0 && h > 0 && w > 0 && k > 0 && r > 0 && s > 0 && sh >= 1 && sw >= 1 && ph >= 0 && pw >= 0 &&
+        h + 2 * int64_t(ph) >= r && w + 2 * int64_t(pw) >= s) {
+        if (frac_bits < 0 || frac_bits > 31) return fail(DS_ERR_INVALID_ARG, "frac_bits must be in [0, 31]");
+        if ((flags & ~0xF00u) != 0 || bits < 0)
+            return fail(DS_ERR_INVALID_ARG, "flags must be 0 apart from DS_CODE_BITS(2..5)");
+    }
+    const ds_status st = backward_shape(n, c, h, w, k, r, s, sh, sw, ph, pw, bits < 0 ? 5 : bits, g);
+    if (st != DS_SUCCESS) return st;
+    const int64_t ye = int64_t(g.n) * g.k * g.oh * g.ow, xe = int64_t(g.n) * g.c * g.h * g.w;
+    const int64_t we = int64_t(g.k) * row_words_bits(g.crs, g.bits);
     const int64_t dyb = 4 * ye, dxb = 4 * xe, wb = 4 * we;
     if (overlap(dx, dxb, dy, dyb) || overlap(dx, dxb, wp, wb))
         return fail(DS_ERR_INVALID_ARG, "dx overlaps an input");
@@ -300,6 +404,28 @@ ds_status check_backward(const void *dy, const void *wp, const void *dx, int64_t
 
 using namespace ds;
 
+static ds_status backward_data(const int32_t *dy, const uint32_t *w_packed, int32_t *dx, int64_t n, int64_t c,
+                               int64_t h, int64_t w, int64_t k, int64_t r, int64_t s, int32_t stride_h,
+                               int32_t stride_w, int32_t pad_h, int32_t pad_w, int32_t frac_bits, uint32_t flags,
+                               void *scratch, int64_t scratch_bytes, void *stream, const char *name)
+{
+    ConvGeom g;
+    ds_status st = check_backward(dy, w_packed, dx, n, c, h, w, k, r, s, stride_h, stride_w, pad_h,
+                                  pad_w, frac_bits, flags, g);
+    if (st != DS_SUCCESS) return st;
+    Workspace ws;
+    st = check_workspace(scratch, scratch_bytes, {{dy, 4 * int64_t(g.n) * g.k * g.oh * g.ow}, {dx, 4 * int64_t(g.n) * g.c * g.h * g.w}}, ws);
+    if (st != DS_SUCCESS) return st;
+    hipError_t e;
+    try {
+        e = run_backward_data(g, dy, w_packed, dx, static_cast<hipStream_t>(stream), ws);
+    } catch (const std::bad_alloc &) {
+        return fail(DS_ERR_HIP, "%s: out of host memory", name);
+    }
+    if (e != hipSuccess) return fail(DS_ERR_HIP, "%s: %s", name, hipGetErrorString(e));
+    return ok();
+}
+
 extern "C" ds_status ds_conv2d_shift_backward_data(const int32_t *dy, const uint32_t *w_packed,
                                                    int32_t *dx, int64_t n, int64_t c, int64_t h,
                                                    int64_t w, int64_t k, int64_t r, int64_t s,
@@ -307,13 +433,33 @@ extern "C" ds_status ds_conv2d_shift_backward_data(const int32_t *dy, const uint
                                                    int32_t pad_h, int32_t pad_w, int32_t frac_bits,
                                                    uint32_t flags, void *stream)
 {
+    return backward_data(dy, w_packed, dx, n, c, h, w, k, r, s, stride_h, stride_w, pad_h, pad_w, frac_bits, flags,
+                         nullptr, 0, stream, "ds_conv2d_shift_backward_data");
+}
+
+extern "C" ds_status ds_conv2d_shift_backward_data_ws(const int32_t *dy, const uint32_t *w_packed, int32_t *dx,
+                                                      int64_t n, int64_t c, int64_t h, int64_t w, int64_t k,
+                                                      int64_t r, int64_t s, int32_t stride_h, int32_t stride_w,
+                                                      int32_t pad_h, int32_t pad_w, int32_t frac_bits,
+                                                      uint32_t flags, void *scratch, int64_t scratch_bytes,
+                                                      void *stream)
+{
+    return backward_data(dy, w_packed, dx, n, c, h, w, k, r, s, stride_h, stride_w, pad_h, pad_w, frac_bits, flags,
+                         scratch, scratch_bytes, stream, "ds_conv2d_shift_backward_data_ws");
+}
+
+extern "C" int64_t ds_conv2d_shift_backward_data_scratch_bytes(int64_t n, int64_t c, int64_t h, int64_t w,
+                                                               int64_t k, int64_t r, int64_t s, int32_t stride_h,
+                                                               int32_t stride_w, int32_t pad_h, int32_t pad_w)
+{
     ConvGeom g;
-    ds_status st = check_backward(dy, w_packed, dx, n, c, h, w, k, r, s, stride_h, stride_w, pad_h,
-                                  pad_w, frac_bits, flags, g);
-    if (st != DS_SUCCESS) return st;
-    const hipError_t e = run_backward_data(g, dy, w_packed, dx, static_cast<hipStream_t>(stream));
-    if (e != hipSuccess) return fail(DS_ERR_HIP, "ds_conv2d_shift_backward_data: %s", hipGetErrorString(e));
-    return ok();
+    if (backward_shape(n, c, h, w, k, r, s, stride_h, stride_w, pad_h, pad_w, 5, g) != DS_SUCCESS) return -1;
+    ok();
+    try {
+        return int64_t(backward_workspace_bytes(g));
+    } catch (const std::bad_alloc &) {
+        return -1;
+    }
 }
 
 extern "C" ds_status ds_linear_shift_backward_data(const int32_t *dy, const uint32_t *w_packed,
@@ -321,13 +467,8 @@ extern "C" ds_status ds_linear_shift_backward_data(const int32_t *dy, const uint
                                                    int64_t out_features, int32_t frac_bits,
                                                    uint32_t flags, void *stream)
 {
-    ConvGeom g;
-    ds_status st = check_backward(dy, w_packed, dx, batch, in_features, 1, 1, out_features, 1, 1,
-                                  1, 1, 0, 0, frac_bits, flags, g);
-    if (st != DS_SUCCESS) return st;
-    const hipError_t e = run_backward_data(g, dy, w_packed, dx, static_cast<hipStream_t>(stream));
-    if (e != hipSuccess) return fail(DS_ERR_HIP, "ds_linear_shift_backward_data: %s", hipGetErrorString(e));
-    return ok();
+    return backward_data(dy, w_packed, dx, batch, in_features, 1, 1, out_features, 1, 1, 1, 1, 0, 0, frac_bits, flags,
+                         nullptr, 0, stream, "ds_linear_shift_backward_data");
 }
 
 extern "C" ds_status ds_conv2d_shift_backward_data_describe(int64_t n, int64_t c, int64_t h,

@@ -106,4 +106,10 @@ inline bool overlap(const void *a, int64_t abytes, const void *b, int64_t bbytes
 // runtime. Rejects host pointers and buffers too small for the shape.
 bool device_range_ok(const void *p, int64_t bytes);
 
+
+struct Range {
+    const void *p;
+    int64_t bytes;
+};
+
 }  // namespace ds

@@ -823,7 +823,7 @@ static void plan_splits(const ConvGeom &g, const Variant &v, int &tiles_p, int &
 static bool use_mfma(const ConvGeom &g, const MfmaLayout &l)
 {
     const int fv = forced_variant();
-    return l.fits && (fv == 64 || (fv < 0 && mfma_prefer(g, l)));
+    return l.fits && (fv == 64 || (fv < 0 && mfma_prefer(g, int64_t(g.n) * g.oh * g.ow * g.k * g.crs)));
 }
 
 static bool use_direct(const ConvGeom &g, const Variant &v)
@@ -1340,18 +1340,38 @@ size_t conv_scratch_bytes(const ConvGeom &g0, const OutMap &map, const Padded &p
     return L.direct ? 0 : L.scratch_bytes();
 }
 
+bool matrix_cores_run(const ConvGeom &g)
+{
+    return !rows_path(g, OutMap(), Padded()) && use_mfma(g, mfma_layout(g));
+}
+
+size_t conv_workspace_bytes(const ConvGeom &g)
+{
+    if (rows_path(g, OutMap(), Padded())) return 0;
+    const MfmaLayout l = mfma_layout(g);
+    return use_mfma(g, l) ? l.input_bytes() + l.weight_bytes() : conv_scratch_bytes(g);
+}
+
 hipError_t run_conv(const ConvGeom &g0, const int32_t *x, const uint32_t *wp, const int32_t *wi,
                     const int32_t *bias, int32_t *y, Inner op, hipStream_t st, const Epilogue &epi,
                     const OutMap &map, const Padded &pad, const Workspace &ws)
 {
     if (rows_path(g0, map, pad)) return run_rows(g0, x, wp, wi, bias, y, op, st, epi);
     if (op == Inner::Shift && !(epi.any() && !map.dense())) {
-        const MfmaLayout l = mfma_layout(g0);
-        if (use_mfma(g0, l) && (!ws.ptr || l.bytes() <= ws.bytes)) {
+        MfmaTask t;
+        t.l = mfma_layout(g0);
+        const size_t bytes = t.l.input_bytes() + t.l.weight_bytes();
+        if (use_mfma(g0, t.l) && (!ws.ptr || bytes <= ws.bytes)) {
             void *scratch = ws.ptr;
-            hipError_t e = scratch ? hipSuccess : scratch_alloc(&scratch, l.bytes(), st);
+            hipError_t e = scratch ? hipSuccess : scratch_alloc(&scratch, bytes, st);
             if (e != hipSuccess) return e;
-            e = run_mfma(g0, l, x, wp, bias, y, st, epi, map, scratch);
+            unsigned char *input = static_cast<unsigned char *>(scratch);
+            t.g = g0;
+            t.map = map;
+            t.w = mfma_forward_weights(g0);
+            t.weights = input + t.l.input_bytes();
+            e = mfma_prepare(&t, 1, x, 4, wp, input, bias, y, st);
+            if (e == hipSuccess) e = mfma_multiply(&t, 1, input, bias, y, epi, st);
             if (ws.ptr) return e;
             const hipError_t ef = hipFreeAsync(scratch, st);
             return e != hipSuccess ? e : ef;

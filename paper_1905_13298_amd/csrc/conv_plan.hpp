@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <initializer_list>
 #include <vector>
 
 #include "common.hpp"
@@ -69,6 +70,10 @@ struct Workspace {
     size_t bytes = 0;
 };
 
+// A caller's scratch as a workspace: none when it is NULL or empty; device memory,
+// 256-byte aligned, apart from `others` otherwise.
+ds_status check_workspace(void *scratch, int64_t bytes, std::initializer_list<Range> others, Workspace &ws);
+
 // Enqueue the whole computation of y on `stream`. Exactly one of `wpacked`
 // (Shift) and `wint` (Mul) is used. g.oh and g.ow give the output grid; with
 // the defaults of `map` and `pad` they must be the usual output sizes. With a
@@ -101,6 +106,14 @@ struct GradPhase {
 // out residues with no dx positions; a phase that no tap reaches has g.r == 0
 // or g.s == 0 (its dx positions are zero).
 std::vector<GradPhase> grad_phases(const ConvGeom &g);
+
+// Whether a shift problem of this geometry runs on the matrix cores by itself
+// (not under every forced variant).
+bool matrix_cores_run(const ConvGeom &g);
+
+// Scratch bytes of a call that may take any amount of it (conv_scratch_bytes is
+// what the vector kernels need, the least a call can do with).
+size_t conv_workspace_bytes(const ConvGeom &g);
 
 // Whether run_conv runs g (with `pad`) on the tiled kernel rather than the
 // one-thread-per-output kernel.

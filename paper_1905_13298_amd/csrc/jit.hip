@@ -40,6 +40,7 @@
 #include "common.hpp"
 #include "conv_plan.hpp"
 #include "jit.hpp"
+#include "mfma_conv.hpp"
 #include "tuning.hpp"
 
 // The template code object, embedded by the build (see build.py).
@@ -968,6 +969,10 @@ struct ds_jit_conv {
     OutMap scatter;                 // ... and where they go in dx
     std::vector<ds_jit_conv *> parts;
     std::vector<GradPhase> zeros;   // backward: phases whose dx positions are 0
+    // A plan on the matrix cores: its weight matrices and the packed copy of x in
+    // `matrix`, bias, mul and add as above (init NULL: no bias), no generated code.
+    std::vector<MfmaTask> tasks;
+    unsigned char *matrix = nullptr;
 };
 
 static ds_status destroy_plan(ds_jit_conv *p)
@@ -985,6 +990,10 @@ static ds_status destroy_plan(ds_jit_conv *p)
             const hipError_t f = hipFree(q);
             if (e == hipSuccess) e = f;
         }
+    if (p->matrix) {
+        const hipError_t f = hipFree(p->matrix);
+        if (e == hipSuccess) e = f;
+    }
     delete p;
     if (e != hipSuccess) return fail(DS_ERR_HIP, "ds_jit_conv_destroy: %s", hipGetErrorString(e));
     if (st != DS_SUCCESS) return st;
@@ -998,6 +1007,47 @@ static ds_status upload(int32_t **dst, const int32_t *src, int k, bool zeros)
                          : hipMemcpy(*dst, src, size_t(k) * 4, hipMemcpyHostToDevice);
     if (e != hipSuccess) return fail(DS_ERR_HIP, "upload: %s", hipGetErrorString(e));
     return ok();
+}
+
+// Whether a plan is free to run on the matrix cores: no layout of the generated
+// code is asked for (a split, or a tuning override of it).
+static bool matrix_allowed(int splits)
+{
+    for (const Knob k : {kJitWsplit, kJitSlots, kJitMap, kJitGroupTiles, kJitOrder, kJitTn, kJitPgroups, kJitTranspose})
+        if (tuning(k) >= 0) return false;
+    return splits == 0 && (forced_variant() < 0 || forced_variant() == 64);
+}
+
+// Completes a plan on the matrix cores: allocates its weights and the packed copy
+// of its input, and expands the weights (wp: host packed codes, `words` of them).
+static ds_status build_matrix_plan(ds_jit_conv *p, const uint32_t *wp, size_t words, const Spec &spec)
+{
+    size_t bytes = p->tasks[0].l.input_bytes(), at = bytes;
+    for (const MfmaTask &t : p->tasks) bytes += t.l.weight_bytes();
+    uint32_t *codes = nullptr;
+    hipError_t e = hipMalloc(&p->matrix, bytes);
+    if (e == hipSuccess) e = hipMalloc(&codes, words * 4);
+    if (e == hipSuccess) e = hipMemcpy(codes, wp, words * 4, hipMemcpyHostToDevice);
+    for (MfmaTask &t : p->tasks) {
+        t.weights = p->matrix + at;
+        at += t.l.weight_bytes();
+        p->code_bytes += int64_t(t.l.weight_bytes());
+    }
+    for (size_t i = 0; i < p->tasks.size() && e == hipSuccess; i += kMfmaTasks)
+        e = mfma_prepare(&p->tasks[i], int(std::min<size_t>(kMfmaTasks, p->tasks.size() - i)), nullptr, 4, codes,
+                         nullptr, nullptr, nullptr, nullptr);
+    if (e == hipSuccess) e = hipDeviceSynchronize();
+    if (codes) {
+        const hipError_t f = hipFree(codes);
+        if (e == hipSuccess) e = f;
+    }
+    if (e != hipSuccess) return fail(DS_ERR_HIP, "making the weight matrices: %s", hipGetErrorString(e));
+    ds_status st = ok();
+    const int K = p->tasks[0].g.k;
+    if (spec.bias) st = upload(&p->init, spec.bias, K, false);
+    if (st == DS_SUCCESS && spec.mul) st = upload(&p->mul, spec.mul, K, false);
+    if (st == DS_SUCCESS && spec.add) st = upload(&p->add, spec.add, K, false);
+    return st;
 }
 
 // Generates, loads and completes the plan of one planned spec (host bias, mul
@@ -1105,6 +1155,32 @@ extern "C" ds_status ds_jit_conv_create(const uint32_t *w_packed, const int32_t 
                            stride_h, stride_w, pad_h, pad_w, flags, splits};
         ds_status st = plan_spec(a, sp);
         if (st != DS_SUCCESS) return st;
+        const ConvGeom &g = sp.xt ? sp.lin : sp.g;
+        MfmaTask t;
+        t.g = g;
+        t.w = mfma_forward_weights(g);
+        if (matrix_allowed(splits)) t.l = mfma_layout(g);
+        if (t.l.fits && (forced_variant() == 64 ||
+                         mfma_prefer_plan(&t, 1, int64_t(g.n) * g.c * g.h * g.w, int64_t(g.n) * g.oh * g.ow * g.k * g.crs))) {
+            if (sp.act_bytes < 4) t.l.dig_bytes = 0;   // no input leaves the range of one digit
+            ds_jit_conv *p = new ds_jit_conv;
+            p->sp = sp;
+            p->tasks.push_back(t);
+            if (hipGetDevice(&p->device) != hipSuccess) {
+                delete p;
+                return fail(DS_ERR_HIP, "no HIP device");
+            }
+            st = build_matrix_plan(p, w_packed, size_t(g.k) * size_t(row_words_bits(g.crs, g.bits)), sp);
+            if (st != DS_SUCCESS) {
+                const std::string msg = last_error();
+                destroy_plan(p);
+                return fail(st, "%s", msg.c_str());
+            }
+            p->sp.bias = p->sp.mul = p->sp.add = nullptr;
+            p->sp.wp = nullptr;
+            *plan = p;
+            return ok();
+        }
         return build_plan(sp, plan);
     } catch (const std::bad_alloc &) {
         return fail(DS_ERR_HIP, "out of host memory");
@@ -1149,6 +1225,20 @@ extern "C" ds_status ds_jit_conv_backward_data_create(const uint32_t *w_packed, 
         }
         for (const GradPhase &ph : phases)
             if (ph.g.r == 0 || ph.g.s == 0) p->zeros.push_back(ph);
+        bool zeros = false;
+        int64_t terms = 0;
+        if (matrix_allowed(splits) && mfma_gradient_tasks(g, p->tasks, zeros, terms) &&
+            (forced_variant() == 64 || mfma_prefer_plan(p->tasks.data(), p->tasks.size(), int64_t(g.n) * g.k * g.oh * g.ow, terms))) {
+            st = build_matrix_plan(p, w_packed, size_t(g.k) * size_t(rw), Spec());
+            if (st != DS_SUCCESS) {
+                const std::string msg = last_error();
+                destroy_plan(p);
+                return fail(st, "%s", msg.c_str());
+            }
+            *plan = p;
+            return ok();
+        }
+        p->tasks.clear();
         // Stride phases fused into one kernel when they can be (no split of the
         // reduction: the wave split supplies the parallelism); else one per phase.
         {
@@ -1412,7 +1502,7 @@ extern "C" ds_status ds_jit_conv_run(const ds_jit_conv *plan, const void *xv,
     if (hipGetDevice(&dev) != hipSuccess || dev != plan->device)
         return fail(DS_ERR_INVALID_ARG, "the plan was made on device %d, the current device is %d", plan->device, dev);
     // Forward: x [n][c][h][w] -> y [n][k][oh][ow]; input gradient: dy -> dx of the forward layer.
-    const ConvGeom &g = plan->backward ? plan->fwd : plan->sp.g;
+    const ConvGeom &g = plan->backward ? plan->fwd : !plan->tasks.empty() ? plan->tasks[0].g : plan->sp.g;
     const int64_t fx = int64_t(g.n) * g.c * g.h * g.w * (plan->backward ? 4 : plan->sp.act_bytes);
     const int64_t fy = int64_t(g.n) * g.k * g.oh * g.ow * 4;
     const int64_t xb = plan->backward ? fy : fx, yb = plan->backward ? fx : fy;
@@ -1426,7 +1516,24 @@ extern "C" ds_status ds_jit_conv_run(const ds_jit_conv *plan, const void *xv,
 
     hipStream_t st = static_cast<hipStream_t>(stream);
     hipError_t e = hipSuccess;
-    if (!plan->backward) {
+    if (!plan->tasks.empty()) {
+        Epilogue epi;
+        if (!plan->backward) {
+            epi.mul = plan->mul;
+            epi.add = plan->add;
+            epi.res = residual;
+            epi.mul_shift = plan->sp.mul_shift;
+            epi.relu = plan->sp.relu;
+        }
+        if (!plan->zeros.empty()) e = run_fill_zero(y, int64_t(g.n) * g.c * g.h * g.w, st);
+        for (size_t i = 0; i < plan->tasks.size() && e == hipSuccess; i += kMfmaTasks) {
+            const MfmaTask *t = &plan->tasks[i];
+            const int n = int(std::min<size_t>(kMfmaTasks, plan->tasks.size() - i));
+            e = mfma_prepare(t, n, i ? nullptr : xv, plan->backward ? 4 : plan->sp.act_bytes, nullptr, plan->matrix,
+                             plan->init, y, st);
+            if (e == hipSuccess) e = mfma_multiply(t, n, plan->matrix, plan->init, y, epi, st);
+        }
+    } else if (!plan->backward) {
         e = run_part(plan, x, residual, y, xb, yb, st);
     } else {
         // Positions no tap reaches are zero: all of dx is cleared densely first.
@@ -1450,6 +1557,13 @@ extern "C" ds_status ds_jit_conv_query(const ds_jit_conv *plan, int64_t *code_by
         seg += q->sp.nseg;
         sp = std::max(sp, q->sp.nsplit);
     }
+    if (!plan->tasks.empty()) {
+        seg = sp = 0;
+        for (const MfmaTask &t : plan->tasks) {
+            seg += t.l.tiles_k * t.l.splits;
+            sp = std::max(sp, t.l.splits);
+        }
+    }
     if (code_bytes) *code_bytes = plan->code_bytes;
     if (segments) *segments = seg;
     if (splits) *splits = sp;
@@ -1460,6 +1574,14 @@ extern "C" ds_status ds_jit_conv_layout(const ds_jit_conv *plan, int32_t *channe
                                         int32_t *pixel_groups, int32_t *pixel_tiles, int32_t *transposed)
 {
     if (!plan) return fail(DS_ERR_NULL_POINTER, "plan must not be NULL");
+    if (!plan->tasks.empty()) {
+        if (channels) *channels = 64;
+        if (wsplit) *wsplit = 1;
+        if (pixel_groups) *pixel_groups = 4;
+        if (pixel_tiles) *pixel_tiles = plan->tasks[0].l.tiles_p;
+        if (transposed) *transposed = 0;
+        return ok();
+    }
     const ds_jit_conv *k = plan->backward ? (plan->parts.empty() ? nullptr : plan->parts.front()) : plan;
     if (channels) *channels = k ? k->sp.tn : kTN;
     if (wsplit) *wsplit = k ? k->sp.wsplit : 1;
@@ -1468,6 +1590,8 @@ extern "C" ds_status ds_jit_conv_layout(const ds_jit_conv *plan, int32_t *channe
     if (transposed) *transposed = k && k->sp.xt ? 1 : 0;
     return ok();
 }
+
+extern "C" int32_t ds_jit_conv_matrix_cores(const ds_jit_conv *plan) { return plan && !plan->tasks.empty() ? 1 : 0; }
 
 // ---------------------------------------------------------------------------
 // Multiplication plans: the comparison operator of Section 6's timing (a

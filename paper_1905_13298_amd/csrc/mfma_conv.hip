@@ -30,7 +30,9 @@
 
 #include <algorithm>
 #include <cstdlib>
+#include <type_traits>
 
+#include "common.hpp"
 #include "conv_plan.hpp"
 #include "fastdiv.hpp"
 #include "mfma_conv.hpp"
@@ -52,7 +54,7 @@ constexpr int kTileBytes = kFp6 * 1536 + kFp4 * 1024;  // one 32-row tile, 64 re
 constexpr int kStageBytes = 2 * kTileBytes;            // a workgroup's 64 rows
 constexpr int kXpBytes = 88;         // per pixel and 32 channels: 4 nibble planes, h0
 constexpr int kDigBytes = 72;        // the same for h1, h2, h3
-constexpr int kOutPitch = 65;         // LDS words per pixel of the output tile
+constexpr int kOutPitch = 68;         // LDS words per pixel of the output tile: 16-byte rows, no bank conflicts
 constexpr uint32_t kOOB = 0x80000000u;
 constexpr int kRsrcWord3 = 0x00020000;
 constexpr int kLimit = (1 << 24) - 1;  // a float sum of integers stays exact up to 2^24
@@ -130,11 +132,9 @@ __device__ __forceinline__ void block_at(const Reduction &d, int ch, int half, i
 struct PackParams {
     // The packed copy's pixels (n, i, j) and where they come from: x row i * sh,
     // column j * sw - pw + the tap column folded into the channel.
-    int N, C, H, W, HW;          // x
-    int PH, PW, NP, PHW;         // the packed copy
-    int sh, sw, pw, US;
-    int CB, nblk;
-    int64_t xstride_n;
+    int C, W, HW;                // x
+    int NP, PHW;                 // the packed copy
+    int sh, sw, pw, US, nblk;
     FastDiv div_phw, div_pw, div_us;
 };
 
@@ -149,10 +149,18 @@ __device__ __forceinline__ void put6(uint32_t (&o)[6], int e, uint32_t v)
 // row tile) and their bounds. The codes are decoded once into LDS; then each of four
 // groups of 64 threads builds two fp6 and two fp4 matrices, a thread the 32 weights
 // of one lane's share.
-__device__ void prep_weights(const uint32_t *__restrict__ wp, int K, int R, int S, int wpr, const CodeFmt &fmt,
-                             const Reduction &d, int block, unsigned char *__restrict__ wa,
-                             Bounds *__restrict__ bounds)
+struct WeightTask {
+    Reduction d;
+    MfmaWeights w;
+    CodeFmt fmt;
+    int K, blocks;
+    unsigned char *wa;
+    Bounds *bounds;
+};
+
+__device__ void prep_weights(const uint32_t *__restrict__ wp, const WeightTask &t, int block)
 {
+    const Reduction &d = t.d;
     constexpr int kPitch = 80;   // bytes per row of codes: 16-byte reads, spread over the banks
     __shared__ uint32_t lut[4][32];
     __shared__ __align__(16) unsigned char codes[32][kPitch];
@@ -176,18 +184,21 @@ __device__ void prep_weights(const uint32_t *__restrict__ wp, int K, int R, int 
         const int row = tid >> 3, seg = tid & 7, k = mblk * kRows + mt * 32 + row;
         int cb, r, s;
         block_at(d, ch, seg >> 2, cb, r, s);
-        const uint32_t *wrow = wp + int64_t(min(k, K - 1)) * wpr;
+        const int kc = min(k, t.K - 1), tap = t.w.r0 + r * t.w.dr;
         uint32_t c8[8];
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
             const int c = cb * kBlockK + (seg & 3) * 8 + e;
-            int col = (c * R + r) * S + s;
+            const bool ok = k < t.K && cb < d.CB && c < d.C;
+            int cl = ok ? c : 0, sx = s;
             if (d.US > 1) {
-                const int cl = c / d.US;
-                col = (cl * R + r) * S + (c - cl * d.US);
+                const int q = cl / d.US;
+                sx = cl - q * d.US;
+                cl = q;
             }
-            const bool ok = k < K && cb < d.CB && c < d.C;
-            const uint32_t code = fmt.at(wrow, ok ? col : 0);
+            const int prow = t.w.adjoint ? cl : kc, pch = t.w.adjoint ? kc : cl;
+            const int col = ok ? (pch * t.w.R + tap) * t.w.S + t.w.s0 + sx * t.w.ds : 0;
+            const uint32_t code = t.fmt.at(wp + int64_t(prow) * t.w.wpr, col);
             c8[e] = ok ? code : 15u;
         }
         v2i w{};
@@ -217,7 +228,7 @@ __device__ void prep_weights(const uint32_t *__restrict__ wp, int K, int R, int 
             q0 += sft >= 6 && sft < 15 ? 65536 >> sft : 0;
         }
     }
-    unsigned char *st = wa + int64_t(unit) * kStageBytes;
+    unsigned char *st = t.wa + int64_t(unit) * kStageBytes;
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
         const int m = 2 * group + i;
@@ -237,7 +248,7 @@ __device__ void prep_weights(const uint32_t *__restrict__ wp, int K, int R, int 
             q0 = max(q0, __shfl_xor(q0, off));
             r1 = max(r1, __shfl_xor(r1, off));
         }
-        if (lane == 0) bounds[block] = Bounds{p0, q0, r1, 0};
+        if (lane == 0) t.bounds[block] = Bounds{p0, q0, r1, 0};
     }
 }
 
@@ -248,9 +259,9 @@ __device__ __forceinline__ uint32_t e2m3(int h) { return h < 0 ? uint32_t(-h) | 
 // nibbles (bits 4p .. 4p+3 of the 32 channels, channel e in nibble e) and h0; h1
 // .. h3 where some H of the block needs them. hmax[cb][block]: the largest |H|, or
 // 255 when one lies outside -16 .. 15.
-__device__ void pack_x(const int32_t *__restrict__ x, const PackParams &p, int block,
-                       unsigned char *__restrict__ xp, unsigned char *__restrict__ dig,
-                       unsigned char *__restrict__ hmax)
+template <typename T>
+__device__ void pack_x(const T *__restrict__ x, const PackParams &p, int block, unsigned char *__restrict__ xp,
+                       unsigned char *__restrict__ dig, unsigned char *__restrict__ hmax)
 {
     __shared__ int red[4];
     const int cb = block / p.nblk, pb = block - cb * p.nblk;
@@ -258,7 +269,7 @@ __device__ void pack_x(const int32_t *__restrict__ x, const PackParams &p, int b
     const bool in = pix < p.NP;
     const int pc = min(pix, p.NP - 1);
     const int n = fdiv(pc, p.div_phw), rem = pc - n * p.PHW;
-    const int i = fdiv(rem, p.div_pw), j = rem - i * p.PW;
+    const int i = fdiv(rem, p.div_pw), j = rem - i * int(p.div_pw.d);
     const int64_t base = int64_t(n) * p.C * p.HW + int64_t(i) * p.sh * p.W + j * p.sw - p.pw;
     // Loads past the last channel (or, with folded tap columns, outside the row) are
     // redirected to a valid element and replaced by 0: no branch around any of them.
@@ -273,7 +284,7 @@ __device__ void pack_x(const int32_t *__restrict__ x, const PackParams &p, int b
             if (cc >= p.C * p.US || cl != col) v[e] = 0;
         }
     } else {
-        if (p.HW == 1 && c0 + kBlockK <= p.C && (p.C & 3) == 0 && (reinterpret_cast<uintptr_t>(x) & 15) == 0) {
+        if (sizeof(T) == 4 && p.HW == 1 && c0 + kBlockK <= p.C && (p.C & 3) == 0 && (reinterpret_cast<uintptr_t>(x) & 15) == 0) {
             // Row-major inputs of a LinearShift: the 32 channels are consecutive.
             const v4i *src = reinterpret_cast<const v4i *>(x + base + c0);
 #pragma unroll
@@ -283,7 +294,7 @@ __device__ void pack_x(const int32_t *__restrict__ x, const PackParams &p, int b
                 for (int t = 0; t < 4; ++t) v[4 * e + t] = q[t];
             }
         } else {
-            const int32_t *src = x + base + int64_t(c0) * p.HW;
+            const T *src = x + base + int64_t(c0) * p.HW;
             const int last = p.C - 1 - c0;
 #pragma unroll
             for (int e = 0; e < kBlockK; ++e) {
@@ -380,17 +391,36 @@ __device__ void fill_y(const FillParams &f, int block)
     }
 }
 
-__global__ void __launch_bounds__(256)
-mfma_prep_kernel(const int32_t *__restrict__ x, const uint32_t *__restrict__ wp, int K, int R, int S,
-                 int wpr, CodeFmt fmt, Reduction d, PackParams p, int wblocks,
-                 unsigned char *__restrict__ wa, Bounds *__restrict__ bounds,
-                 unsigned char *__restrict__ xp, unsigned char *__restrict__ dig,
-                 unsigned char *__restrict__ hmax, FillParams f)
+struct PrepArgs {
+    const void *x;
+    const uint32_t *wp;
+    unsigned char *xp, *dig, *hmax;
+    PackParams p;
+    int wblocks, pblocks;            // of all tasks together; blocks past both fill
+    int ntasks;
+    WeightTask w[kMfmaTasks];
+    FillParams f[kMfmaTasks];
+};
+
+template <typename T>
+__global__ void __launch_bounds__(256) mfma_prep_kernel(const PrepArgs a)
 {
-    const int block = int(blockIdx.x), pack = block - wblocks, fill = pack - p.CB * p.nblk;
-    if (block < wblocks) prep_weights(wp, K, R, S, wpr, fmt, d, block, wa, bounds);
-    else if (fill < 0) pack_x(x, p, pack, xp, dig, hmax);
-    else fill_y(f, fill);
+    int block = int(blockIdx.x);
+    if (block < a.wblocks) {
+        int i = 0;
+        while (block >= a.w[i].blocks) block -= a.w[i++].blocks;
+        prep_weights(a.wp, a.w[i], block);
+        return;
+    }
+    block -= a.wblocks;
+    if (block < a.pblocks) {
+        pack_x(static_cast<const T *>(a.x), a.p, block, a.xp, a.dig, a.hmax);
+        return;
+    }
+    block -= a.pblocks;
+    int i = 0;
+    while (block >= a.f[i].blocks) block -= a.f[i++].blocks;
+    fill_y(a.f[i], block);
 }
 
 // ---------------------------------------------------------------------------
@@ -405,8 +435,17 @@ struct MfmaParams {
     int atomic_out, fuse_epi, rowmajor;
     int ybase, ynst, ykst, yrst, ycst;
     uint32_t xp_bytes;
-    Epilogue epi;
     FastDiv div_ohow, div_ow;
+    const unsigned char *wa;
+    const Bounds *bounds;
+};
+
+struct ProductArgs {
+    const unsigned char *xp, *dig, *hmax;
+    const int32_t *bias;             // of the tasks that are not split
+    int32_t *y;
+    Epilogue epi;
+    MfmaParams p[kMfmaTasks];
 };
 
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc(const void *p, uint32_t bytes)
@@ -440,19 +479,22 @@ __device__ __forceinline__ v16f mms(v8i a, v8i b, v16f c, int scales)
 }
 
 __global__ void __launch_bounds__(256, 2)
-mfma_conv_kernel(const unsigned char *__restrict__ xp, const unsigned char *__restrict__ dig,
-                 const unsigned char *__restrict__ hmax, const unsigned char *__restrict__ wa,
-                 const Bounds *__restrict__ bounds, const int32_t *__restrict__ bias,
-                 int32_t *__restrict__ y, const MfmaParams p)
+mfma_conv_kernel(const ProductArgs a)
 {
+    const MfmaParams &p = a.p[blockIdx.z];
+    const Epilogue &epi = a.epi;
+    int32_t *const y = a.y;
+    const int32_t *const bias = p.atomic_out ? nullptr : a.bias;
+    const unsigned char *const hmax = a.hmax;
     __shared__ __align__(16) unsigned char lds[2 * kStageBytes];
     const int lane = threadIdx.x & 63, half = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));
     // Blocks are dealt to the 8 XCDs in turn: each XCD takes an eighth of the tiles, all
     // row blocks of a pixel tile one after the other, so that they read its inputs
     // through one L2.
-    const int at = (int(blockIdx.x) & 7) * int(gridDim.x >> 3) + int(blockIdx.x >> 3);
-    if (at >= p.tiles_p * p.tiles_k) return;
+    const int tiles = p.tiles_p * p.tiles_k, share = (tiles + 7) >> 3, place = int(blockIdx.x >> 3);
+    const int at = (int(blockIdx.x) & 7) * share + place;
+    if (place >= share || at >= tiles) return;
     const int tp = at / p.tiles_k, mblk = at - tp * p.tiles_k;
     const int ch0 = int(blockIdx.y) * p.cps, ch1 = min(p.d.nchunks, ch0 + p.cps);
     const int CB = p.d.CB, R = p.d.R, S = p.d.S;
@@ -476,8 +518,8 @@ mfma_conv_kernel(const unsigned char *__restrict__ xp, const unsigned char *__re
         const int ih = (at0[t] >> 16) + r, iw = int(int16_t(at0[t])) + s;
         return unsigned(ih) < unsigned(p.PH) && unsigned(iw) < unsigned(p.PW) ? pb[t] + r * p.PW + s : -1;
     };
-    const __amdgpu_buffer_rsrc_t xr = rsrc(xp, p.xp_bytes);
-    const unsigned char *wrow = wa + int64_t(mblk) * p.d.nchunks * kStageBytes;
+    const __amdgpu_buffer_rsrc_t xr = rsrc(a.xp, p.xp_bytes);
+    const unsigned char *wrow = p.wa + int64_t(mblk) * p.d.nchunks * kStageBytes;
     const __amdgpu_buffer_rsrc_t wr = rsrc(wrow, uint32_t(p.d.nchunks) * uint32_t(kStageBytes));
     const int np16 = p.NP * 16, np64 = p.NP * 64, np80 = p.NP * 80, cbs = p.NP * kXpBytes;
 
@@ -496,7 +538,7 @@ mfma_conv_kernel(const unsigned char *__restrict__ xp, const unsigned char *__re
         }
     };
     uint32_t off[2], base;   // byte of the pixel in a plane of 16-byte entries; of the block
-    auto place = [&]() {
+    auto locate = [&]() {
         base = uint32_t(cb) * uint32_t(cbs);
 #pragma unroll
         for (int t = 0; t < 2; ++t) {
@@ -517,12 +559,14 @@ mfma_conv_kernel(const unsigned char *__restrict__ xp, const unsigned char *__re
             xh[t] = __builtin_amdgcn_raw_buffer_load_b64(xr, off[t] == kOOB ? kOOB : (off[t] + base) >> 1, np80, 0);
         }
     };
+    // (past the last chunk: zeros from outside the buffer, so that a chunk always has
+    // the same number of loads in flight)
     auto stage = [&](int ch, int buf) {
         const uint32_t from = uint32_t(ch) * uint32_t(kStageBytes), mine = uint32_t(wave * 1024 + lane * 16);
 #pragma unroll
         for (int i = 0; i < kStageBytes / 4096; ++i)
             __builtin_amdgcn_raw_ptr_buffer_load_lds(wr, (lds_ptr_t)(lds + buf * kStageBytes + i * 4096 + wave * 1024),
-                                                     16, mine, from + uint32_t(i) * 4096u, 0, 0);
+                                                     16, ch < ch1 ? mine : kOOB, from + uint32_t(i) * 4096u, 0, 0);
     };
 
     v16f c0[2][2], c1[2][2];
@@ -547,12 +591,14 @@ mfma_conv_kernel(const unsigned char *__restrict__ xp, const unsigned char *__re
 #pragma unroll
             for (int m = 0; m < 2; ++m)
 #pragma unroll
-                for (int g = 0; g < 4; ++g)
+                for (int g = 0; g < 4; ++g) {
+                    v4i v;
 #pragma unroll
                     for (int i = 0; i < 4; ++i)
-                        out[(t * 32 + (lane & 31)) * kOutPitch + m * 32 + g * 8 + half * 4 + i] =
-                            int(uint32_t(int(c0[m][t][g * 4 + i] * 32.0f)) +
-                                (uint32_t(int(c1[m][t][g * 4 + i] * 16.0f)) << 7));
+                        v[i] = int(uint32_t(int(c0[m][t][g * 4 + i] * 32.0f)) +
+                                   (uint32_t(int(c1[m][t][g * 4 + i] * 16.0f)) << 7));
+                    *reinterpret_cast<v4i *>(out + (t * 32 + (lane & 31)) * kOutPitch + m * 32 + g * 8 + half * 4) = v;
+                }
         // Written and read back by the same wave, whose LDS accesses run in order.
         __builtin_amdgcn_wave_barrier();
         // Sixteen outputs a lane at a time: the channels of one pixel (64 consecutive
@@ -571,81 +617,109 @@ mfma_conv_kernel(const unsigned char *__restrict__ xp, const unsigned char *__re
         const int32_t *src = out + (byrow ? lane : lane * kOutPitch);
         const int sstep = byrow ? kOutPitch : 1;
         // Lane l holds the parameters of channel l of the tile.
-        const bool affine = last && p.fuse_epi && p.epi.mul;
+        const bool affine = last && p.fuse_epi && epi.mul;
         int pbias = 0, pmul = 0, padd = 0;
         if (kb + lane < p.K) {
             if (last && bias) pbias = bias[kb + lane];
-            if (affine) pmul = p.epi.mul[kb + lane];
-            if (affine && p.epi.add) padd = p.epi.add[kb + lane];
+            if (affine) pmul = epi.mul[kb + lane];
+            if (affine && epi.add) padd = epi.add[kb + lane];
         }
-        const bool res = last && p.fuse_epi && p.epi.res, relu = last && p.fuse_epi && p.epi.relu;
+        const bool res = last && p.fuse_epi && epi.res, relu = last && p.fuse_epi && epi.relu;
+        // (Conditions stand outside the loops over the sixteen: a branch per output took
+        // 7 us of a tile that the stores take 2 us of.)
         for (int j0 = 0; j0 < count; j0 += 16, o += 16 * ostep, src += 16 * sstep) {
             uint32_t v[16];
+            if (byrow) {
 #pragma unroll
-            for (int j = 0; j < 16; ++j) v[j] = uint32_t(src[j * sstep]) << shift;
+                for (int j = 0; j < 16; ++j) v[j] = uint32_t(src[j * kOutPitch]) << shift;
+            } else {
+#pragma unroll
+                for (int j = 0; j < 16; j += 4) {
+                    const v4i q = *reinterpret_cast<const v4i *>(src + j);
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) v[j + i] = uint32_t(q[i]) << shift;
+                }
+            }
             if (!in) continue;
             const int left = count - j0;
+            int32_t *yp = y + o;
             if (p.atomic_out) {
 #pragma unroll
                 for (int j = 0; j < 16; ++j)
-                    if (j < left) atomicAdd(reinterpret_cast<unsigned int *>(y + o + j * ostep), v[j]);
+                    if (j < left) atomicAdd(reinterpret_cast<unsigned int *>(yp + j * ostep), v[j]);
                 continue;
             }
             if (more) {
 #pragma unroll
                 for (int j = 0; j < 16; ++j)
-                    if (j < left)
-                        v[j] += uint32_t(__hip_atomic_load(y + o + j * ostep, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+                    v[j] += uint32_t(__hip_atomic_load(yp + min(j, left - 1) * ostep, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
             }
-            int32_t rv[16];
-            if (res) {
+            if (byrow) {
 #pragma unroll
-                for (int j = 0; j < 16; ++j) rv[j] = p.epi.res[o + min(j, left - 1) * ostep];
+                for (int j = 0; j < 16; ++j) v[j] += uint32_t(pbias);
+            } else if (bias) {
+#pragma unroll
+                for (int j = 0; j < 16; ++j) v[j] += uint32_t(__builtin_amdgcn_readlane(pbias, (j0 + j) & 63));
             }
+            if (affine) {
 #pragma unroll
-            for (int j = 0; j < 16; ++j) {
-                v[j] += uint32_t(byrow ? pbias : __builtin_amdgcn_readlane(pbias, (j0 + j) & 63));
-                if (affine) {
+                for (int j = 0; j < 16; ++j) {
                     const int mul = byrow ? pmul : __builtin_amdgcn_readlane(pmul, (j0 + j) & 63);
                     const int add = byrow ? padd : __builtin_amdgcn_readlane(padd, (j0 + j) & 63);
-                    v[j] = uint32_t((int64_t(int32_t(v[j])) * mul) >> p.epi.mul_shift) + uint32_t(add);
+                    v[j] = uint32_t((int64_t(int32_t(v[j])) * mul) >> epi.mul_shift) + uint32_t(add);
                 }
-                if (res) v[j] += uint32_t(rv[j]);
-                if (relu && int32_t(v[j]) < 0) v[j] = 0u;
-                if (j < left) y[o + j * ostep] = int32_t(v[j]);
+            }
+            if (res) {
+                const int32_t *rp = epi.res + o;
+                int32_t rv[16];
+#pragma unroll
+                for (int j = 0; j < 16; ++j) rv[j] = rp[min(j, left - 1) * ostep];
+#pragma unroll
+                for (int j = 0; j < 16; ++j) v[j] += uint32_t(rv[j]);
+            }
+            if (relu) {
+#pragma unroll
+                for (int j = 0; j < 16; ++j) v[j] = uint32_t(max(int32_t(v[j]), 0));
+            }
+            if (left >= 16) {
+#pragma unroll
+                for (int j = 0; j < 16; ++j, yp += ostep) *yp = int32_t(v[j]);
+            } else {
+#pragma unroll
+                for (int j = 0; j < 16; ++j)
+                    if (j < left) yp[j * ostep] = int32_t(v[j]);
             }
         }
     };
 
     const int lane8x = (lane ^ 1) * 8;
     const int sc = kScales;
-    if (ch0 >= ch1) return;
+    if (ch0 >= ch1) return;   // a task with fewer parts than the launch
+    // Largest |H| of the images this tile reads (255: their h1 .. h3 are needed). The
+    // first entries are fetched before everything else, so that their maximum is
+    // formed while the first chunk is on its way.
+    const int hb0 = fdiv(tp * kPix, p.div_ohow) * p.PHW / 256;
+    const int hnb = ((fdiv(min(tp * kPix + kPix, p.NQ) - 1, p.div_ohow) + 1) * p.PHW - 1) / 256 - hb0 + 1;
+    auto hload = [&](int i) {
+        const int b = i / hnb;
+        return i < hnb * CB ? int(hmax[b * p.nblk + hb0 + i - b * hnb]) : 0;
+    };
+    int hm = hload(lane);
     stage(ch0, 0);
     seek(ch0);
-    place();
+    locate();
 #pragma unroll
     for (int pl = 0; pl < 4; ++pl) load_plane(pl);
     load_h();
-    // Largest |H| of the images this tile reads (255: their h1 .. h3 are needed).
-    int hm = 0;
-    {
-        const int nlo = fdiv(tp * kPix, p.div_ohow), nhi = fdiv(min(tp * kPix + kPix, p.NQ) - 1, p.div_ohow);
-        const int b0 = nlo * p.PHW / 256, b1 = ((nhi + 1) * p.PHW - 1) / 256, nb = b1 - b0 + 1;
-        for (int i = lane; i < nb * CB; i += 64) {
-            const int cb = i / nb;
-            hm = max(hm, int(hmax[cb * p.nblk + b0 + i - cb * nb]));
-        }
-        for (int off = 32; off > 0; off >>= 1) hm = max(hm, __shfl_xor(hm, off));
-        hm = __builtin_amdgcn_readfirstlane(hm);
-    }
-    const bool digits = hm == 255;
-    hm = min(hm, 16);
-
-    const __amdgpu_buffer_rsrc_t dr = rsrc(dig, uint32_t(CB) * uint32_t(p.NP) * uint32_t(kDigBytes));
-    const Bounds *bd = bounds + 2 * mblk * p.d.nchunks;
+    const __amdgpu_buffer_rsrc_t dr = rsrc(a.dig, uint32_t(CB) * uint32_t(p.NP) * uint32_t(kDigBytes));
+    const Bounds *bd = p.bounds + 2 * mblk * p.d.nchunks;
     // Pass 0 forms the products of the nibble planes and h0; passes 1 .. 3, for
     // inputs beyond 20 bits, those of h1, h2, h3, 5 bits further up each.
-    const int passes = digits ? 4 : 1;
+    for (int i = lane + 64; i - lane < hnb * CB; i += 64) hm = max(hm, hload(i));
+    for (int off = 32; off > 0; off >>= 1) hm = max(hm, __shfl_xor(hm, off));
+    hm = __builtin_amdgcn_readfirstlane(hm);
+    const int passes = hm == 255 ? 4 : 1;
+    hm = min(hm, 16);
     int pass = 0, ch = ch0;
     bool more = false;
     for (;;) {
@@ -668,7 +742,7 @@ mfma_conv_kernel(const unsigned char *__restrict__ xp, const unsigned char *__re
                 asm volatile("s_waitcnt vmcnt(12) lgkmcnt(0)" ::: "memory");
                 __builtin_amdgcn_s_barrier();
                 asm volatile("" ::: "memory");
-                stage(min(ch + 1, ch1 - 1), (ch + 1 - ch0) & 1);
+                stage(ch + 1, (ch + 1 - ch0) & 1);
                 asm volatile("" ::: "memory");
                 const unsigned char *buf = lds + ((ch - ch0) & 1) * kStageBytes;
                 auto a6 = [&](v8i (&a)[2], int i) {
@@ -676,114 +750,156 @@ mfma_conv_kernel(const unsigned char *__restrict__ xp, const unsigned char *__re
                     for (int m = 0; m < 2; ++m)
                         a[m] = wide(*reinterpret_cast<const v4i *>(buf + fp6_lo(i, m) + lane * 16),
                                     *reinterpret_cast<const v2i *>(buf + fp6_hi(i, m) + (m ? lane8x : lane * 8)));
-                    __builtin_amdgcn_sched_barrier(0);
                 };
                 auto a4 = [&](v8i (&a)[2], int i) {
 #pragma unroll
                     for (int m = 0; m < 2; ++m)
                         a[m] = wide(*reinterpret_cast<const v4i *>(buf + fp4_at(i, m) + lane * 16));
-                    __builtin_amdgcn_sched_barrier(0);
                 };
                 // Where the next chunk's inputs are.
                 if (ch + 1 < ch1) {
                     step();
                     if (!p.d.even) step();
-                    place();
+                    locate();
                 } else {
                     off[0] = off[1] = kOOB;
                 }
                 constexpr int kDig = 0x33333333, kBit = 0x22222222;
-                auto up = [&](v4i (&u)[2], int pl) {
+                // A step: the products of one matrix, the reads of the next one's share, and
+                // the next digits, cut out while the products run. `region` ends it (the
+                // scheduler keeps a step's instructions together: four products, with
+                // vector instructions between them).
+                v8i aa[2], ab[2];
+                v4i d0[2], d1[2], u[2];
+                auto cut = [&](v4i (&d)[2], const v4i &x0, const v4i &x1, int mask) {
+                    d[0] = x0 & mask;
+                    d[1] = x1 & mask;
+                };
+                auto up = [&](int pl) {
 #pragma unroll
                     for (int t = 0; t < 2; ++t)
 #pragma unroll
                         for (int g = 0; g < 4; ++g) u[t][g] = int(uint32_t(xw[t][pl][g]) >> 2);
                 };
-                auto fp4_step = [&](const v8i (&a)[2], const v4i &d0, const v4i &d1, int mask) {
+                auto region = [&](auto products) {
+                    // (a count of the products the step holds, in twos of two and three
+                    // vector instructions)
+                    constexpr int n = decltype(products)::value;
+                    __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);
 #pragma unroll
-                    for (int m = 0; m < 2; ++m) {
-                        c0[m][0] = mms<kE2M1, kE2M1, kM4>(a[m], wide(d0 & mask), c0[m][0], sc);
-                        c0[m][1] = mms<kE2M1, kE2M1, kM4>(a[m], wide(d1 & mask), c0[m][1], sc);
+                    for (int i = 0; i < n; ++i) {
+                        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                        __builtin_amdgcn_sched_group_barrier(0x002, 5, 0);
                     }
                     __builtin_amdgcn_sched_barrier(0);
                 };
-                auto fp6_step = [&](const v8i (&a)[2], const v4i &d0, const v4i &d1) {
+                using Four = std::integral_constant<int, 4>;
+                using Eight = std::integral_constant<int, 8>;
+                auto bits = [&](const v8i (&a)[2], const v4i (&d)[2]) {     // S_b, P_0
 #pragma unroll
-                    for (int m = 0; m < 2; ++m) {
-                        c0[m][0] = mm<kE3M2, kE2M1>(a[m], wide(d0 & kDig), c0[m][0]);
-                        c0[m][1] = mm<kE3M2, kE2M1>(a[m], wide(d1 & kDig), c0[m][1]);
-                    }
-                    __builtin_amdgcn_sched_barrier(0);
+                    for (int m = 0; m < 2; ++m)
+#pragma unroll
+                        for (int t = 0; t < 2; ++t) c0[m][t] = mms<kE2M1, kE2M1, kM4>(a[m], wide(d[t]), c0[m][t], sc);
                 };
-                // Each matrix is read one step ahead of its products; a plane's registers
-                // take the next chunk's plane as soon as its last digit is cut out.
-                v8i aa[2], ab[2];
-                v4i u[2];
+                auto powers = [&](const v8i (&a)[2], const v4i (&d)[2]) {   // P_2 ..
+#pragma unroll
+                    for (int m = 0; m < 2; ++m)
+#pragma unroll
+                        for (int t = 0; t < 2; ++t) c0[m][t] = mm<kE3M2, kE2M1>(a[m], wide(d[t]), c0[m][t]);
+                };
                 a4(aa, 0);
-                a4(ab, 1);
-                fp4_step(aa, xw[0][0], xw[1][0], kDig);    // P_0
-                a6(aa, kP2);
-                fp4_step(ab, xw[0][0], xw[1][0], kBit);    // S_1
-                a4(ab, 2);
-                up(u, 0);
-                load_plane(0);
-                fp6_step(aa, u[0], u[1]);                  // P_2
-                a6(aa, kP4);
-                fp4_step(ab, u[0], u[1], kBit);            // S_3
-                a4(ab, 3);
-                fp6_step(aa, xw[0][1], xw[1][1]);          // P_4
-                a6(aa, kP6);
-                fp4_step(ab, xw[0][1], xw[1][1], kBit);    // S_5
-                a4(ab, 4);
-                up(u, 1);
-                load_plane(1);
-                fp6_step(aa, u[0], u[1]);                  // P_6
-                a6(aa, kP8);
-                fp4_step(ab, u[0], u[1], kBit);            // S_7
+                cut(d0, xw[0][0], xw[1][0], kDig);
+                __builtin_amdgcn_sched_barrier(0);
+                // A plane's registers take the next chunk's plane as soon as its last digit is
+                // cut out.
+                auto plane = [&](auto pl_, auto first, auto last) {
+                    constexpr int pl = decltype(pl_)::value;
+                    a4(ab, 2 * pl + 1);
+                    if constexpr (pl == 0) bits(aa, d0);
+                    else powers(aa, d0);                               // P of the low digit
+                    cut(d1, xw[0][pl], xw[1][pl], kBit);
+                    region(Four());
+                    a6(aa, 2 * pl);
+                    bits(ab, d1);                                      // S of its upper bit
+                    up(pl);
+                    cut(d0, u[0], u[1], kDig);
+                    region(Four());
+                    load_plane(pl);
+                    first();
+                    powers(aa, d0);                                    // P of the high digit
+                    cut(d1, u[0], u[1], kBit);
+                    region(Four());
+                    last();
+                };
+                plane(std::integral_constant<int, 0>(), [&] { a4(ab, 2); }, [&] {
+                    a6(aa, kP4);
+                    bits(ab, d1);                                      // S_3
+                    cut(d0, xw[0][1], xw[1][1], kDig);
+                    region(Four());
+                });
+                plane(std::integral_constant<int, 1>(), [&] { a4(ab, 4); }, [&] {
+                    a6(aa, kP8);
+                    bits(ab, d1);                                      // S_7
+                    cut(d0, xw[0][2], xw[1][2], kDig);
+                    region(Four());
+                });
                 a4(ab, 5);
-                fp6_step(aa, xw[0][2], xw[1][2]);          // P_8
+                powers(aa, d0);                                        // P_8
+                cut(d1, xw[0][2], xw[1][2], kBit);
+                region(Four());
                 a6(aa, kP10);
-                fp4_step(ab, xw[0][2], xw[1][2], kBit);    // S_9
-                a4(ab, 6);
-                up(u, 2);
+                bits(ab, d1);                                          // S_9
+                up(2);
+                cut(d0, u[0], u[1], kDig);
+                region(Four());
                 load_plane(2);
-                fp6_step(aa, u[0], u[1]);                  // P_10
+                a4(ab, 6);
+                powers(aa, d0);                                        // P_10
+                cut(d1, u[0], u[1], kBit);
+                region(Four());
                 a6(aa, kW);
-                fp4_step(ab, u[0], u[1], kBit);            // S_11
+                bits(ab, d1);                                          // S_11
+                cut(d1, xw[0][3], xw[1][3], kDig);
+                region(Four());
                 a6(ab, kP12);
 #pragma unroll
                 for (int m = 0; m < 2; ++m)
 #pragma unroll
-                    for (int t = 0; t < 2; ++t)
-                        c0[m][t] = mms<kE3M2, kE2M1, kP4x>(aa[m], wide(u[t] & kDig), c0[m][t], sc);
-                __builtin_amdgcn_sched_barrier(0);
-                fp6_step(ab, xw[0][3], xw[1][3]);          // P_12
-                a4(ab, 7);
-#pragma unroll
-                for (int m = 0; m < 2; ++m)
-#pragma unroll
-                    for (int t = 0; t < 2; ++t)
-                        c1[m][t] = mm<kE3M2, kE2M1>(aa[m], wide(xw[t][3] & kDig), c1[m][t]);
-                __builtin_amdgcn_sched_barrier(0);
-                fp4_step(ab, xw[0][3], xw[1][3], kBit);    // S_13
-                a6(ab, kP14);
-                up(u, 3);
-                load_plane(3);
-#pragma unroll
-                for (int m = 0; m < 2; ++m)
-#pragma unroll
-                    for (int t = 0; t < 2; ++t) {
-                        c1[m][t] = mms<kE3M2, kE2M1, kP2x>(aa[m], wide(u[t] & kDig), c1[m][t], sc);
-                        c1[m][t] = mms<kE3M2, kE2M3, kP2x, kP4x>(aa[m], wide(xl[t], xh[t]), c1[m][t], sc);
+                    for (int t = 0; t < 2; ++t) {                      // W x d(10), d(12)
+                        c0[m][t] = mms<kE3M2, kE2M1, kP4x>(aa[m], wide(d0[t]), c0[m][t], sc);
+                        c1[m][t] = mm<kE3M2, kE2M1>(aa[m], wide(d1[t]), c1[m][t]);
                     }
-                __builtin_amdgcn_sched_barrier(0);
-                fp6_step(ab, u[0], u[1]);                  // P_14
+                region(Eight());
+                cut(d0, xw[0][3], xw[1][3], kBit);
+                powers(ab, d1);                                        // P_12
+                up(3);
+                region(Four());
+                load_plane(3);
+                a4(ab, 7);
+                cut(d1, u[0], u[1], kDig);
 #pragma unroll
                 for (int m = 0; m < 2; ++m)
 #pragma unroll
-                    for (int t = 0; t < 2; ++t)
-                        c0[m][t] = mms<kE3M2, kE2M3, kP4x>(ab[m], wide(xl[t], xh[t]), c0[m][t], sc);
+                    for (int t = 0; t < 2; ++t)                        // W x H
+                        c1[m][t] = mms<kE3M2, kE2M3, kP2x, kP4x>(aa[m], wide(xl[t], xh[t]), c1[m][t], sc);
+                region(Four());
+#pragma unroll
+                for (int m = 0; m < 2; ++m)
+#pragma unroll
+                    for (int t = 0; t < 2; ++t)                        // W x d(14)
+                        c1[m][t] = mms<kE3M2, kE2M1, kP2x>(aa[m], wide(d1[t]), c1[m][t], sc);
+                __builtin_amdgcn_sched_barrier(0);
+                a6(aa, kP14);
+                bits(ab, d0);                                          // S_13
+                region(Four());
+#pragma unroll
+                for (int m = 0; m < 2; ++m)
+#pragma unroll
+                    for (int t = 0; t < 2; ++t)                        // P_14 x H
+                        c0[m][t] = mms<kE3M2, kE2M3, kP4x>(aa[m], wide(xl[t], xh[t]), c0[m][t], sc);
                 load_h();
+                __builtin_amdgcn_sched_barrier(0);
+                powers(aa, d1);                                        // P_14
                 __builtin_amdgcn_sched_barrier(0);
                 ++ch;
             } while (ch < ch1 && fits(ch));
@@ -838,39 +954,44 @@ constexpr int64_t round256(int64_t v) { return (v + 255) & ~int64_t(255); }
 
 }  // namespace
 
-MfmaLayout mfma_layout(const ConvGeom &g)
+MfmaLayout mfma_layout(const ConvGeom &g, bool shared, int tasks)
 {
     MfmaLayout l;
-    const bool point = g.r == 1 && g.s == 1 && g.ph == 0 && g.pw == 0 &&
-                       g.oh <= (g.h - 1) / g.sh + 1 && g.ow <= (g.w - 1) / g.sw + 1;
+    l.sampled = !shared && g.r == 1 && g.s == 1 && g.ph == 0 && g.pw == 0 && g.oh <= (g.h - 1) / g.sh + 1 &&
+                g.ow <= (g.w - 1) / g.sw + 1;
     // Few channels would leave most of a 32-channel block empty: the columns of a tap
     // row become channels instead, if that saves a third of the blocks or more.
     const int64_t plain = int64_t((g.c + kBlockK - 1) / kBlockK) * g.s;
     const int64_t folded = (int64_t(g.c) * g.s + kBlockK - 1) / kBlockK;
-    l.US = !point && g.s > 1 && 3 * folded <= 2 * plain ? g.s : 1;
-    l.PH = point ? g.oh : g.h;
-    l.PW = point || l.US > 1 ? g.ow : g.w;
-    l.CB = int((int64_t(g.c) * l.US + kBlockK - 1) / kBlockK);
-    l.T = g.r * (l.US > 1 ? 1 : g.s);
-    l.even = l.CB % 2 == 0;
+    l.US = !shared && !l.sampled && g.s > 1 && 3 * folded <= 2 * plain ? g.s : 1;
+    l.PH = l.sampled ? g.oh : g.h;
+    l.PW = l.sampled || l.US > 1 ? g.ow : g.w;
+    const int64_t cb = (int64_t(g.c) * l.US + kBlockK - 1) / kBlockK, t = int64_t(g.r) * (l.US > 1 ? 1 : g.s);
     const int64_t np = int64_t(g.n) * l.PH * l.PW, nq = int64_t(g.n) * g.oh * g.ow;
-    const int64_t nchunks = (int64_t(l.CB) * l.T + 1) / 2;
+    // Extents whose products below could not be formed are far past every limit.
+    if (cb <= 0 || t <= 0 || nq <= 0 || cb > (1 << 24) || t > (1 << 24) || np > (int64_t(1) << 31) ||
+        nq > (int64_t(1) << 31))
+        return l;
+    const int64_t nchunks = (cb * t + 1) / 2;
     const int64_t tiles_p = (nq + kPix - 1) / kPix, tiles_k = (g.k + kRows - 1) / kRows;
-    l.xp_bytes = size_t(round256(int64_t(l.CB) * np * kXpBytes));
-    l.dig_bytes = size_t(round256(int64_t(l.CB) * np * kDigBytes));
     const int64_t nblk = (np + 255) / 256;
-    l.hm_bytes = size_t(round256(int64_t(l.CB) * nblk));
+    // 32-bit buffer offsets (an address past 2^31 marks a position outside x), 32-bit
+    // block counts, and rows and columns in 16 bits (the extents, a window's start up
+    // to a padding before them, a tap up to a window after it).
+    constexpr int64_t kMax = int64_t(1) << 31;
+    l.fits = cb * np * kXpBytes < kMax - 512 && nchunks * kStageBytes < kMax && tiles_p * tiles_k < kMax / 4 &&
+             tiles_k * nchunks < kMax / 8 && cb * nblk < kMax / 4 && int64_t(g.n) * g.k * g.oh * g.ow < kMax &&
+             std::max(l.PH, l.PW) < 16384 && std::max(g.r, g.s) < 8192 &&
+             std::max(std::abs(g.ph), std::abs(g.pw)) < 8192;
+    if (!l.fits) return l;
+    l.CB = int(cb);
+    l.T = int(t);
+    l.even = l.CB % 2 == 0;
+    l.xp_bytes = size_t(round256(cb * np * kXpBytes));
+    l.dig_bytes = size_t(round256(cb * np * kDigBytes));
+    l.hm_bytes = size_t(round256(cb * nblk));
     l.wa_bytes = size_t(tiles_k * nchunks * kStageBytes);
     l.bd_bytes = size_t(round256(2 * tiles_k * nchunks * int64_t(sizeof(Bounds))));
-    // 32-bit buffer offsets (an address past 2^31 marks a position outside x), and
-    // grids of 2^31 blocks at most.
-    l.fits = int64_t(l.xp_bytes) < (int64_t(1) << 31) && nchunks * kStageBytes < (int64_t(1) << 31) &&
-             tiles_p * tiles_k + 8 * tiles_k < (int64_t(1) << 31) && int64_t(l.CB) * nblk + 2 * tiles_k * nchunks < (int64_t(1) << 31) &&
-             int64_t(g.c) * l.US < (int64_t(1) << 30) &&
-             // rows and columns in 16 bits (the extents, a window start up to a padding
-             // before them, a tap up to a window after it)
-             std::max(l.PH, l.PW) < 16384 && std::max(g.r, g.s) < 8192 && std::max(std::abs(g.ph), std::abs(g.pw)) < 8192;
-    if (!l.fits) return l;
     l.NP = int(np);
     l.nblk = int(nblk);
     l.nchunks = int(nchunks);
@@ -878,7 +999,7 @@ MfmaLayout mfma_layout(const ConvGeom &g)
     l.tiles_k = int(tiles_k);
     // Two workgroups fit a CU: a smaller grid splits the reduction, keeping two chunks
     // per part.
-    const int64_t tiles = tiles_p * tiles_k;
+    const int64_t tiles = tiles_p * tiles_k * tasks;
     int64_t splits = 1;
     if (tiles < 384) splits = std::max<int64_t>(1, std::min<int64_t>(512 / tiles, nchunks / 2));
     l.cps = int((nchunks + splits - 1) / splits);
@@ -893,89 +1014,199 @@ MfmaLayout mfma_layout(const ConvGeom &g)
 // 21.4, 128 -> 128 3 x 3 on 28 x 28 (116 M) 30.6 and 22.2, and 256 -> 256 3 x 3 on
 // 14 x 14 at batch 128 (14.8 G) 935 and 150. A LinearShift (256 rows or more here)
 // takes five launches there: 128 -> 64 at batch 300 (2.5 M) 26.4 against 19.5.
-bool mfma_prefer(const ConvGeom &g, const MfmaLayout &l)
+bool mfma_prefer(const ConvGeom &g, int64_t terms)
 {
-    if (!l.fits) return false;
-    const int64_t terms = int64_t(g.n) * g.oh * g.ow * g.k * g.crs;
     const bool linear = g.h == 1 && g.w == 1 && g.r == 1 && g.s == 1;
-    return !linear && ((g.k > 16 && terms >= 4000000) || terms >= 50000000);
+    return linear || (g.k > 16 && terms >= 4000000) || terms >= 50000000;
 }
 
-hipError_t run_mfma(const ConvGeom &g, const MfmaLayout &l, const int32_t *x, const uint32_t *wp,
-                    const int32_t *bias, int32_t *y, hipStream_t st, const Epilogue &epi,
-                    const OutMap &map, void *scratch)
+// A plan's two paths, in microseconds on MI355X (graph replays). Here: two launches
+// and what a tile does besides its products (10), the packed copy of x written and
+// read at 5.5 TB/s, the products of whole tiles at 130 T terms/s, y at 4 TB/s, 15
+// for a split reduction. Generated code: 50 T terms/s at the ResNets' share of zero
+// weights, and a launch. Measured (estimated) here against generated code: 256 ->
+// 256 3x3 on 14x14 at batch 128 138 (138) against 280 (299), 64 -> 64 3x3 on 56x56
+// 177 (181) against 278 (299), 1024 -> 256 on 14x14 95 (98) against 134 (135), 512
+// -> 512 3x3 on 7x7 at batch 32 63 (55) against 86 (77), 4096 -> 4096 at batch 256
+// 64 (60) against 102 (89); the other way 512 -> 128 on 28x28 135 (136) against 124
+// (135), 64 -> 256 on 56x56 196 (195) against 157 (135), the 7x7 stem 376 (355)
+// against 313 (305), 128 -> 128 3x3 on 28x28 at batch 8 32 (35) against 28 (21).
+bool mfma_prefer_plan(const MfmaTask *tasks, size_t ntasks, int64_t x_elems, int64_t terms)
 {
-    if (!l.fits) return hipErrorInvalidValue;
-    unsigned char *xp = static_cast<unsigned char *>(scratch);
-    unsigned char *dig = xp + l.xp_bytes;
-    unsigned char *hm = dig + l.dig_bytes;
-    unsigned char *wa = hm + l.hm_bytes;
-    Bounds *bounds = reinterpret_cast<Bounds *>(wa + l.wa_bytes);
-    const bool point = l.T == 1 && l.US == 1 && g.ph == 0 && g.pw == 0 && l.PH == g.oh && l.PW == g.ow;
+    const MfmaLayout &l = tasks[0].l;
+    double us = 10.0 + (4.0 * x_elems + 2.75 * 32.0 * l.CB * l.NP) / 5.5e6;
+    bool split = false;
+    for (size_t i = 0; i < ntasks; ++i) {
+        const MfmaTask &t = tasks[i];
+        us += double(t.l.tiles_p) * kPix * t.l.tiles_k * kRows * t.l.nchunks * 64.0 / 130e6 +
+              4.0 * t.g.n * double(t.g.k) * t.g.oh * t.g.ow / 4e6;
+        split = split || t.l.splits > 1;
+    }
+    if (split) us += 15.0;
+    return us < 3.0 + double(terms) / 50e6;
+}
 
+MfmaWeights mfma_forward_weights(const ConvGeom &g)
+{
+    MfmaWeights w;
+    w.R = g.r;
+    w.S = g.s;
+    w.wpr = int(row_words_bits(g.crs, g.bits));
+    w.bits = g.bits;
+    return w;
+}
+
+MfmaWeights mfma_phase_weights(const ConvGeom &f, const GradPhase &ph)
+{
+    MfmaWeights w;
+    w.R = f.r;
+    w.S = f.s;
+    w.r0 = ph.r0 + f.sh * (ph.g.r - 1);   // the phase's taps in reverse order
+    w.dr = -f.sh;
+    w.s0 = ph.s0 + f.sw * (ph.g.s - 1);
+    w.ds = -f.sw;
+    w.adjoint = true;
+    w.wpr = int(row_words_bits(f.crs, f.bits));
+    w.bits = f.bits;
+    return w;
+}
+
+namespace {
+
+Reduction reduction(const MfmaTask &t)
+{
     Reduction d{};
-    d.CB = l.CB;
-    d.R = g.r;
-    d.S = l.US > 1 ? 1 : g.s;
-    d.US = l.US;
-    d.C = g.c * l.US;
-    d.even = l.even;
-    d.nchunks = l.nchunks;
+    d.CB = t.l.CB;
+    d.R = t.g.r;
+    d.S = t.l.US > 1 ? 1 : t.g.s;
+    d.US = t.l.US;
+    d.C = t.g.c * t.l.US;
+    d.even = t.l.even;
+    d.nchunks = t.l.nchunks;
+    return d;
+}
 
-    PackParams k{};
-    k.N = g.n; k.C = g.c; k.H = g.h; k.W = g.w; k.HW = g.h * g.w;
-    k.PH = l.PH; k.PW = l.PW; k.NP = l.NP; k.PHW = l.PH * l.PW;
-    k.sh = point ? g.sh : 1;
-    k.sw = point || l.US > 1 ? g.sw : 1;
-    k.pw = l.US > 1 ? g.pw : 0;
-    k.US = l.US;
-    k.CB = l.CB;
-    k.nblk = l.nblk;
-    k.div_phw = make_fastdiv(uint32_t(k.PHW));
-    k.div_pw = make_fastdiv(uint32_t(k.PW));
-    k.div_us = make_fastdiv(uint32_t(l.US));
+OutMap full_output(const MfmaTask &t)
+{
+    const ConvGeom &g = t.g;
+    return t.map.dense() ? OutMap{0, g.k * g.oh * g.ow, g.oh * g.ow, g.ow, 1} : t.map;
+}
 
-    const bool split = l.splits > 1;
-    const OutMap m = map.dense() ? OutMap{0, g.k * g.oh * g.ow, g.oh * g.ow, g.ow, 1} : map;
-    FillParams f{};
-    f.y = y;
-    f.bias = bias;
-    f.K = g.k; f.OHOW = g.oh * g.ow; f.OW = g.ow; f.NK = g.n * g.k;
-    f.ybase = int(m.base); f.ynst = m.nstride; f.ykst = m.kstride; f.yrst = m.rstride; f.ycst = m.cstride;
-    f.div_ohow = make_fastdiv(uint32_t(f.OHOW));
-    f.div_ow = make_fastdiv(uint32_t(f.OW));
-    f.div_k = make_fastdiv(uint32_t(f.K));
-    f.blocks = split ? int(std::min<int64_t>((int64_t(f.NK) * f.OHOW + 1023) / 1024, 2048)) : 0;
+}  // namespace
 
-    const int wblocks = 2 * l.tiles_k * l.nchunks;
-    hipLaunchKernelGGL(mfma_prep_kernel, dim3(unsigned(wblocks) + unsigned(l.CB) * unsigned(l.nblk) + unsigned(f.blocks)),
-                       dim3(256), 0, st, x, wp, g.k, g.r, g.s, int(row_words_bits(g.crs, g.bits)), code_fmt(g.bits), d,
-                       k, wblocks, wa, bounds, xp, dig, hm, f);
+hipError_t mfma_prepare(const MfmaTask *tasks, int ntasks, const void *x, int act_bytes, const uint32_t *wp,
+                        unsigned char *input, const int32_t *bias, int32_t *y, hipStream_t st)
+{
+    if (ntasks < 1 || ntasks > kMfmaTasks) return hipErrorInvalidValue;
+    PrepArgs a{};
+    a.x = x;
+    a.wp = wp;
+    a.ntasks = ntasks;
+    if (x) {
+        const MfmaTask &t = tasks[0];
+        const ConvGeom &g = t.g;
+        const MfmaLayout &l = t.l;
+        a.xp = input;
+        a.dig = input + l.xp_bytes;
+        a.hmax = a.dig + l.dig_bytes;
+        PackParams &k = a.p;
+        k.C = g.c; k.W = g.w; k.HW = g.h * g.w;
+        k.NP = l.NP; k.PHW = l.PH * l.PW;
+        k.sh = l.sampled ? g.sh : 1;
+        k.sw = l.sampled || l.US > 1 ? g.sw : 1;
+        k.pw = l.US > 1 ? g.pw : 0;
+        k.US = l.US;
+        k.nblk = l.nblk;
+        k.div_phw = make_fastdiv(uint32_t(k.PHW));
+        k.div_pw = make_fastdiv(uint32_t(l.PW));
+        k.div_us = make_fastdiv(uint32_t(l.US));
+        a.pblocks = l.CB * l.nblk;
+    }
+    int64_t fills = 0;
+    for (int i = 0; i < ntasks; ++i) {
+        const MfmaTask &t = tasks[i];
+        const ConvGeom &g = t.g;
+        if (!t.l.fits) return hipErrorInvalidValue;
+        if (wp) {
+            WeightTask &w = a.w[i];
+            w.d = reduction(t);
+            w.w = t.w;
+            w.fmt = code_fmt(t.w.bits);
+            w.K = g.k;
+            w.blocks = 2 * t.l.tiles_k * t.l.nchunks;
+            w.wa = t.weights;
+            w.bounds = reinterpret_cast<Bounds *>(t.weights + t.l.wa_bytes);
+            a.wblocks += w.blocks;
+        }
+        FillParams &f = a.f[i];
+        if (t.l.splits > 1 && y) {
+            const OutMap m = full_output(t);
+            f.y = y;
+            f.bias = bias;
+            f.K = g.k; f.OHOW = g.oh * g.ow; f.OW = g.ow; f.NK = g.n * g.k;
+            f.ybase = int(m.base); f.ynst = m.nstride; f.ykst = m.kstride; f.yrst = m.rstride; f.ycst = m.cstride;
+            f.div_ohow = make_fastdiv(uint32_t(f.OHOW));
+            f.div_ow = make_fastdiv(uint32_t(f.OW));
+            f.div_k = make_fastdiv(uint32_t(f.K));
+            f.blocks = int(std::min<int64_t>((int64_t(f.NK) * f.OHOW + 1023) / 1024, 2048));
+            fills += f.blocks;
+        }
+    }
+    const int64_t blocks = int64_t(a.wblocks) + a.pblocks + fills;
+    if (blocks == 0) return hipSuccess;
+    if (blocks > INT32_MAX) return hipErrorInvalidValue;
+    const dim3 grid{unsigned(blocks)}, block{256u};
+    if (act_bytes == 2) hipLaunchKernelGGL(mfma_prep_kernel<int16_t>, grid, block, 0, st, a);
+    else if (act_bytes == 1) hipLaunchKernelGGL(mfma_prep_kernel<int8_t>, grid, block, 0, st, a);
+    else hipLaunchKernelGGL(mfma_prep_kernel<int32_t>, grid, block, 0, st, a);
+    return hipGetLastError();
+}
+
+hipError_t mfma_multiply(const MfmaTask *tasks, int ntasks, const unsigned char *input, const int32_t *bias,
+                         int32_t *y, const Epilogue &epi, hipStream_t st)
+{
+    if (ntasks < 1 || ntasks > kMfmaTasks) return hipErrorInvalidValue;
+    ProductArgs a{};
+    a.xp = input;
+    a.dig = input + tasks[0].l.xp_bytes;
+    a.hmax = a.dig + tasks[0].l.dig_bytes;
+    a.bias = bias;
+    a.y = y;
+    a.epi = epi;
+    int64_t tiles = 0;
+    int splits = 1;
+    for (int i = 0; i < ntasks; ++i) {
+        const MfmaTask &t = tasks[i];
+        const ConvGeom &g = t.g;
+        const MfmaLayout &l = t.l;
+        if (!l.fits) return hipErrorInvalidValue;
+        MfmaParams &p = a.p[i];
+        p.d = reduction(t);
+        p.PH = l.PH; p.PW = l.PW; p.PHW = l.PH * l.PW; p.NP = l.NP;
+        p.sh = l.sampled ? 1 : g.sh;
+        p.sw = l.sampled || l.US > 1 ? 1 : g.sw;
+        p.ph = g.ph;
+        p.pw = l.US > 1 ? 0 : g.pw;
+        p.K = g.k; p.OHOW = g.oh * g.ow; p.NQ = int(int64_t(g.n) * p.OHOW);
+        p.tiles_p = l.tiles_p; p.tiles_k = l.tiles_k; p.cps = l.cps; p.nblk = l.nblk;
+        p.atomic_out = l.splits > 1;
+        p.fuse_epi = epi.any() && l.splits == 1;
+        const OutMap m = full_output(t);
+        p.ybase = int(m.base); p.ynst = m.nstride; p.ykst = m.kstride; p.yrst = m.rstride; p.ycst = m.cstride;
+        p.rowmajor = m.kstride == 1 && p.OHOW == 1;
+        p.xp_bytes = uint32_t(l.xp_bytes);
+        p.div_ohow = make_fastdiv(uint32_t(p.OHOW));
+        p.div_ow = make_fastdiv(uint32_t(g.ow));
+        p.wa = t.weights;
+        p.bounds = reinterpret_cast<const Bounds *>(t.weights + l.wa_bytes);
+        tiles = std::max(tiles, int64_t(l.tiles_p) * l.tiles_k);
+        splits = std::max(splits, l.splits);
+    }
+    hipLaunchKernelGGL(mfma_conv_kernel, dim3(unsigned((tiles + 7) / 8 * 8), unsigned(splits), unsigned(ntasks)),
+                       dim3(256), 0, st, a);
     hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-
-    MfmaParams p{};
-    p.d = d;
-    p.PH = l.PH; p.PW = l.PW; p.PHW = k.PHW; p.NP = l.NP;
-    p.sh = point ? 1 : g.sh;
-    p.sw = point || l.US > 1 ? 1 : g.sw;
-    p.ph = g.ph;
-    p.pw = l.US > 1 ? 0 : g.pw;
-    p.K = g.k; p.OHOW = g.oh * g.ow; p.NQ = int(int64_t(g.n) * p.OHOW);
-    p.tiles_p = l.tiles_p; p.tiles_k = l.tiles_k; p.cps = l.cps; p.nblk = l.nblk;
-    p.atomic_out = split;
-    p.fuse_epi = epi.any() && !split;
-    p.ybase = int(m.base); p.ynst = m.nstride; p.ykst = m.kstride; p.yrst = m.rstride; p.ycst = m.cstride;
-    p.rowmajor = m.kstride == 1 && p.OHOW == 1;
-    p.xp_bytes = uint32_t(l.xp_bytes);
-    p.epi = epi;
-    p.div_ohow = make_fastdiv(uint32_t(p.OHOW));
-    p.div_ow = make_fastdiv(uint32_t(g.ow));
-    const unsigned grid = unsigned(int64_t(l.tiles_p) * l.tiles_k + 7) / 8u * 8u;
-    hipLaunchKernelGGL(mfma_conv_kernel, dim3(grid, unsigned(l.splits)), dim3(256), 0, st, xp, dig, hm, wa, bounds,
-                       split ? nullptr : bias, y, p);
-    e = hipGetLastError();
-    if (e == hipSuccess && split && epi.any()) e = run_epilogue(g, y, epi, st);
+    // The epilogue of a split task (one on its own, dense) is a pass over y.
+    if (e == hipSuccess && epi.any() && tasks[0].l.splits > 1) e = run_epilogue(tasks[0].g, y, epi, st);
     return e;
 }
 

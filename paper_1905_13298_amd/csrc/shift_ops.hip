@@ -75,6 +75,18 @@ static ds_status check_conv(const void *x, const void *wts, const void *bias, co
     return DS_SUCCESS;
 }
 
+ds_status check_workspace(void *scratch, int64_t bytes, std::initializer_list<Range> others, Workspace &ws)
+{
+    if (!scratch || bytes <= 0) return DS_SUCCESS;
+    if (reinterpret_cast<uintptr_t>(scratch) & 255) return fail(DS_ERR_INVALID_ARG, "scratch is not 256-byte aligned");
+    for (const Range &o : others)
+        if (overlap(scratch, bytes, o.p, o.bytes)) return fail(DS_ERR_INVALID_ARG, "scratch overlaps a tensor");
+    if (!device_range_ok(scratch, bytes))
+        return fail(DS_ERR_INVALID_ARG, "scratch is not a device buffer of %lld bytes", (long long)bytes);
+    ws = Workspace{scratch, size_t(bytes)};
+    return DS_SUCCESS;
+}
+
 static ds_status hip_status(hipError_t e, const char *what)
 {
     if (e == hipSuccess) return ok();
@@ -102,14 +114,15 @@ extern "C" ds_status ds_conv2d_shift(const int32_t *x, const uint32_t *w_packed,
                       "ds_conv2d_shift");
 }
 
-extern "C" ds_status ds_conv2d_shift_fused(const int32_t *x, const uint32_t *w_packed,
-                                           const int32_t *bias, const int32_t *mul,
-                                           const int32_t *add, int32_t mul_shift,
-                                           const int32_t *residual, int32_t *y, int64_t n,
-                                           int64_t c, int64_t h, int64_t w, int64_t k, int64_t r,
-                                           int64_t s, int32_t stride_h, int32_t stride_w,
-                                           int32_t pad_h, int32_t pad_w, int32_t frac_bits,
-                                           uint32_t flags, void *stream)
+static ds_status conv2d_shift_fused(const int32_t *x, const uint32_t *w_packed,
+                                    const int32_t *bias, const int32_t *mul,
+                                    const int32_t *add, int32_t mul_shift,
+                                    const int32_t *residual, int32_t *y, int64_t n,
+                                    int64_t c, int64_t h, int64_t w, int64_t k, int64_t r,
+                                    int64_t s, int32_t stride_h, int32_t stride_w,
+                                    int32_t pad_h, int32_t pad_w, int32_t frac_bits,
+                                    uint32_t flags, void *scratch, int64_t scratch_bytes,
+                                    void *stream, const char *name)
 {
     ConvGeom g;
     // Arguments first (no device access), then the buffers.
@@ -140,9 +153,49 @@ extern "C" ds_status ds_conv2d_shift_fused(const int32_t *x, const uint32_t *w_p
     epi.mul_shift = mul_shift;
     epi.res = residual;
     epi.relu = (flags & DS_RELU) != 0;
+    Workspace ws;
+    st = check_workspace(scratch, scratch_bytes, {{x, 4 * int64_t(g.n) * g.c * g.h * g.w}, {y, yb}}, ws);
+    if (st != DS_SUCCESS) return st;
+    // Scratch that is too small for the call's kernels is not used.
+    if (ws.bytes < conv_workspace_bytes(g)) ws = Workspace();
     return hip_status(run_conv(g, x, w_packed, nullptr, bias, y, Inner::Shift,
-                               static_cast<hipStream_t>(stream), epi),
-                      "ds_conv2d_shift_fused");
+                               static_cast<hipStream_t>(stream), epi, OutMap(), Padded(), ws),
+                      name);
+}
+
+extern "C" ds_status ds_conv2d_shift_fused(const int32_t *x, const uint32_t *w_packed,
+                                           const int32_t *bias, const int32_t *mul,
+                                           const int32_t *add, int32_t mul_shift,
+                                           const int32_t *residual, int32_t *y, int64_t n,
+                                           int64_t c, int64_t h, int64_t w, int64_t k, int64_t r,
+                                           int64_t s, int32_t stride_h, int32_t stride_w,
+                                           int32_t pad_h, int32_t pad_w, int32_t frac_bits,
+                                           uint32_t flags, void *stream)
+{
+    return conv2d_shift_fused(x, w_packed, bias, mul, add, mul_shift, residual, y, n, c, h, w, k, r, s, stride_h,
+                              stride_w, pad_h, pad_w, frac_bits, flags, nullptr, 0, stream, "ds_conv2d_shift_fused");
+}
+
+extern "C" ds_status ds_conv2d_shift_fused_ws(const int32_t *x, const uint32_t *w_packed, const int32_t *bias,
+                                              const int32_t *mul, const int32_t *add, int32_t mul_shift,
+                                              const int32_t *residual, int32_t *y, int64_t n, int64_t c, int64_t h,
+                                              int64_t w, int64_t k, int64_t r, int64_t s, int32_t stride_h,
+                                              int32_t stride_w, int32_t pad_h, int32_t pad_w, int32_t frac_bits,
+                                              uint32_t flags, void *scratch, int64_t scratch_bytes, void *stream)
+{
+    return conv2d_shift_fused(x, w_packed, bias, mul, add, mul_shift, residual, y, n, c, h, w, k, r, s, stride_h,
+                              stride_w, pad_h, pad_w, frac_bits, flags, scratch, scratch_bytes, stream,
+                              "ds_conv2d_shift_fused_ws");
+}
+
+extern "C" int64_t ds_conv2d_shift_scratch_bytes(int64_t n, int64_t c, int64_t h, int64_t w, int64_t k, int64_t r,
+                                                 int64_t s, int32_t stride_h, int32_t stride_w, int32_t pad_h,
+                                                 int32_t pad_w)
+{
+    ConvGeom g;
+    if (check_shape(n, c, h, w, k, r, s, stride_h, stride_w, pad_h, pad_w, true, g) != DS_SUCCESS) return -1;
+    ok();
+    return int64_t(conv_workspace_bytes(g));
 }
 
 extern "C" ds_status ds_linear_shift(const int32_t *x, const uint32_t *w_packed, const int32_t *bias,

@@ -7,6 +7,7 @@ weights are int32 tensors holding the uint32 words bit for bit.
 from __future__ import annotations
 
 import ctypes
+import math
 
 import numpy as np
 import torch
@@ -466,6 +467,8 @@ class JitConv:
         # that run each segment, and whether a LinearShift runs on x^T.
         self.channels, self.wsplit, self.pixel_groups, self.pixel_tiles = tn.value, ws.value, pg.value, tiles.value
         self.transposed = bool(tr.value)
+        # Whether the plan runs on the matrix cores rather than generated code.
+        self.matrix_cores = bool(lib().ds_jit_conv_matrix_cores(self._h))
 
     # Cost model of the two paths on MI355X (microseconds), fitted to calls timed
     # back to back. A plan's waves each stream their share of the straight-line
@@ -495,6 +498,11 @@ class JitConv:
     def estimate_us(self) -> float:
         """Modelled duration of one run of this plan on MI355X (see the cost
         model above)."""
+        if getattr(self, "matrix_cores", False):
+            # the packed copy of x (4 bytes read and 2.75 written an element) and the
+            # products, at the rates of a full grid, and two launches
+            elems = math.prod(self.x_shape)
+            return 8.0 + 6.75 * elems / 5.5e6 + self.sac / 115e6
         streams = max(1, self.segments * self.wsplit)
         executed = self.code_bytes / 4.2 * max(1, self.pixel_tiles) * max(1, self.pixel_groups)
         t = max(self.code_bytes / streams / self.PLAN_STREAM_BPUS, executed / self.PLAN_ISSUE_PER_US)
@@ -527,6 +535,8 @@ class JitConv:
         the layers of ResNet-18 (batch 32) and ResNet-50 (batch 128) measured /
         modelled plan durations have medians 1.16 and 1.04, runtime-kernel ones
         0.97 and 0.92."""
+        if getattr(self, "matrix_cores", False):
+            return True     # the runtime call's kernels, with the weights expanded already
         return self.estimate_us() < self.runtime_estimate_us()
 
     def __call__(self, x: torch.Tensor, residual: torch.Tensor | None = None, out=None):

@@ -113,3 +113,110 @@ def test_matrix_core_short_codes_match_oracle(bits, knob):
     y = ops.conv2d_shift(to_dev(x), to_dev(ops.pack_shift_weights(codes, bits).view(np.int32)), None, 3, 1, 1,
                          code_bits=bits)
     np.testing.assert_array_equal(y.cpu().numpy(), oracle.conv2d_shift(x, codes, None, r=3, stride=1, pad=1))
+
+
+GRADS = [
+    # n, c, h, w, k, r, s, stride, pad
+    (2, 64, 14, 14, 32, 3, 3, 1, 1),      # one phase, dense
+    (2, 70, 16, 16, 33, 3, 3, 2, 1),      # four phases on one packed copy, ragged channels
+    (2, 40, 15, 13, 64, 3, 3, 2, 0),      # phase grids of different sizes
+    (1, 20, 20, 21, 40, 7, 7, 2, 3),      # four phases of 3 and 4 taps
+    (2, 33, 12, 12, 40, 1, 1, 2, 0),      # positions no tap reaches
+    (2, 20, 14, 14, 24, 5, 5, 3, 2),      # nine phases: groups of four tasks
+    (1, 17, 9, 9, 24, 3, 3, 1, 4),        # padding beyond the window
+    (260, 100, 1, 1, 130, 1, 1, 1, 0),    # LinearShift
+]
+
+
+@pytest.mark.parametrize("mode", ["digit", "edges"])
+@pytest.mark.parametrize("case", GRADS, ids=[str(i) for i in range(len(GRADS))])
+def test_matrix_core_gradients_match_oracle(case, mode, knob):
+    """Calls and plans, every element of dx written."""
+    n, c, h, w, k, r, s, stride, pad = case
+    rng = np.random.default_rng(GRADS.index(case))
+    oh, ow = (h + 2 * pad - r) // stride + 1, (w + 2 * pad - s) // stride + 1
+    dy = inputs(rng, mode, (n, k, oh, ow))
+    codes = random_codes(rng, (k, c * r * s), zero_frac=0.1)
+    knob("DS_FORCE_VARIANT", 64)
+    assert "matrix cores" in ops.describe_conv2d_backward_data(n, c, h, w, k, (r, s), stride, pad)
+    print(case, mode, flush=True)
+    want = oracle.conv2d_shift_backward_data(dy, codes, (n, c, h, w), r=r, s=s, stride=stride, pad=pad)
+    wp = ops.pack_shift_weights(codes)
+    out = torch.full((n, c, h, w), 0x5A5A5A5A, dtype=torch.int32, device=DEV)
+    dx = ops.conv2d_shift_backward_data(to_dev(dy), to_dev(wp.view(np.int32)), (n, c, h, w), (r, s), stride, pad, out=out)
+    np.testing.assert_array_equal(dx.cpu().numpy(), want)
+    plan = ops.JitConvBackwardData(wp, (n, c, h, w), (r, s), stride, pad)
+    assert plan.matrix_cores
+    out.fill_(0x5A5A5A5A)
+    np.testing.assert_array_equal(plan(to_dev(dy), out=out).cpu().numpy(), want)
+    plan.close()
+
+
+@pytest.mark.parametrize("act_bits", [32, 16, 8])
+@pytest.mark.parametrize("shape", [(96, 64, 16, 64, 1, 1, 0), (2, 100, 14, 100, 3, 1, 1), (2, 3, 30, 40, 7, 2, 3),
+                                   (260, 64, 1, 72, 1, 1, 0)], ids=["whole", "split", "folded", "linear"])
+def test_matrix_core_plans_match_oracle(shape, act_bits, knob):
+    """Plans of every input width with the whole epilogue, run twice on new inputs, the
+    second time as replays of a captured graph."""
+    n, c, h, k, r, stride, pad = shape
+    rng = np.random.default_rng(n + c + act_bits)
+    codes = random_codes(rng, (k, c * r * r), zero_frac=0.1)
+    bias, mul, add = (rng.integers(-(2 ** 18), 2 ** 18, k).astype(np.int32) for _ in range(3))
+    knob("DS_FORCE_VARIANT", 64)
+    plan = ops.JitConv(ops.pack_shift_weights(codes), (n, c, h, h), r, stride, pad, bias=bias, mul=mul, add=add,
+                       mul_shift=13, residual=True, relu=True, act_bits=act_bits)
+    assert plan.matrix_cores and plan.preferred
+    dtype = {32: np.int32, 16: np.int16, 8: np.int8}[act_bits]
+
+    def draw():
+        info = np.iinfo(dtype)
+        x = rng.integers(info.min, info.max + 1, (n, c, h, h), dtype=np.int64).astype(dtype)
+        res = rng.integers(-(2 ** 31), 2 ** 31, plan.y_shape, dtype=np.int64).astype(np.int32)
+        v = oracle.conv2d_shift(x.astype(np.int32), codes, bias, r=r, stride=stride, pad=pad)
+        return x, res, oracle.epilogue(v, mul, add, 13, res, True)
+
+    x, res, want = draw()
+    xt, rt = to_dev(x), to_dev(res)
+    y = plan(xt, residual=rt)
+    np.testing.assert_array_equal(y.cpu().numpy(), want)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        plan(xt, residual=rt, out=y)
+    for _ in range(3):
+        x, res, want = draw()
+        xt.copy_(to_dev(x))
+        rt.copy_(to_dev(res))
+        y.fill_(7)
+        graph.replay()
+        np.testing.assert_array_equal(y.cpu().numpy(), want)
+    plan.close()
+
+
+def test_scratch_entry_points(knob):
+    """Scratch given to a call, too little of it (the call then allocates), none, and
+    bad scratch, which is refused before anything runs."""
+    import ctypes
+    from paper_1905_13298_amd import _native
+    lib = _native.lib()
+    rng = np.random.default_rng(5)
+    n, c, h, k = 2, 40, 12, 70
+    x = inputs(rng, "digit", (n, c, h, h))
+    codes = random_codes(rng, (k, c * 9))
+    want = oracle.conv2d_shift(x, codes, None, r=3, stride=1, pad=1)
+    xt, wt = to_dev(x), to_dev(ops.pack_shift_weights(codes).view(np.int32))
+    shape = (n, c, h, h, k, 3, 3, 1, 1, 1, 1)
+    stream = ctypes.c_void_p(torch.cuda.current_stream(DEV).cuda_stream)
+    for variant in (64, 4):
+        knob("DS_FORCE_VARIANT", variant)
+        need = lib.ds_conv2d_shift_scratch_bytes(*shape)
+        buf = torch.empty(need + 256, dtype=torch.uint8, device=DEV)
+        for ptr, size, status in ((buf.data_ptr(), need, 0), (buf.data_ptr(), need - 1, 0), (None, 0, 0),
+                                  (buf.data_ptr() + 4, need, 3), (buf.data_ptr(), 1 << 40, 3), (xt.data_ptr(), 256, 3)):
+            y = torch.full(want.shape, 7, dtype=torch.int32, device=DEV)
+            st = lib.ds_conv2d_shift_fused_ws(xt.data_ptr(), wt.data_ptr(), None, None, None, 0, None, y.data_ptr(),
+                                              *shape, 16, 0, ptr, size, stream)
+            assert st == status, (variant, size, st)
+            if status == 0:
+                np.testing.assert_array_equal(y.cpu().numpy(), want)
+            else:
+                assert torch.all(y == 7)
