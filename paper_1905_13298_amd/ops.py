@@ -130,6 +130,34 @@ def _stream(dev: torch.device) -> int:
     return torch.cuda.current_stream(dev).cuda_stream
 
 
+class _on:
+    """The device context of a call: nothing to enter when `dev` is current already
+    (entering it costs microseconds)."""
+
+    def __init__(self, dev: torch.device):
+        self.ctx = None if dev.index == torch.cuda.current_device() else torch.cuda.device(dev)
+
+    def __enter__(self):
+        if self.ctx is not None:
+            self.ctx.__enter__()
+
+    def __exit__(self, *exc):
+        if self.ctx is not None:
+            return self.ctx.__exit__(*exc)
+        return False
+
+
+def _scratch(entry: str, shape, dev: torch.device):
+    """A call's scratch from PyTorch's caching allocator on the current stream (the
+    caller holds it until its work is enqueued; the allocator orders its reuse), and
+    its size: the library's own stream-ordered allocation costs about 12 us a call, and
+    350 us for 128 MB after a synchronisation."""
+    size = getattr(lib(), entry)(*shape)
+    if size <= 0:
+        return None, 0
+    return torch.empty(size, dtype=torch.uint8, device=dev), size
+
+
 def out_size(size: int, pad: int, k: int, stride: int) -> int:
     return (size + 2 * pad - k) // stride + 1
 
@@ -150,10 +178,22 @@ def linear_shift(x: torch.Tensor, w_packed: torch.Tensor, bias: torch.Tensor | N
     fout = w_packed.shape[0]
     y = out if out is not None else torch.empty((batch, fout), dtype=torch.int32, device=x.device)
     _dev_i32(y, "out")
-    with torch.cuda.device(x.device):
-        call("ds_linear_shift", _ptr(x), _ptr(w_packed), _ptr(bias), _ptr(y), batch, fin, fout,
-             frac_bits, (DS_RELU if relu else 0) | code_bits_flag(code_bits), _stream(x.device))
+    flags = (DS_RELU if relu else 0) | code_bits_flag(code_bits)
+    if batch < 256:      # these run without scratch
+        with _on(x.device):
+            call("ds_linear_shift", _ptr(x), _ptr(w_packed), _ptr(bias), _ptr(y), batch, fin, fout, frac_bits,
+                 flags, _stream(x.device))
+    else:
+        _forward(x, w_packed, bias, None, None, 0, None, y, (batch, fin, 1, 1, fout, 1, 1, 1, 1, 0, 0),
+                 frac_bits, flags)
     return y
+
+
+def _forward(x, w_packed, bias, mul, add, mul_shift, residual, y, shape, frac_bits, flags):
+    with _on(x.device):
+        scratch, size = _scratch("ds_conv2d_shift_scratch_bytes", shape, x.device)
+        call("ds_conv2d_shift_fused_ws", _ptr(x), _ptr(w_packed), _ptr(bias), _ptr(mul), _ptr(add), mul_shift,
+             _ptr(residual), _ptr(y), *shape, frac_bits, flags, _ptr(scratch), size, _stream(x.device))
 
 
 def conv2d_shift(x: torch.Tensor, w_packed: torch.Tensor, bias: torch.Tensor | None,
@@ -174,10 +214,8 @@ def conv2d_shift(x: torch.Tensor, w_packed: torch.Tensor, bias: torch.Tensor | N
     y = out if out is not None else torch.empty((n, k, max(oh, 0), max(ow, 0)), dtype=torch.int32,
                                                 device=x.device)
     _dev_i32(y, "out")
-    with torch.cuda.device(x.device):
-        call("ds_conv2d_shift", _ptr(x), _ptr(w_packed), _ptr(bias), _ptr(y), n, c, h, w, k, r, s,
-             sh, sw, ph, pw, frac_bits, (DS_RELU if relu else 0) | code_bits_flag(code_bits),
-             _stream(x.device))
+    _forward(x, w_packed, bias, None, None, 0, None, y, (n, c, h, w, k, r, s, sh, sw, ph, pw),
+             frac_bits, (DS_RELU if relu else 0) | code_bits_flag(code_bits))
     return y
 
 
@@ -195,10 +233,15 @@ def conv2d_shift_backward_data(dy: torch.Tensor, w_packed: torch.Tensor, x_shape
     k = w_packed.shape[0]
     dx = out if out is not None else torch.empty((n, c, h, w), dtype=torch.int32, device=dy.device)
     _dev_i32(dx, "out")
-    with torch.cuda.device(dy.device):
-        call("ds_conv2d_shift_backward_data", _ptr(dy), _ptr(w_packed), _ptr(dx), n, c, h, w, k, r, s,
-             sh, sw, ph, pw, frac_bits, code_bits_flag(code_bits), _stream(dy.device))
+    _backward(dy, w_packed, dx, (n, c, h, w, k, r, s, sh, sw, ph, pw), frac_bits, code_bits_flag(code_bits))
     return dx
+
+
+def _backward(dy, w_packed, dx, shape, frac_bits, flags):
+    with _on(dy.device):
+        scratch, size = _scratch("ds_conv2d_shift_backward_data_scratch_bytes", shape, dy.device)
+        call("ds_conv2d_shift_backward_data_ws", _ptr(dy), _ptr(w_packed), _ptr(dx), *shape, frac_bits, flags,
+             _ptr(scratch), size, _stream(dy.device))
 
 
 def linear_shift_backward_data(dy: torch.Tensor, w_packed: torch.Tensor, in_features: int,
@@ -209,9 +252,8 @@ def linear_shift_backward_data(dy: torch.Tensor, w_packed: torch.Tensor, in_feat
     batch, fout = dy.shape
     dx = out if out is not None else torch.empty((batch, in_features), dtype=torch.int32, device=dy.device)
     _dev_i32(dx, "out")
-    with torch.cuda.device(dy.device):
-        call("ds_linear_shift_backward_data", _ptr(dy), _ptr(w_packed), _ptr(dx), batch, in_features,
-             fout, frac_bits, code_bits_flag(code_bits), _stream(dy.device))
+    _backward(dy, w_packed, dx, (batch, in_features, 1, 1, fout, 1, 1, 1, 1, 0, 0), frac_bits,
+              code_bits_flag(code_bits))
     return dx
 
 
@@ -340,10 +382,8 @@ def conv2d_shift_fused(x: torch.Tensor, w_packed: torch.Tensor, bias, kernel_siz
     y = out if out is not None else torch.empty((n, k, max(oh, 0), max(ow, 0)), dtype=torch.int32,
                                                 device=x.device)
     _dev_i32(y, "out")
-    with torch.cuda.device(x.device):
-        call("ds_conv2d_shift_fused", _ptr(x), _ptr(w_packed), _ptr(bias), _ptr(mul), _ptr(add),
-             mul_shift, _ptr(residual), _ptr(y), n, c, h, w, k, r, s, sh, sw, ph, pw, frac_bits,
-             (DS_RELU if relu else 0) | code_bits_flag(code_bits), _stream(x.device))
+    _forward(x, w_packed, bias, mul, add, mul_shift, residual, y, (n, c, h, w, k, r, s, sh, sw, ph, pw),
+             frac_bits, (DS_RELU if relu else 0) | code_bits_flag(code_bits))
     return y
 
 
