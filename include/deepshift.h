@@ -545,7 +545,8 @@ int64_t ds_conv2d_shift_noalloc_scratch_bytes(int64_t n, int64_t c, int64_t h, i
  * ds_conv2d_shift and the input gradients; 64: the matrix-core kernel wherever
  * it has a layout; any other value the tiled vector kernel, 8 with 8 pixels per
  * lane where such an instance exists), "DS_ROWS_BATCH" (1, 2, 4 or 8 batch rows per
- * workgroup of the kernel that runs a LinearShift below 256 rows) and the plan
+ * workgroup of the kernel that runs a LinearShift below 256 rows; 16: its table
+ * form, the choice for large weights) and the plan
  * knobs listed with ds_jit_conv_create.
  * Each starts from the environment variable of the same name, read once when
  * the library is loaded (unset: -1, the library's own choice); no entry point

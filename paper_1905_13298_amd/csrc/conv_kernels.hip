@@ -1276,9 +1276,14 @@ static bool rows_path(const ConvGeom &g, const OutMap &map, const Padded &pad)
            pad.vh == 0 && pad.iwp == 0 && g.n < 256 && forced_variant() < 0;
 }
 
+static bool table_path(const ConvGeom &g);
+static hipError_t run_table(const ConvGeom &g, const int32_t *x, const uint32_t *wp, const int32_t *bias, int32_t *y,
+                            hipStream_t st, const Epilogue &epi);
+
 static hipError_t run_rows(const ConvGeom &g, const int32_t *x, const uint32_t *wp, const int32_t *wi,
                            const int32_t *bias, int32_t *y, Inner op, hipStream_t st, const Epilogue &epi)
 {
+    if (op == Inner::Shift && table_path(g)) return run_table(g, x, wp, bias, y, st, epi);
     const int units = op == Inner::Shift ? int(row_words_bits(g.c, g.bits)) : g.c;
     const int rows = rows_per_block(g, units, !epi.any());
     const int64_t blocks = int64_t((g.k + 63) / 64) * ((g.n + rows - 1) / rows);
@@ -1301,6 +1306,151 @@ static hipError_t run_rows(const ConvGeom &g, const int32_t *x, const uint32_t *
     else if (op == Inner::Mul) launch_rows_op<Inner::Mul>(g, x, a, rows, splits, st);
     else launch_rows_op<Inner::Mul24>(g, x, a, rows, splits, st);
     return hipGetLastError();
+}
+
+// Small-batch LinearShift with large weights: a table instead of arithmetic. Every
+// weight on column j contributes one of the 2^BITS values +-(x[j] >> s) or 0, the
+// same 2^BITS for all output channels, so a workgroup builds them once per column in
+// LDS and each lane, which walks its channel's packed row, adds the entry its code
+// selects: two instructions to cut the code out as an address, an LDS read (the
+// lanes of a wave read within one column's entries: no bank conflicts) and an add,
+// where the kernel above decodes each code in about ten. Entries past the last
+// column are 0, whatever the code. 512 threads: 512 channels, ROWS batch rows
+// (neighbours in an entry) and one part of the packed words, in chunks whose table
+// fits kTableBytes; the parts' sums meet in y, which a fill pass starts at the bias.
+constexpr int kTableThreads = 512;
+constexpr int kTableBytes = 48 * 1024;
+
+template <int BITS, int ROWS>
+constexpr int table_chunk_words() { return kTableBytes / ((32 / BITS) * (4 << BITS) * ROWS) / 16 * 16; }
+
+template <int BITS, int ROWS>
+__global__ void __launch_bounds__(kTableThreads)
+linear_table_kernel(const int32_t *__restrict__ x, const RowsArgs a, int part_words)
+{
+    constexpr int PER = 32 / BITS, ENT = 1 << BITS, CHUNK = table_chunk_words<BITS, ROWS>();
+    constexpr int LOG = ROWS == 4 ? 4 : ROWS == 2 ? 3 : 2;   // bytes of an entry, as a power of two
+    constexpr int COL = ENT << LOG;                          // bytes of a column's entries
+    typedef int vrow __attribute__((ext_vector_type(ROWS)));
+    typedef uint32_t words4 __attribute__((ext_vector_type(4), aligned(4)));
+    __shared__ __align__(16) unsigned char table[CHUNK * PER * COL];
+    const int k = int(blockIdx.x) * kTableThreads + int(threadIdx.x);
+    const int b0 = int(blockIdx.y) * ROWS;
+    const int p0 = int(blockIdx.z) * part_words, p1 = min(a.wpr, p0 + part_words);
+    const uint32_t *row = a.wp + int64_t(min(k, a.K - 1)) * a.wpr;
+    uint32_t acc[ROWS] = {};
+    for (int c0 = p0; c0 < p1; c0 += CHUNK) {
+        const int n = min(CHUNK, p1 - c0);
+        if (c0 > p0) __syncthreads();   // the last chunk's entries have been read
+        // Entry e of a column is thread e's, so neighbours write neighbouring entries.
+        for (int i = int(threadIdx.x); i < n * PER * ENT; i += kTableThreads) {
+            const int e = i % ENT, col = c0 * PER + i / ENT;
+            const int sh = e & (ENT / 2 - 1);
+            const bool zero = sh == ENT / 2 - 1 || col >= a.C;
+            int v[ROWS];
+#pragma unroll
+            for (int r = 0; r < ROWS; ++r) {
+                const int32_t t = x[int64_t(min(b0 + r, a.B - 1)) * a.C + min(col, a.C - 1)] >> sh;
+                v[r] = zero ? 0 : e >= ENT / 2 ? int(0u - uint32_t(t)) : t;
+            }
+#pragma unroll
+            for (int r = 0; r < ROWS; ++r) reinterpret_cast<int *>(table)[i * ROWS + r] = v[r];
+        }
+        __syncthreads();
+        if (int(blockIdx.x) * kTableThreads + int(threadIdx.x & ~63u) >= a.K) continue;   // a wave past K
+        auto add = [&](uint32_t w, int u) {
+#pragma unroll
+            for (int j = 0; j < PER; ++j) {
+                constexpr uint32_t mask = uint32_t(ENT - 1) << LOG;
+                const int at = BITS * j - LOG;
+                const uint32_t code = (at >= 0 ? w >> (at >= 0 ? at : 0) : w << (at < 0 ? -at : 0)) & mask;
+                const vrow t = *reinterpret_cast<const vrow *>(table + ((code | uint32_t(u * PER * COL)) + j * COL));
+                if constexpr (ROWS == 1) acc[0] += uint32_t(t[0]);
+                else
+#pragma unroll
+                    for (int r = 0; r < ROWS; ++r) acc[r] += uint32_t(t[r]);
+            }
+        };
+        // 64 bytes of a row at a time, the next ones on their way: the lanes' lines are
+        // far more than the L1 holds, so a line read in pieces would come from L2 again
+        // for each (25088 -> 4096 at batch 1: 69 us in pieces of 16 bytes).
+        const uint32_t *wp = row + c0;
+        const int n16 = n & ~15;
+        words4 next[4];
+        auto load = [&](int u) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) next[i] = *reinterpret_cast<const words4 *>(wp + u + 4 * i);
+        };
+        if (n16) load(0);
+        for (int u = 0; u < n16; u += 16) {
+            words4 w[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) w[i] = next[i];
+            if (u + 16 < n16) load(u + 16);
+#pragma unroll
+            for (int i = 0; i < 16; ++i) add(w[i >> 2][i & 3], u + i);
+        }
+        for (int u = n16; u < n; ++u) add(wp[u], u);
+    }
+    if (k < a.K)
+#pragma unroll
+        for (int r = 0; r < ROWS; ++r)
+            if (b0 + r < a.B) atomicAdd(reinterpret_cast<unsigned int *>(a.y + int64_t(b0 + r) * a.K + k), acc[r]);
+}
+
+template <int ROWS>
+static void launch_table(dim3 grid, const int32_t *x, const RowsArgs &a, int part_words, int bits, hipStream_t st)
+{
+    const dim3 block(kTableThreads);
+    if (bits == 5) hipLaunchKernelGGL((linear_table_kernel<5, ROWS>), grid, block, 0, st, x, a, part_words);
+    else if (bits == 4) hipLaunchKernelGGL((linear_table_kernel<4, ROWS>), grid, block, 0, st, x, a, part_words);
+    else if (bits == 3) hipLaunchKernelGGL((linear_table_kernel<3, ROWS>), grid, block, 0, st, x, a, part_words);
+    else hipLaunchKernelGGL((linear_table_kernel<2, ROWS>), grid, block, 0, st, x, a, part_words);
+}
+
+// Where the table pays for its fill pass and 512-channel workgroups (MI355X, graph
+// replays, against the kernel above): 25088 -> 4096 at batch 1 25.0 against 41.4 us
+// (2.7 TB/s of packed weights), 17000 -> 1000 with 3-bit codes 8.0 against 14.2, 9000
+// -> 1700 with 2-bit codes (15 M terms) 7.7 against 10.7; 4096 -> 4096 at batch 2, 8,
+// 32, 128 10.1, 16.6, 44, 150 against 11.5, 21.4, 63, 232; 2048 -> 1000 at batch 128
+// 26 against 33. Smaller ones keep the kernel above: 2048 -> 1000 at batch 8 (16 M)
+// 7.9 against 9.4, 512 -> 1000 at batch 32 5.8 against 9.4, 4383 -> 67 at batch 4 6.5
+// against 8.9. DS_ROWS_BATCH: 16 forces the table, its other values the kernel above.
+static bool table_path(const ConvGeom &g)
+{
+    const int forced = tuning(kRowsBatch);
+    if (forced == 16) return true;
+    const int64_t terms = int64_t(g.n) * g.c * g.k;
+    return forced < 0 && g.k >= 256 && terms >= (g.n == 1 ? 14000000 : 24000000);
+}
+
+static hipError_t run_table(const ConvGeom &g, const int32_t *x, const uint32_t *wp, const int32_t *bias, int32_t *y,
+                            hipStream_t st, const Epilogue &epi)
+{
+    hipError_t e = bias ? run_fill_init(g, bias, y, st) : run_fill_zero(y, int64_t(g.n) * g.k, st);
+    if (e != hipSuccess) return e;
+    RowsArgs a;
+    a.wp = wp;
+    a.wi = nullptr;
+    a.bias = nullptr;
+    a.y = y;
+    a.B = g.n;
+    a.C = g.c;
+    a.K = g.k;
+    a.wpr = int(row_words_bits(g.c, g.bits));
+    const int rows = g.n >= 3 ? 4 : g.n;
+    const int64_t blocks = int64_t((g.k + kTableThreads - 1) / kTableThreads) * ((g.n + rows - 1) / rows);
+    // Parts of at least 16 words (64 bytes of each row), 1024 workgroups (25088 -> 4096
+    // at batch 1: 35.3, 29.9, 25.0, 24.8, 27.0 us with 256, 512, 768, 1024, 1536).
+    const int64_t parts = std::max<int64_t>(1, std::min<int64_t>((a.wpr + 15) / 16, 1024 / blocks));
+    const int part_words = (int((a.wpr + parts - 1) / parts) + 15) & ~15;
+    const dim3 grid(unsigned((g.k + kTableThreads - 1) / kTableThreads), unsigned((g.n + rows - 1) / rows),
+                    unsigned((a.wpr + part_words - 1) / part_words));
+    if (rows == 4) launch_table<4>(grid, x, a, part_words, g.bits, st);
+    else if (rows == 2) launch_table<2>(grid, x, a, part_words, g.bits, st);
+    else launch_table<1>(grid, x, a, part_words, g.bits, st);
+    e = hipGetLastError();
+    return e == hipSuccess && epi.any() ? run_epilogue(g, y, epi, st) : e;
 }
 
 static ConvLayout conv_layout(const ConvGeom &g0, const OutMap &map, const Padded &pad)
