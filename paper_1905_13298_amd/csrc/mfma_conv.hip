@@ -979,7 +979,7 @@ MfmaLayout mfma_layout(const ConvGeom &g, bool shared, int tasks)
     // block counts, and rows and columns in 16 bits (the extents, a window's start up
     // to a padding before them, a tap up to a window after it).
     constexpr int64_t kMax = int64_t(1) << 31;
-    l.fits = cb * np * kXpBytes < kMax - 512 && nchunks * kStageBytes < kMax && tiles_p * tiles_k < kMax / 4 &&
+    l.fits = cb * np * kXpBytes < kMax - 512 && nchunks * kStageBytes < kMax - 65536 && tiles_p * tiles_k < kMax / 4 &&
              tiles_k * nchunks < kMax / 8 && cb * nblk < kMax / 4 && int64_t(g.n) * g.k * g.oh * g.ow < kMax &&
              std::max(l.PH, l.PW) < 16384 && std::max(g.r, g.s) < 8192 &&
              std::max(std::abs(g.ph), std::abs(g.pw)) < 8192;
@@ -998,10 +998,16 @@ MfmaLayout mfma_layout(const ConvGeom &g, bool shared, int tasks)
     l.tiles_p = int(tiles_p);
     l.tiles_k = int(tiles_k);
     // Two workgroups fit a CU: a smaller grid splits the reduction, keeping two chunks
-    // per part.
+    // per part. That pays for long reductions only: y is filled first, its parts are
+    // added to it and an epilogue is a pass of its own, while a workgroup alone on a CU
+    // takes 2.2 us a chunk and two together 3.7. Measured (plans with a ReLU; without)
+    // split and whole: 196 tiles of 18 chunks 62.5, 56.5 and 54.2, 54.8 us; 148 of 16
+    // 63.6, 58.1 and 56.4, 55.7; 92 of 8 42.5, 36.6 and 33.3, 33.2; the other way 148 of
+    // 18 55.9, 50.0 and 53.6, 54.5; 64 of 8 32.2, 28.0 and 30.6, 30.0; 200 of 72 148,
+    // 144 and 158, 160.
     const int64_t tiles = tiles_p * tiles_k * tasks;
     int64_t splits = 1;
-    if (tiles < 384) splits = std::max<int64_t>(1, std::min<int64_t>(512 / tiles, nchunks / 2));
+    if (tiles < 9 * nchunks) splits = std::max<int64_t>(1, std::min<int64_t>(512 / tiles, nchunks / 2));
     l.cps = int((nchunks + splits - 1) / splits);
     l.splits = int((nchunks + l.cps - 1) / l.cps);
     return l;
@@ -1022,8 +1028,8 @@ bool mfma_prefer(const ConvGeom &g, int64_t terms)
 
 // A plan's two paths, in microseconds on MI355X (graph replays). Here: two launches
 // and what a tile does besides its products (10), the packed copy of x written and
-// read at 5.5 TB/s, the products of whole tiles at 130 T terms/s, y at 4 TB/s, 15
-// for a split reduction. Generated code: 50 T terms/s at the ResNets' share of zero
+// read at 5.5 TB/s, the products of whole tiles at 130 T terms/s (2.2 a chunk at
+// least), y at 4 TB/s, 15 for a split reduction. Generated code: 50 T terms/s at the ResNets' share of zero
 // weights, and a launch. Measured (estimated) here against generated code: 256 ->
 // 256 3x3 on 14x14 at batch 128 138 (138) against 280 (299), 64 -> 64 3x3 on 56x56
 // 177 (181) against 278 (299), 1024 -> 256 on 14x14 95 (98) against 134 (135), 512
@@ -1038,7 +1044,8 @@ bool mfma_prefer_plan(const MfmaTask *tasks, size_t ntasks, int64_t x_elems, int
     bool split = false;
     for (size_t i = 0; i < ntasks; ++i) {
         const MfmaTask &t = tasks[i];
-        us += double(t.l.tiles_p) * kPix * t.l.tiles_k * kRows * t.l.nchunks * 64.0 / 130e6 +
+        us += std::max(double(t.l.tiles_p) * kPix * t.l.tiles_k * kRows * t.l.nchunks * 64.0 / 130e6,
+                       ntasks == 1 ? 2.2 * t.l.cps : 0.0) +
               4.0 * t.g.n * double(t.g.k) * t.g.oh * t.g.ow / 4e6;
         split = split || t.l.splits > 1;
     }
