@@ -162,22 +162,28 @@ __device__ void prep_weights(const uint32_t *__restrict__ wp, const WeightTask &
 {
     const Reduction &d = t.d;
     constexpr int kPitch = 80;   // bytes per row of codes: 16-byte reads, spread over the banks
-    __shared__ uint32_t lut[4][32];
+    __shared__ uint2 lut[4][32], sizes[32];
     __shared__ __align__(16) unsigned char codes[32][kPitch];
     const int tid = threadIdx.x, group = tid >> 6, lane = tid & 63, half = lane >> 5;
     const int unit = block >> 1, mt = block & 1;
     const int mblk = unit / d.nchunks, ch = unit - mblk * d.nchunks;
     if (tid < 128) {
-        // A code's entries in a group's four matrices: 6 + 6 + 4 + 4 bits.
+        // A code's entries in a group's four matrices: two of 6 bits in the halves of x,
+        // two of 4 in those of y, so that neighbours are joined for both at once. (About twelve
+        // instructions a code with all four in one word, five so; the expansion of 4096 x
+        // 4096 codes, 168 MB, 58.6 us then and 45.7 now.)
         const int g = tid >> 5, code = tid & 31, s = code & 15, neg = code >> 4;
-        uint32_t v = 0;
+        uint2 v{};
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
             const uint32_t a = fp6_code(2 * g + i, s), b = fp4_code(2 * g + i, s);
-            v |= (a && neg ? a | 32u : a) << (6 * i);
-            v |= (b && neg ? b | 8u : b) << (12 + 4 * i);
+            v.x |= (a && neg ? a | 32u : a) << (16 * i);
+            v.y |= (b && neg ? b | 8u : b) << (16 * i);
         }
         lut[g][code] = v;
+        // Its shares of the bounds: x = p0 | r1 << 20 (32 codes stay below 2^20, 2^11).
+        if (g == 0)
+            sizes[code] = uint2{uint32_t(s <= 5 ? 4095 >> s | 32 >> s << 20 : 0), uint32_t(s >= 6 && s < 15 ? 65536 >> s : 0)};
     }
     {
         // Eight codes per thread: row tid / 8, elements 8 (tid % 8) .. of one block.
@@ -203,7 +209,7 @@ __device__ void prep_weights(const uint32_t *__restrict__ wp, const WeightTask &
         }
         v2i w{};
 #pragma unroll
-        for (int e = 0; e < 8; ++e) w[e >> 2] |= int(c8[e] << (8 * (e & 3)));
+        for (int e = 0; e < 8; ++e) w[e >> 2] |= int(c8[e] << (8 * (e & 3) + 3));   // times an entry's bytes
         *reinterpret_cast<v2i *>(&codes[row][seg * 8]) = w;
     }
     __syncthreads();
@@ -211,22 +217,28 @@ __device__ void prep_weights(const uint32_t *__restrict__ wp, const WeightTask &
     cw[0] = *reinterpret_cast<const v4i *>(&codes[lane & 31][half * 32]);
     cw[1] = *reinterpret_cast<const v4i *>(&codes[lane & 31][half * 32 + 16]);
     uint32_t o6[2][6] = {}, o4[2][4] = {};
-    int p0 = 0, q0 = 0, r1 = 0;
+    auto entry = [&](const uint2 *table, int e) {
+        const uint32_t byte = (uint32_t(cw[e >> 4][(e >> 2) & 3]) >> (8 * (e & 3))) & 255u;
+        return *reinterpret_cast<const uint2 *>(reinterpret_cast<const unsigned char *>(table) + byte);
+    };
+    auto put12 = [](uint32_t (&o)[6], int pair, uint32_t v) {
+        const int at = 12 * pair, sh = at & 31;
+        o[at >> 5] |= v << sh;
+        if (sh + 12 > 32) o[(at >> 5) + 1] |= v >> (32 - sh);
+    };
 #pragma unroll
-    for (int e = 0; e < kBlockK; ++e) {
-        const uint32_t code = (uint32_t(cw[e >> 4][(e >> 2) & 3]) >> (8 * (e & 3))) & 31u;
-        const uint32_t v = lut[group][code];
+    for (int e = 0; e < kBlockK; e += 8) {
+        uint32_t four[2] = {};
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            put6(o6[i], e, (v >> (6 * i)) & 63u);
-            o4[i][e >> 3] |= ((v >> (12 + 4 * i)) & 15u) << (4 * (e & 7));
+        for (int j = 0; j < 8; j += 2) {
+            const uint2 u = entry(lut[group], e + j), v = entry(lut[group], e + j + 1);
+            const uint32_t six = u.x | v.x << 6;
+            put12(o6[0], (e + j) / 2, six & 0xffffu);
+            put12(o6[1], (e + j) / 2, six >> 16);
+            four[j >> 2] |= (u.y | v.y << 4) << (4 * (j & 2));
         }
-        if (group == 0) {
-            const int sft = int(code & 15u);
-            p0 += sft <= 5 ? 4095 >> sft : 0;
-            r1 += sft <= 5 ? 32 >> sft : 0;
-            q0 += sft >= 6 && sft < 15 ? 65536 >> sft : 0;
-        }
+        o4[0][e >> 3] = (four[0] & 0xffffu) | four[1] << 16;
+        o4[1][e >> 3] = four[0] >> 16 | (four[1] & 0xffff0000u);
     }
     unsigned char *st = t.wa + int64_t(unit) * kStageBytes;
 #pragma unroll
@@ -239,6 +251,15 @@ __device__ void prep_weights(const uint32_t *__restrict__ wp, const WeightTask &
             v4i{int(o4[i][0]), int(o4[i][1]), int(o4[i][2]), int(o4[i][3])};
     }
     if (group == 0) {
+        uint32_t pr = 0;
+        int q0 = 0;
+#pragma unroll
+        for (int e = 0; e < kBlockK; ++e) {
+            const uint2 v = entry(sizes, e);
+            pr += v.x;
+            q0 += int(v.y);
+        }
+        int p0 = int(pr & 0xfffffu), r1 = int(pr >> 20);
         // A row's two halves together, then the largest over the rows.
         p0 += __shfl_xor(p0, 32);
         q0 += __shfl_xor(q0, 32);
