@@ -3,26 +3,28 @@
 A step is one pass of every layer of the workload (each layer's ConvShift or
 LinearShift call on its own seeded input, all inputs resident in HBM).
 Two paths compute the same outputs bit for bit (checked before timing):
-  jit      (default) a weight-specialised plan per layer, its code generated
-           at setup from the fixed weights (Section 6's run-time compilation);
+  jit      (default) a plan per layer, made at setup from the fixed weights: code
+           generated from them (Section 6's run-time compilation), or their matrices
+           for the matrix cores where those are expected to be faster;
            a layer whose plan is not preferred (JitConv.preferred: a cost
            model of both paths, in the per-layer JSON) runs the runtime kernel
   runtime  ds_conv2d_shift / ds_linear_shift with the packed weights as data
 Prints ONE JSON line:
   value       whole-step throughput in G shift-accumulates/s (dense SAC =
               output elements x reduction terms, zero weights included)
-  roofline    the dominant kernel against the int32 VALU roofline: the runtime
-              kernel at 2 VALU instructions per dense shift-accumulate (one of
+  roofline    the dominant kernel: the matrix-core kernel at 20 f8f6f4 products
+              per dense shift-accumulate; or the int32 VALU roofline: the vector
+              kernels at 2 VALU instructions per dense shift-accumulate (one of
               them three-operand, 64 lanes per CU per clock); the generated
               kernel at one two-operand add/sub per non-zero weight term (128
               lanes per CU per clock)
   runtime_weights  the runtime path timed on the same inputs (path jit)
   cpu_baseline the oracle on the host cores, on a prefix (small batch) of
               the same seeded inputs
-  mul_comparison  the multiplication-based comparison on the same layers, at
-              the tiling of each shift path: int32 and 24-bit multiply-adds in
-              the runtime kernel's tiling, 24-bit multiply-adds baked into
-              plans like the shifts
+  mul_comparison  the multiplication-based comparison on the same layers:
+              int32 and 24-bit multiply-adds in the tiling of the vector
+              kernels, 24-bit multiply-adds baked into generated code (the
+              matrix cores take over from both shift paths where faster)
 
 Usage: python bench.py [--gpus 1] [--steps K] [--warmup W] [--workload resnet50]
                        [--path jit|runtime]
@@ -73,6 +75,11 @@ CUS, LANES_PER_CU, CLOCK_GHZ = 256, 64, 2.4
 INT32_OPS_PEAK_T = CUS * LANES_PER_CU * CLOCK_GHZ / 1000.0        # 39.32 T int32 ops/s (VOP3)
 VOP2_OPS_PEAK_T = 2 * INT32_OPS_PEAK_T                              # 78.64 T int32 ops/s (VOP2)
 SAC_PEAK_T = INT32_OPS_PEAK_T / 2.0                                  # 19.66 T SAC/s
+# A SIMD's matrix core forms the products of a 32 x 32 x 64 instruction on 6- and 4-bit
+# operands in 32 clocks: 5.03 P products/s; a register-only probe reached
+# 4.40. A dense shift-accumulate takes 20 of them.
+MATRIX_PRODUCTS = 20
+MATRIX_SAC_PEAK_T = CUS * 4 * 32 * 32 * 64 / 32 * CLOCK_GHZ / 1000.0 / MATRIX_PRODUCTS   # 251.7 T SAC/s
 HBM_PEAK_GBS = 8000.0
 
 
@@ -141,8 +148,17 @@ JIT_KERNEL = "ds_jit_conv_template"
 JIT_ENTRY_POINTS = ("ds_jit_conv_template", "ds_jit_conv_one_tap_template")
 
 
-def is_jit_kernel(name: str) -> bool:
-    return any(e in name for e in JIT_ENTRY_POINTS)
+MATRIX_KERNEL = "mfma_conv_kernel"
+
+
+def planned_kernel(kernel_name: str):
+    """What group_name takes for a layer whose main dispatch has this name."""
+    return MATRIX_KERNEL if MATRIX_KERNEL in kernel_name else any(e in kernel_name for e in JIT_ENTRY_POINTS)
+
+
+def plan_kind(plan):
+    """The same for a plan (None: the layer runs the runtime call)."""
+    return MATRIX_KERNEL if plan is not None and plan.matrix_cores else plan is not None
 
 # Per kernel family: the sources its code comes from, and the committed HBM
 # traffic record of its counters on the ResNet-50 workload.
@@ -175,7 +191,7 @@ def _pmc_rows(directory: str):
     return [rows[k] for k in sorted(rows)]
 
 
-MAIN_KERNELS = ("tiled_kernel", "conv_direct_kernel", "linear_rows_kernel") + JIT_ENTRY_POINTS
+MAIN_KERNELS = ("tiled_kernel", "conv_direct_kernel", "linear_rows_kernel", "linear_table_kernel", MATRIX_KERNEL) + JIT_ENTRY_POINTS
 
 
 def _main_rows(rows, layers):
@@ -197,7 +213,7 @@ def pmc_summary(copy_fetch, copy_write, fetch, write, copy_bytes, workload, path
     w_rows = _main_rows(_pmc_rows(write), layers)
     per_kernel = {}
     for L, fr, wr in zip(layers, f_rows, w_rows):
-        name = group_name(L, path, is_jit_kernel(fr["name"]))
+        name = group_name(L, path, planned_kernel(fr["name"]))
         k = per_kernel.setdefault(name, {"launches": 0, "fetch_bytes": 0.0, "write_bytes": 0.0,
                                           "algorithmic_bytes": 0})
         k["launches"] += 1
@@ -232,7 +248,7 @@ def sq_summary(directory, workload, path):
     per = {}
     for li, (L, r) in enumerate(zip(layers, rows)):
         codes = W.gen_codes(L, seed, li)
-        name = group_name(L, path, is_jit_kernel(r["name"]))
+        name = group_name(L, path, planned_kernel(r["name"]))
         k = per.setdefault(name, {"launches": 0, "sac": 0, "nz": 0.0, "ns": 0})
         k["launches"] += 1
         k["sac"] += L.sac
@@ -393,7 +409,7 @@ def bench_convert(args):
 def bench_network(args):
     """One step = one forward pass of the network over the batch (every op on the GPU,
     input resident in HBM); reported in images/s, with the shift convolutions'
-    rate against the VALU roofline."""
+    rate against the roofline of the kernels that most of their time goes to."""
     import torch
     from paper_1905_13298_amd import workloads as W
     from paper_1905_13298_amd.network import ShiftNetwork
@@ -446,7 +462,23 @@ def bench_network(args):
     common = {"traffic": None, "launches_per_step": len(conv_idx),
               "avg_launch_ms": round(conv_ms / len(conv_idx), 5), "sac_per_launch_avg": sac // len(conv_idx),
               "dense_tsac_s": round(sac / (conv_ms * 1e-3) / 1e12, 4)}
-    if args.path == "jit":
+    # the kernel family with the most time of the step
+    fam = {}
+    for i in conv_idx:
+        L = graph[i]["layer"]
+        plan = nets[args.path].plans.get(L.name)
+        kernel = group_name(L, args.path, plan_kind(plan))
+        kernel = kernel if kernel in (JIT_KERNEL, MATRIX_KERNEL) else "vector"
+        fam[kernel] = fam.get(kernel, 0.0) + float(op_ms[i])
+    if max(fam, key=fam.get) == MATRIX_KERNEL:
+        achieved = sac / (conv_ms * 1e-3) / 1e12
+        roofline = {"bound": "alu", "achieved": round(achieved, 4), "peak": round(MATRIX_SAC_PEAK_T, 4),
+                    "unit": "TSAC/s", "frac": round(achieved / MATRIX_SAC_PEAK_T, 4), **common,
+                    "work_unit": "dense shift-accumulate, 20 f8f6f4 products each",
+                    "kernel": "shift convolutions with fused epilogue (all 21 layers)",
+                    "ms_by_kernel": {k: round(v, 4) for k, v in fam.items()},
+                    "timed_span": "library call per layer"}
+    elif args.path == "jit":
         achieved = nz / (conv_ms * 1e-3) / 1e12
         roofline = {"bound": "alu", "achieved": round(achieved, 4), "peak": round(VOP2_OPS_PEAK_T, 4),
                     "unit": "T int32 ops/s", "frac": round(achieved / VOP2_OPS_PEAK_T, 4), **common,
@@ -569,7 +601,8 @@ def bench_backward(args):
     value = sac_step / (ms_per_step * 1e-3) / 1e9
     groups = {}
     for i, (li, L) in enumerate(layers):
-        gname = JIT_KERNEL if plans[i] is not None else names[i]
+        gname = MATRIX_KERNEL if plan_kind(plans[i]) == MATRIX_KERNEL or (
+            plans[i] is None and "matrix cores" in names[i]) else JIT_KERNEL if plans[i] is not None else names[i]
         g = groups.setdefault(gname, {"sac": 0, "nz": 0.0, "ms": 0.0, "launches": 0, "bytes": 0})
         g["sac"] += L.sac
         g["nz"] += L.sac * nonzero[i]
@@ -589,6 +622,13 @@ def bench_backward(args):
                     "entry_points": list(JIT_ENTRY_POINTS),
                     "dense_tsac_s": round(g["sac"] / (g["ms"] * 1e-3) / 1e12, 4),
                     "timed_span": "library call per layer (zero fills, the phases' generated kernels)"}
+    elif name == MATRIX_KERNEL:
+        achieved = g["sac"] / (g["ms"] * 1e-3) / 1e12
+        roofline = {"bound": "alu", "achieved": round(achieved, 4), "peak": round(MATRIX_SAC_PEAK_T, 4),
+                    "unit": "TSAC/s", "frac": round(achieved / MATRIX_SAC_PEAK_T, 4), **common,
+                    "work_unit": "dense shift-accumulate, 20 f8f6f4 products each",
+                    "timed_span": "library call per layer (zero fills, dy packed, weights expanded unless a plan "
+                                  "holds them, products of all phases)"}
     else:
         achieved = g["sac"] / (g["ms"] * 1e-3) / 1e12
         roofline = {"bound": "alu", "achieved": round(achieved, 4), "peak": round(SAC_PEAK_T, 4),
@@ -692,12 +732,16 @@ def jit_supported(L) -> bool:
     return L.kind in ("conv", "linear")
 
 
-def group_name(L, path: str, planned: bool | None = None) -> str:
+def group_name(L, path: str, planned=None) -> str:
     """The kernel a layer's call is accounted to (one kernel instance). `planned`:
-    whether the layer runs a weight-specialised plan (default: whenever one covers it)."""
+    whether the layer runs generated code (default: whenever a plan covers it), or
+    MATRIX_KERNEL."""
+    if planned == MATRIX_KERNEL:
+        return MATRIX_KERNEL
     if path == "jit" and (jit_supported(L) if planned is None else planned):
         return JIT_KERNEL
-    return kernel_variant(L).rsplit(" splits", 1)[0]
+    variant = kernel_variant(L)
+    return MATRIX_KERNEL if "matrix cores" in variant else variant.rsplit(" splits", 1)[0]
 
 
 def time_graph(calls, outs, steps, warmup):
@@ -823,6 +867,12 @@ def roofline_of(layers, d, path, nonzero, planned=None, act_bits=32, workload=No
                 "nonzero_sac_per_launch_avg": int(g["nz"] // g["launches"]),
                 "dense_tsac_s": round(dense, 4),
                 "timed_span": "library call per launch (split-K fill pass, or for a LinearShift on x^T the transposing passes, + generated kernel)"}
+    if name == MATRIX_KERNEL:
+        return {"bound": "alu", "achieved": round(dense, 4), "peak": round(MATRIX_SAC_PEAK_T, 4),
+                "unit": "TSAC/s", "frac": round(dense / MATRIX_SAC_PEAK_T, 4), **common,
+                "work_unit": "dense shift-accumulate, 20 f8f6f4 products each",
+                "timed_span": "library call per launch (x packed, weights expanded unless a plan holds them, products, "
+                              "and a split reduction's epilogue)"}
     return {"bound": "alu", "achieved": round(dense, 4), "peak": round(SAC_PEAK_T, 4),
             "unit": "TSAC/s", "frac": round(dense / SAC_PEAK_T, 4), **common,
             "work_unit": "dense shift-accumulate, 2 int32 VALU ops each",
@@ -936,7 +986,7 @@ def bench_layers(args):
         timing = {"mode": "HIP graph of consecutive steps, replayed", "steps_per_graph": rep,
                   "graph_ms_per_step": round(ms_per_step, 5), "eager_ms_per_step": timing["eager_ms_per_step"]}
     value = sac_step / (ms_per_step * 1e-3) / 1e9
-    planned = [p is not None for p in plans]
+    planned = [plan_kind(p) for p in plans]
     wl_name = W.CONFIG_NAMES[cfg] if cfg is not None else args.workload
     roofline = roofline_of(layers, d, args.path, nonzero, planned, act, workload=wl_name)
 
@@ -950,28 +1000,32 @@ def bench_layers(args):
                    "roofline": roofline_of(layers, d_rt, "runtime", nonzero, workload=wl_name)}
 
     per_layer = []
-    fr = [L.sac * nonzero[li] / (float(np.median(d[:, li])) * 1e-3) / 1e12 / VOP2_OPS_PEAK_T
-          for li, L in enumerate(layers)]
+
+    def frac(li):
+        # against the peak of the kernel the layer runs
+        name, t = group_name(layers[li], args.path, planned[li]), float(np.median(d[:, li])) * 1e9
+        if name == JIT_KERNEL:
+            return layers[li].sac * nonzero[li] / t / VOP2_OPS_PEAK_T
+        return layers[li].sac / t / (MATRIX_SAC_PEAK_T if name == MATRIX_KERNEL else SAC_PEAK_T)
+
+    fr = [frac(li) for li in range(len(layers))]
     order = np.argsort(fr)
     layer_summary = {
         "layers": len(layers),
-        "frac_basis": ("non-zero terms / (median call time x 78.64 T VOP2 lane-ops/s)" if args.path == "jit"
-                       else "dense SAC / (median call time x 19.66 T SAC/s)"),
-        "min_frac": round(float(min(fr)), 4) if args.path == "jit" else None,
-        "median_frac": round(float(np.median(fr)), 4) if args.path == "jit" else None,
-        "layers_frac_ge_0_6": int(sum(f >= 0.6 for f in fr)) if args.path == "jit" else None,
-        "worst": [[layers[i].name, round(float(fr[i]), 3)] for i in order[:5]] if args.path == "jit" else None,
+        "frac_basis": "of the kernel a layer runs: dense SAC / (median call time x 251.7 T SAC/s) on the matrix "
+                      "cores, non-zero terms / (x 78.64 T VOP2 lane-ops/s) in generated code, dense SAC / (x 19.66 T "
+                      "SAC/s) in the vector kernels",
+        "matrix_core_layers": sum(group_name(L, args.path, planned[li]) == MATRIX_KERNEL for li, L in enumerate(layers)),
+        "min_frac": round(float(min(fr)), 4),
+        "median_frac": round(float(np.median(fr)), 4),
+        "layers_frac_ge_0_6": int(sum(f >= 0.6 for f in fr)),
+        "worst": [[layers[i].name, round(float(fr[i]), 3)] for i in order[:5]],
         "nonzero_tsac_s": round(nz_step / (ms_per_step * 1e-3) / 1e12, 3),
         "per_layer": [[L.name, round(float(np.median(d[:, li])), 5),
                        round(L.sac / (float(np.median(d[:, li])) * 1e-3) / 1e9, 1)]
                       for li, L in enumerate(layers)],
         "per_layer_fields": ["layer", "median ms", "dense G SAC/s"],
     }
-    if args.path != "jit":
-        frs = [L.sac / (float(np.median(d[:, li])) * 1e-3) / 1e12 / SAC_PEAK_T for li, L in enumerate(layers)]
-        layer_summary.update({"min_frac": round(float(min(frs)), 4), "median_frac": round(float(np.median(frs)), 4),
-                              "layers_frac_ge_0_6": int(sum(f >= 0.6 for f in frs)),
-                              "worst": [[layers[i].name, round(float(frs[i]), 3)] for i in np.argsort(frs)[:5]]})
     for li, L in enumerate(layers):
         med = float(np.median(d[:, li]))
         row = {
@@ -1009,7 +1063,7 @@ def bench_layers(args):
         per_layer[li]["rejected_plan_ms_median"] = float(np.median(d_rej[:, 0]))
         plan.close()
 
-    # ---- multiplication-based comparison, each against the shift path of the same tiling
+    # ---- multiplication-based comparison, each against the shift path that takes the same weights
     mul = None
     if not args.no_mul and act == 32:
         rt_shift_ms = runtime["ms_per_step"] if runtime is not None else (
@@ -1027,8 +1081,8 @@ def bench_layers(args):
         torch.cuda.empty_cache()
         cpu = cpu_baseline(args, cfg, seed, layers, act) if cfg is not None else None
 
-    path_desc = ("weight-specialised plans (code generated per layer at setup), the runtime "
-                 "kernel where a plan is not preferred"
+    path_desc = ("plans made per layer at setup (generated code, or the matrix cores), the runtime "
+                 "call where a plan is not preferred"
                  if args.path == "jit" else "runtime weights (ds_conv2d_shift / ds_linear_shift)")
     out = {
         "metric": "G shift-accumulates/s per layer and % of int32 VALU peak on one MI355X",
@@ -1059,7 +1113,7 @@ def bench_layers(args):
 def mul_comparison(args, res, layers, seed, stream, rt_shift_ms, plan_shift_ms):
     """The multiplication-based comparison (the paper's Section 6 times its shift
     kernels against a multiplication kernel), each timed against the shift path
-    of the same tiling: the runtime kernel's tiling with an int32 multiply-add
+    that takes its weights the same way: the vector kernels' tiling with an int32 multiply-add
     (v_mul_lo_u32 + v_add3_u32, 1.5 instructions per term) and with a 24-bit one
     (v_mad_i32_i24), on random 16-bit weights; and the plans' tiling, with each
     layer's own weights as 14-bit fixed-point integers sign * 2^(14 - shift)

@@ -36,14 +36,16 @@
  * take device pointers on the current HIP device; the pack/unpack helpers
  * take host pointers. y must not overlap any input. The runtime-weights
  * entry points (ds_linear_shift, ds_conv2d_shift and their variants) take
- * device scratch memory (decoded weights, per-channel start values, transposed
- * operands; none for a LinearShift of fewer than 256 rows, whose kernel decodes
- * the packed codes itself) in stream order from the device's default memory pool
+ * device scratch memory (a packed copy of x and expanded weights on the matrix
+ * cores; decoded weights, per-channel start values, transposed operands; none for
+ * a LinearShift of fewer than 256 rows, whose kernel decodes the packed codes
+ * itself) in stream order from the device's default memory pool
  * (hipMallocAsync) and give it back in stream order (hipFreeAsync) within the
  * same call: the library keeps no pool and no device memory between calls.
  * Under the runtime's default release threshold the memory returns to the
- * driver at the caller's next synchronisation. Callers that cannot allocate
- * use ds_conv2d_shift_noalloc (below). Plans (ds_jit_conv_*) hold the device
+ * driver at the caller's next synchronisation. Callers with memory of their own
+ * use the _ws variants (below), callers that cannot allocate
+ * ds_conv2d_shift_noalloc (below). Plans (ds_jit_conv_*) hold the device
  * memory they need from create to destroy.
  *
  * Errors: arguments are validated before any device work. On a validation
@@ -304,8 +306,9 @@ ds_status ds_avgpool2d_global(const int32_t *x, int32_t *y, int64_t n, int64_t c
  * w_packed device uint32, the forward layer's packed weights [k][ds_packed_row_words(c*r*s)]
  * dx       device int32 [n][c][h][w], written (not accumulated); must not overlap dy or w_packed
  * flags    0, or DS_CODE_BITS(b) for b-bit packed codes; stream as for ds_linear_shift.
- * Device scratch (re-packed codes per stride phase, decoded weights) comes from
- * the library's stream-ordered pool, as for the forward operators.
+ * Device scratch (the packed copy of dy and expanded weights on the matrix cores;
+ * re-packed codes per stride phase, decoded weights) comes from the device's
+ * stream-ordered pool, as for the forward operators.
  * Errors as for ds_conv2d_shift. */
 ds_status ds_conv2d_shift_backward_data(const int32_t *dy, const uint32_t *w_packed, int32_t *dx,
                                         int64_t n, int64_t c, int64_t h, int64_t w, int64_t k,
@@ -404,13 +407,14 @@ ds_status ds_conv2d_shift_describe(int64_t n, int64_t c, int64_t h, int64_t w, i
  * DS_ACT_I16 / DS_ACT_I8), residual and y [n][k][oh][ow] (int32), device
  * memory on the plan's device; residual must be non-NULL exactly when the
  * plan was made with DS_JIT_RESIDUAL. Asynchronous on `stream`. y must not
- * overlap x or residual. A plan may hold device scratch (the padded or
- * transposed copy of x; y^T; the partial sums of split strided phases of an
+ * overlap x or residual. A plan may hold device scratch (the padded,
+ * transposed or packed copy of x; y^T; the partial sums of split strided phases of an
  * input-gradient plan), so runs
  * of one plan must not overlap in time: issue them on one stream, or order
  * them with events.
  *
- * ds_jit_conv_image: the code object ds_jit_conv_create would load, written
+ * ds_jit_conv_image: the code object that generated code for the plan makes (the
+ * one ds_jit_conv_create would load, unless it takes the matrix cores), written
  * to host memory `image` of `capacity` bytes (*size = bytes needed;
  * DS_ERR_BUFFER_TOO_SMALL when capacity is short). Touches no device; for
  * inspection and tests.

@@ -12,7 +12,8 @@
 // order (t' = Ta - 1 - t) makes each phase (a, b) an ordinary stride-1
 // correlation of dy with a Ta x Tb window, top padding pt = Ta - 1 - q (left
 // likewise), whose outputs land on a regular sub-grid of dx. Each phase runs
-// on the forward tiled kernel: its codes are re-packed (rows = input channels
+// on the forward kernels: large problems as tasks of one launch on the matrix
+// cores (mfma_conv.hip), the others on the tiled kernel, where its codes are re-packed (rows = input channels
 // c, columns = (k, t', u') in the kernel's reduction order), and an output map
 // places output (n, c, i, j) at dx[n][c][a + sh*i][b + sw*j]. Phases without
 // taps are zero. A stride-1 layer is a single phase (the rotated, transposed

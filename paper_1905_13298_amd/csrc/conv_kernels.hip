@@ -1,5 +1,6 @@
-// Kernels of the shift operators for CDNA4 (gfx950) and the host code that
-// plans and launches them.
+// Vector kernels of the shift operators for CDNA4 (gfx950) and the host code that
+// plans and launches them; convolutions large enough (mfma_prefer) run on the matrix
+// cores instead (mfma_conv.hip).
 //
 // The computation (DeepShift Section 3, Eqs. 1-3, Figure 1a) is an implicit
 // GEMM over output pixels q = (n, oh, ow) and output channels k with the

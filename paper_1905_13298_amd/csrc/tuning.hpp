@@ -8,7 +8,8 @@
 namespace ds {
 
 enum Knob {
-    kForceVariant,   // DS_FORCE_VARIANT: 0 one-thread-per-output kernel, 8 tiled with 8 pixels per lane
+    kForceVariant,   // DS_FORCE_VARIANT: 0 one-thread-per-output kernel, 4 or 8 tiled (vector) kernel,
+                     // 8: with 8 pixels per lane; 64 matrix cores; plans: any but 64 generated code
     kJitWsplit,      // DS_JIT_WSPLIT: waves per 64 pixels in a plan (1, 2, 4, 8, 16)
     kJitSlots,       // DS_JIT_SLOTS: loads in flight per wave in a plan
     kJitMap,         // DS_JIT_MAP: 96 = the 96-register code for one-tap layers too
@@ -16,7 +17,8 @@ enum Knob {
     kJitOrder,       // DS_JIT_ORDER: 0 grouped, 1 tile-major, 2 XCD-local tile-major
     kJitTn,          // DS_JIT_TN: output channels per code segment in a plan (16, 32, 64)
     kJitPgroups,     // DS_JIT_PGROUPS: groups of 64 pixels per workgroup in a plan (1, 2, 4)
-    kRowsBatch,      // DS_ROWS_BATCH: batch rows per workgroup of the small-batch LinearShift (1, 2, 4, 8)
+    kRowsBatch,      // DS_ROWS_BATCH: batch rows per workgroup of the small-batch LinearShift (1, 2, 4, 8);
+                     // 16: its table kernel
     kJitTranspose,   // DS_JIT_TRANSPOSE: LinearShift plans on x^T: 0 never, 1 from batch 2 (default: batch >= 32)
     kKnobs
 };

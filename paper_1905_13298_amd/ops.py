@@ -510,8 +510,9 @@ class JitConv:
         # Whether the plan runs on the matrix cores rather than generated code.
         self.matrix_cores = bool(lib().ds_jit_conv_matrix_cores(self._h))
 
-    # Cost model of the two paths on MI355X (microseconds), fitted to calls timed
-    # back to back. A plan's waves each stream their share of the straight-line
+    # Cost model of generated code and the vector kernels on MI355X (microseconds),
+    # fitted to calls timed back to back. (A call or plan on the matrix cores is the
+    # faster of its kind already: the plan holds the weights the call expands.) A plan's waves each stream their share of the straight-line
     # code at about 1.6 GB/s when few waves share it (instruction fetch: a 64-byte
     # line per L2 round trip with a few in flight; the 4096 -> 4096 LinearShift
     # at batch 256, 290 KB per wave, 174 us), and the chip issues at most 0.355
@@ -564,17 +565,15 @@ class JitConv:
     def preferred(self) -> bool:
         """Whether this plan is expected to beat the runtime kernel, by the cost
         model above. Measured on MI355X as graph replays (model in brackets),
-        plan against runtime kernel: 4096 -> 4096 at batch 256 on x^T 104-109
-        us (108) against 346 us (329); 2048 -> 1000 at batch 128 on x^T 17.0 us
+        plan against runtime call: 4096 -> 4096 at batch 256, both on the matrix
+        cores, 64 us against 94; generated code against the vector kernels: 2048 -> 1000 at batch 128 on x^T 17.0 us
         (17.5) against 32.5-36 us (33); 1024 -> 1024 at batch 64 on x^T 11.9 us
         (12.0) against 13.7 us (12.5); 512 -> 512 at batch 128 on x^T 10.3 us
-        (12.0) against 8.4 us (9.0); 128 -> 128 3 x 3 at 28 x 28, batch 1 8.6 us
-        (10) against 42 us eager (33); 256 -> 128 at batch 8 4.2 us (5.5)
+        (12.0) against 8.4 us (9.0); 256 -> 128 at batch 8 4.2 us (5.5)
         against 4.5 us (5.5); 512 -> 1000 at batch 32 10.2 us (11) against 6.5
-        us (7.2); 25088 -> 4096 at batch 1 344 us (282) against 41 us (42). Over
-        the layers of ResNet-18 (batch 32) and ResNet-50 (batch 128) measured /
-        modelled plan durations have medians 1.16 and 1.04, runtime-kernel ones
-        0.97 and 0.92."""
+        us (7.2); 25088 -> 4096 at batch 1 344 us (282) against 24 us (42).
+        Over the layers of ResNet-18 (batch 32) and ResNet-50 (batch 128) in generated
+        code, measured / modelled plan durations have medians 1.16 and 1.04."""
         if getattr(self, "matrix_cores", False):
             return True     # the runtime call's kernels, with the weights expanded already
         return self.estimate_us() < self.runtime_estimate_us()
