@@ -262,7 +262,11 @@ size_t backward_workspace_bytes(const ConvGeom &g)
 {
     std::vector<MfmaTask> tasks;
     bool zeros = false;
-    return matrix_phases(g, tasks, zeros) ? matrix_phase_bytes(tasks) : 0;
+    if (matrix_phases(g, tasks, zeros)) return matrix_phase_bytes(tasks);
+    // The vector kernels: the phases' re-packed codes.
+    std::vector<PhasePlan> phases;
+    size_t words = 0;
+    return forced_variant() != 0 && plan_phases(g, phases, words) ? words * 4 : 0;
 }
 
 hipError_t run_backward_data(const ConvGeom &g, const int32_t *dy, const uint32_t *wp, int32_t *dx,
@@ -292,8 +296,9 @@ hipError_t run_backward_data(const ConvGeom &g, const int32_t *dy, const uint32_
         hipLaunchKernelGGL(bwd_direct_kernel, dim3(grid), dim3(256), 0, st, dy, wp, dx, g, wpr, fmt);
         return hipGetLastError();
     }
-    void *scratch = nullptr;
-    hipError_t e = words ? scratch_alloc(&scratch, words * 4, st) : hipSuccess;
+    void *scratch = ws.ptr && ws.bytes >= words * 4 ? ws.ptr : nullptr;
+    const bool own = !scratch && words;
+    hipError_t e = own ? scratch_alloc(&scratch, words * 4, st) : hipSuccess;
     if (e != hipSuccess) return e;
     uint32_t *packed = static_cast<uint32_t *>(scratch);
     // Rows or columns no tap reaches are zero: dx is cleared densely first (the
@@ -318,7 +323,7 @@ hipError_t run_backward_data(const ConvGeom &g, const int32_t *dy, const uint32_
             e = run_conv(p.g, dy, pw, nullptr, nullptr, dx, Inner::Shift, st, Epilogue(), p.map,
                          pp.pad);
     }
-    const hipError_t ef = scratch ? hipFreeAsync(scratch, st) : hipSuccess;
+    const hipError_t ef = own ? hipFreeAsync(scratch, st) : hipSuccess;
     return e != hipSuccess ? e : ef;
 }
 
