@@ -1416,13 +1416,17 @@ static void launch_table(dim3 grid, const int32_t *x, const RowsArgs &a, int par
 // 32, 128 10.1, 16.6, 44, 150 against 11.5, 21.4, 63, 232; 2048 -> 1000 at batch 128
 // 26 against 33. Smaller ones keep the kernel above: 2048 -> 1000 at batch 8 (16 M)
 // 7.9 against 9.4, 512 -> 1000 at batch 32 5.8 against 9.4, 4383 -> 67 at batch 4 6.5
-// against 8.9. DS_ROWS_BATCH: 16 forces the table, its other values the kernel above.
+// against 8.9; so do those of more rows and shorter reductions up to 100 M terms,
+// where the fill is a third of the call: 512 -> 2048 at batch 32 (34 M) 7.9 against
+// 9.9, 1024 -> 1024 at batch 64 (67 M) 11.9 against 13.1, but 8000 -> 300 at batch 16
+// (38 M) 13.7 against 10.9. DS_ROWS_BATCH: 16 forces the table, its other values the kernel above.
 static bool table_path(const ConvGeom &g)
 {
     const int forced = tuning(kRowsBatch);
     if (forced == 16) return true;
     const int64_t terms = int64_t(g.n) * g.c * g.k;
-    return forced < 0 && g.k >= 256 && terms >= (g.n == 1 ? 14000000 : 24000000);
+    return forced < 0 && g.k >= 256 &&
+           (terms >= 100000000 || (terms >= 24000000 && (g.n <= 4 || g.c >= 8000)) || (terms >= 14000000 && g.n == 1));
 }
 
 static hipError_t run_table(const ConvGeom &g, const int32_t *x, const uint32_t *wp, const int32_t *bias, int32_t *y,
