@@ -989,9 +989,10 @@ MfmaLayout mfma_layout(const ConvGeom &g, bool shared, int tasks)
     l.PW = l.sampled || l.US > 1 ? g.ow : g.w;
     const int64_t cb = (int64_t(g.c) * l.US + kBlockK - 1) / kBlockK, t = int64_t(g.r) * (l.US > 1 ? 1 : g.s);
     const int64_t np = int64_t(g.n) * l.PH * l.PW, nq = int64_t(g.n) * g.oh * g.ow;
-    // Extents whose products below could not be formed are far past every limit.
+    // Extents whose products below could not be formed are far past every limit; the
+    // end of the last tile of kPix output pixels is formed in 32 bits.
     if (cb <= 0 || t <= 0 || nq <= 0 || cb > (1 << 24) || t > (1 << 24) || np > (int64_t(1) << 31) ||
-        nq > (int64_t(1) << 31))
+        nq > (int64_t(1) << 31) - kPix)
         return l;
     const int64_t nchunks = (cb * t + 1) / 2;
     const int64_t tiles_p = (nq + kPix - 1) / kPix, tiles_k = (g.k + kRows - 1) / kRows;
