@@ -661,34 +661,44 @@ mfma_conv_kernel(const ProductArgs a)
                     for (int i = 0; i < 4; ++i) v[j + i] = uint32_t(q[i]) << shift;
                 }
             }
-            if (!in) continue;
             const int left = count - j0;
             int32_t *yp = y + o;
             if (p.atomic_out) {
+                if (in) {
 #pragma unroll
-                for (int j = 0; j < 16; ++j)
-                    if (j < left) atomicAdd(reinterpret_cast<unsigned int *>(yp + j * ostep), v[j]);
+                    for (int j = 0; j < 16; ++j)
+                        if (j < left) atomicAdd(reinterpret_cast<unsigned int *>(yp + j * ostep), v[j]);
+                }
                 continue;
             }
+            // The parameters are read while every lane is there: a lane past the last
+            // pixel holds a channel's too.
+            int bj[16], mj[16], aj[16];
+            if (bias) {
+#pragma unroll
+                for (int j = 0; j < 16; ++j) bj[j] = byrow ? pbias : __builtin_amdgcn_readlane(pbias, (j0 + j) & 63);
+            }
+            if (affine) {
+#pragma unroll
+                for (int j = 0; j < 16; ++j) {
+                    mj[j] = byrow ? pmul : __builtin_amdgcn_readlane(pmul, (j0 + j) & 63);
+                    aj[j] = byrow ? padd : __builtin_amdgcn_readlane(padd, (j0 + j) & 63);
+                }
+            }
+            if (!in) continue;
             if (more) {
 #pragma unroll
                 for (int j = 0; j < 16; ++j)
                     v[j] += uint32_t(__hip_atomic_load(yp + min(j, left - 1) * ostep, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
             }
-            if (byrow) {
+            if (bias) {
 #pragma unroll
-                for (int j = 0; j < 16; ++j) v[j] += uint32_t(pbias);
-            } else if (bias) {
-#pragma unroll
-                for (int j = 0; j < 16; ++j) v[j] += uint32_t(__builtin_amdgcn_readlane(pbias, (j0 + j) & 63));
+                for (int j = 0; j < 16; ++j) v[j] += uint32_t(bj[j]);
             }
             if (affine) {
 #pragma unroll
-                for (int j = 0; j < 16; ++j) {
-                    const int mul = byrow ? pmul : __builtin_amdgcn_readlane(pmul, (j0 + j) & 63);
-                    const int add = byrow ? padd : __builtin_amdgcn_readlane(padd, (j0 + j) & 63);
-                    v[j] = uint32_t((int64_t(int32_t(v[j])) * mul) >> epi.mul_shift) + uint32_t(add);
-                }
+                for (int j = 0; j < 16; ++j)
+                    v[j] = uint32_t((int64_t(int32_t(v[j])) * mj[j]) >> epi.mul_shift) + uint32_t(aj[j]);
             }
             if (res) {
                 const int32_t *rp = epi.res + o;

@@ -88,8 +88,8 @@ def test_sums_past_the_accumulators_exact_range(value, shift, knob):
 
 
 @pytest.mark.parametrize("mode", ["digit", "edges"])
-@pytest.mark.parametrize("shape", [(96, 64, 16, 64, 1), (2, 128, 14, 100, 3), (260, 64, 1, 72, 1)],
-                         ids=["whole", "split", "linear"])
+@pytest.mark.parametrize("shape", [(96, 64, 16, 64, 1), (2, 128, 14, 100, 3), (260, 64, 1, 72, 1), (3, 40, 9, 65, 1)],
+                         ids=["whole", "split", "linear", "ragged"])
 def test_matrix_core_epilogue_matches_oracle(shape, mode, knob):
     n, c, h, k, r = shape
     rng = np.random.default_rng(n + c)
@@ -98,6 +98,10 @@ def test_matrix_core_epilogue_matches_oracle(shape, mode, knob):
     bias, mul, add = (rng.integers(-(2 ** 18), 2 ** 18, k).astype(np.int32) for _ in range(3))
     res = rng.integers(-(2 ** 31), 2 ** 31, (n, k, h, h), dtype=np.int64).astype(np.int32)
     knob("DS_FORCE_VARIANT", 64)
+    # ragged: one launch applies the epilogue to a last wave of 51 pixels and to one
+    # channel past a row tile, each lane's parameters being another channel's
+    if shape == (3, 40, 9, 65, 1):
+        assert ops.describe_conv2d(n, c, h, h, k, r, 1, r // 2).endswith("parts 1")
     y = ops.conv2d_shift_fused(to_dev(x), to_dev(ops.pack_shift_weights(codes).view(np.int32)), to_dev(bias), r, 1,
                                r // 2, mul=to_dev(mul), add=to_dev(add), mul_shift=13, residual=to_dev(res), relu=True)
     want = oracle.epilogue(oracle.conv2d_shift(x, codes, bias, r=r, stride=1, pad=r // 2), mul, add, 13, res, True)
@@ -154,7 +158,8 @@ def test_matrix_core_gradients_match_oracle(case, mode, knob):
 
 @pytest.mark.parametrize("act_bits", [32, 16, 8])
 @pytest.mark.parametrize("shape", [(96, 64, 16, 64, 1, 1, 0), (2, 100, 14, 100, 3, 1, 1), (2, 3, 30, 40, 7, 2, 3),
-                                   (260, 64, 1, 72, 1, 1, 0)], ids=["whole", "split", "folded", "linear"])
+                                   (260, 64, 1, 72, 1, 1, 0), (3, 40, 18, 65, 1, 2, 0)],
+                         ids=["whole", "split", "folded", "linear", "ragged"])
 def test_matrix_core_plans_match_oracle(shape, act_bits, knob):
     """Plans of every input width with the whole epilogue, run twice on new inputs, the
     second time as replays of a captured graph."""
