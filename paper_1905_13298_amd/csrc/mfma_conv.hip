@@ -737,6 +737,9 @@ mfma_conv_kernel(const ProductArgs a)
     };
     int hm = hload(lane);
     stage(ch0, 0);
+    // The chunk loop waits for the staged weights by count: the twelve loads of the
+    // inputs have to come after them.
+    asm volatile("" ::: "memory");
     seek(ch0);
     locate();
 #pragma unroll
