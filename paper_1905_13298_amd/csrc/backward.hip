@@ -258,15 +258,26 @@ hipError_t run_matrix_phases(std::vector<MfmaTask> &tasks, bool zeros, const Con
     return e;
 }
 
+// Scratch of the vector kernels: the phases' re-packed codes, then what the largest
+// of the phases' convolutions takes (they run one after the other).
+size_t packed_code_bytes(size_t words) { return (words * 4 + 255) & ~size_t(255); }
+
+size_t vector_phase_bytes(const std::vector<PhasePlan> &phases, size_t words)
+{
+    size_t most = 0;
+    for (const PhasePlan &p : phases)
+        if (p.ph.g.r > 0 && p.ph.g.s > 0) most = std::max(most, conv_workspace_bytes(p.ph.g, p.ph.map, p.pad));
+    return packed_code_bytes(words) + most;
+}
+
 size_t backward_workspace_bytes(const ConvGeom &g)
 {
     std::vector<MfmaTask> tasks;
     bool zeros = false;
     if (matrix_phases(g, tasks, zeros)) return matrix_phase_bytes(tasks);
-    // The vector kernels: the phases' re-packed codes.
     std::vector<PhasePlan> phases;
     size_t words = 0;
-    return forced_variant() != 0 && plan_phases(g, phases, words) ? words * 4 : 0;
+    return forced_variant() != 0 && plan_phases(g, phases, words) ? vector_phase_bytes(phases, words) : 0;
 }
 
 hipError_t run_backward_data(const ConvGeom &g, const int32_t *dy, const uint32_t *wp, int32_t *dx,
@@ -296,11 +307,13 @@ hipError_t run_backward_data(const ConvGeom &g, const int32_t *dy, const uint32_
         hipLaunchKernelGGL(bwd_direct_kernel, dim3(grid), dim3(256), 0, st, dy, wp, dx, g, wpr, fmt);
         return hipGetLastError();
     }
-    void *scratch = ws.ptr && ws.bytes >= words * 4 ? ws.ptr : nullptr;
-    const bool own = !scratch && words;
-    hipError_t e = own ? scratch_alloc(&scratch, words * 4, st) : hipSuccess;
+    const size_t bytes = vector_phase_bytes(phases, words);
+    void *scratch = ws.ptr && ws.bytes >= bytes ? ws.ptr : nullptr;
+    const bool own = !scratch && bytes;
+    hipError_t e = own ? scratch_alloc(&scratch, bytes, st) : hipSuccess;
     if (e != hipSuccess) return e;
     uint32_t *packed = static_cast<uint32_t *>(scratch);
+    const Workspace conv{static_cast<unsigned char *>(scratch) + packed_code_bytes(words), bytes - packed_code_bytes(words)};
     // Rows or columns no tap reaches are zero: dx is cleared densely first (the
     // phases then write their own positions), which is several times faster than
     // filling the empty phases through their strided maps.
@@ -321,7 +334,7 @@ hipError_t run_backward_data(const ConvGeom &g, const int32_t *dy, const uint32_
         e = hipGetLastError();
         if (e == hipSuccess)
             e = run_conv(p.g, dy, pw, nullptr, nullptr, dx, Inner::Shift, st, Epilogue(), p.map,
-                         pp.pad);
+                         pp.pad, conv.bytes ? conv : Workspace());
     }
     const hipError_t ef = own ? hipFreeAsync(scratch, st) : hipSuccess;
     return e != hipSuccess ? e : ef;

@@ -1495,16 +1495,11 @@ size_t conv_scratch_bytes(const ConvGeom &g0, const OutMap &map, const Padded &p
     return L.direct ? 0 : L.scratch_bytes();
 }
 
-bool matrix_cores_run(const ConvGeom &g)
+size_t conv_workspace_bytes(const ConvGeom &g, const OutMap &map, const Padded &pad)
 {
-    return !rows_path(g, OutMap(), Padded()) && use_mfma(g, mfma_layout(g));
-}
-
-size_t conv_workspace_bytes(const ConvGeom &g)
-{
-    if (rows_path(g, OutMap(), Padded())) return 0;
+    if (rows_path(g, map, pad)) return 0;
     const MfmaLayout l = mfma_layout(g);
-    return use_mfma(g, l) ? l.input_bytes() + l.weight_bytes() : conv_scratch_bytes(g);
+    return use_mfma(g, l) ? l.input_bytes() + l.weight_bytes() : conv_scratch_bytes(g, map, pad);
 }
 
 hipError_t run_conv(const ConvGeom &g0, const int32_t *x, const uint32_t *wp, const int32_t *wi,

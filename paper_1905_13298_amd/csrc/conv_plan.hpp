@@ -107,13 +107,10 @@ struct GradPhase {
 // or g.s == 0 (its dx positions are zero).
 std::vector<GradPhase> grad_phases(const ConvGeom &g);
 
-// Whether a shift problem of this geometry runs on the matrix cores by itself
-// (not under every forced variant).
-bool matrix_cores_run(const ConvGeom &g);
-
-// Scratch bytes of a call that may take any amount of it (conv_scratch_bytes is
-// what the vector kernels need, the least a call can do with).
-size_t conv_workspace_bytes(const ConvGeom &g);
+// Scratch bytes with which run_conv runs a shift problem as it would without a
+// workspace (conv_scratch_bytes is what the vector kernels need, the least a call
+// can do with).
+size_t conv_workspace_bytes(const ConvGeom &g, const OutMap &map = OutMap(), const Padded &pad = Padded());
 
 // Whether run_conv runs g (with `pad`) on the tiled kernel rather than the
 // one-thread-per-output kernel.

@@ -354,3 +354,33 @@ def test_random_shapes_both_paths_match_oracle(spec):
     dxp = plan(to_dev(dy)).cpu().numpy()
     plan.close()
     np.testing.assert_array_equal(dxp, want, err_msg="plan")
+
+
+@pytest.mark.parametrize("variant", [4, 64])
+@pytest.mark.parametrize("shape", [(2, 70, 16, 16, 33, 3, 2, 1), (2, 64, 14, 14, 256, 3, 1, 1), (300, 70, 1, 1, 65, 1, 1, 0)])
+def test_recorded_gradient_holds_kernels_only(shape, variant, knob):
+    """The binding brings all of a call's scratch, on the vector kernels too: a recorded
+    call holds kernel launches and no allocation. (Recorded only, never launched.)"""
+    import ctypes
+    n, c, h, w, k, r, st, pd = shape
+    knob("DS_FORCE_VARIANT", variant)
+    dy, codes, _ = make(5, n, c, h, w, k, r, r, st, pd)
+    wp, dyd = to_dev(ops.pack_shift_weights(codes).view(np.int32)), to_dev(dy)
+    dx = ops.conv2d_shift_backward_data(dyd, wp, (n, c, h, w), r, st, pd)
+    np.testing.assert_array_equal(dx.cpu().numpy(), oracle.conv2d_shift_backward_data(dy, codes, (n, c, h, w), r=r,
+                                                                                     stride=st, pad=pd))
+    with open("/proc/self/maps") as f:
+        hip = ctypes.CDLL(next(ln.split()[-1] for ln in f if "libamdhip64.so" in ln))
+    graph = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(graph):
+        ops.conv2d_shift_backward_data(dyd, wp, (n, c, h, w), r, st, pd, out=dx)
+    raw, count = ctypes.c_void_p(graph.raw_cuda_graph()), ctypes.c_size_t()
+    assert hip.hipGraphGetNodes(raw, None, ctypes.byref(count)) == 0 and count.value > 0
+    nodes = (ctypes.c_void_p * count.value)()
+    assert hip.hipGraphGetNodes(raw, nodes, ctypes.byref(count)) == 0
+    kinds = []
+    for node in nodes:
+        kind = ctypes.c_int(-1)
+        assert hip.hipGraphNodeGetType(ctypes.c_void_p(node), ctypes.byref(kind)) == 0
+        kinds.append(kind.value)
+    assert set(kinds) == {0}, kinds      # hipGraphNodeTypeKernel

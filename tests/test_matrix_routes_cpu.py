@@ -14,3 +14,19 @@ def test_pixel_counts_near_2_31_keep_off_the_matrix_cores():
     assert "matrix cores" not in d
     # one image fewer is far from the limit
     assert "matrix cores" in ops.describe_conv2d(n - 1, 1, 1, 3, 1, 1, 1, 8191)
+
+
+@pytest.mark.parametrize("shape", [(2, 64, 14, 14, 32, 3, 1, 1), (2, 70, 16, 16, 33, 3, 2, 1), (3, 20, 15, 15, 33, 1, 2, 0)])
+def test_gradient_scratch_covers_its_convolutions(shape, knob):
+    """On the vector kernels a gradient runs one convolution per stride phase; the scratch
+    that the caller is told to bring holds the phase's codes and all that the
+    convolution takes (which the call would otherwise allocate)."""
+    n, c, h, w, k, r, stride, pad = shape
+    lib = _native.lib()
+    knob("DS_FORCE_VARIANT", 4)
+    oh = (h + 2 * pad - r) // stride + 1
+    # the phase of the most taps, as a forward problem on dy (padding does not change its scratch's weights)
+    taps = -(-r // stride)
+    need = lib.ds_conv2d_shift_scratch_bytes(n, k, oh, oh, c, taps, taps, 1, 1, taps - 1, taps - 1)
+    assert need > 0
+    assert lib.ds_conv2d_shift_backward_data_scratch_bytes(n, c, h, w, k, r, r, stride, stride, pad, pad) >= need
