@@ -528,9 +528,13 @@ ds_status ds_jit_conv_mul_image(const int32_t *w, const int32_t *bias, int64_t n
  * code object and held from the library's first use on that GPU until the
  * process ends. A problem whose scratch would exceed it fails with
  * DS_ERR_UNSUPPORTED before anything is launched; ds_conv2d_shift_noalloc_
- * scratch_bytes gives a shape's need (-1 for an invalid shape; 0 for shapes
- * on the one-thread-per-output kernel). Every call on a GPU uses that GPU's one
- * array: calls on one stream are ordered, but calls that overlap in time on
+ * scratch_bytes gives what a shape uses (-1 for an invalid shape; 0 for shapes on
+ * the one-thread-per-output kernel and LinearShifts of fewer than 256 rows, which
+ * stay off the array). The matrix cores run a problem as they do for
+ * ds_conv2d_shift where their scratch fits the array (layers of up to about 6
+ * million inputs), the vector kernels the others. Every call on a GPU that uses
+ * scratch uses that GPU's one array: calls on one stream are ordered, but calls
+ * that overlap in time on
  * one GPU (several streams, several host threads) race on it and must be
  * serialised by the caller. */
 #define DS_NOALLOC_SCRATCH_BYTES (32u << 20)

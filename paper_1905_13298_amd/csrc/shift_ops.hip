@@ -294,6 +294,17 @@ hipError_t noalloc_scratch(void **out)
     return hipSuccess;
 }
 
+// Bytes of the array that a problem uses: what its kernels need, where the matrix
+// cores run it and their scratch fits, else what the vector kernels need. Problems
+// that need none there stay off the array altogether.
+size_t noalloc_bytes(const ConvGeom &g)
+{
+    const size_t need = conv_scratch_bytes(g), limit = DS_NOALLOC_SCRATCH_BYTES;
+    if (need == 0 || need > limit) return need;
+    const size_t chosen = conv_workspace_bytes(g);
+    return chosen <= limit ? chosen : need;
+}
+
 }  // namespace
 }  // namespace ds
 
@@ -311,7 +322,7 @@ extern "C" ds_status ds_conv2d_shift_noalloc(const int32_t *x, const uint32_t *w
         ds_status st = check_shape(n, c, h, w, k, r, s, stride_h, stride_w, pad_h, pad_w, true, g,
                                    bits < 0 ? 5 : bits);
         if (st != DS_SUCCESS) return st;
-        const size_t need = conv_scratch_bytes(g);
+        const size_t need = noalloc_bytes(g);
         if (need > size_t(DS_NOALLOC_SCRATCH_BYTES))
             return fail(DS_ERR_UNSUPPORTED,
                         "ds_conv2d_shift_noalloc: this problem needs %zu bytes of scratch, more than "
@@ -328,7 +339,7 @@ extern "C" ds_status ds_conv2d_shift_noalloc(const int32_t *x, const uint32_t *w
     epi.relu = (flags & DS_RELU) != 0;
     return hip_status(run_conv(g, x, w_packed, nullptr, bias, y, Inner::Shift,
                                static_cast<hipStream_t>(stream), epi, OutMap(), Padded(),
-                               Workspace{ws, size_t(DS_NOALLOC_SCRATCH_BYTES)}),
+                               Workspace{ws, noalloc_bytes(g)}),
                       "ds_conv2d_shift_noalloc");
 }
 
@@ -341,5 +352,5 @@ extern "C" int64_t ds_conv2d_shift_noalloc_scratch_bytes(int64_t n, int64_t c, i
     if (check_shape(n, c, h, w, k, r, s, stride_h, stride_w, pad_h, pad_w, true, g) != DS_SUCCESS)
         return -1;
     ok();
-    return int64_t(conv_scratch_bytes(g));
+    return int64_t(noalloc_bytes(g));
 }

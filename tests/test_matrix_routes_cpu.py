@@ -30,3 +30,20 @@ def test_gradient_scratch_covers_its_convolutions(shape, knob):
     need = lib.ds_conv2d_shift_scratch_bytes(n, k, oh, oh, c, taps, taps, 1, 1, taps - 1, taps - 1)
     assert need > 0
     assert lib.ds_conv2d_shift_backward_data_scratch_bytes(n, c, h, w, k, r, r, stride, stride, pad, pad) >= need
+
+
+def test_noalloc_reports_the_scratch_it_uses():
+    """A shape that is told to need none stays off the one array; one that the matrix cores
+    run there uses their scratch; one whose scratch there would not fit, the vector
+    kernels'."""
+    lib = _native.lib()
+    need = lambda *a: lib.ds_conv2d_shift_noalloc_scratch_bytes(*a)
+    matrix = lambda *a: lib.ds_conv2d_shift_scratch_bytes(*a)
+    fits = (4, 64, 28, 28, 128, 3, 3, 1, 1, 1, 1)
+    assert "matrix cores" in ops.describe_conv2d(4, 64, 28, 28, 128, 3, 1, 1)
+    assert need(*fits) == matrix(*fits) < 32 << 20
+    none = (1, 64, 56, 56, 64, 6, 6, 1, 1, 2, 2)      # no tiled instance
+    assert need(*none) == 0 < matrix(*none)
+    large = (64, 64, 112, 112, 64, 3, 3, 1, 1, 1, 1)
+    assert 0 < need(*large) < 32 << 20 < matrix(*large)
+    assert need(8, 256, 1, 1, 128, 1, 1, 1, 1, 0, 0) == 0

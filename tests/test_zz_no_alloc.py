@@ -57,6 +57,8 @@ SEQUENCE = [
     (3, 16, 8, 8, 40, 1, 2, 0, True, 0),
     (64, 512, 1, 1, 1000, 1, 1, 0, False, 0),
     (8, 256, 1, 1, 128, 1, 1, 0, True, DS_RELU),
+    (2, 64, 20, 20, 64, 6, 1, 2, True, 0),        # no tiled instance: stays off the array
+    (68, 64, 40, 40, 64, 3, 1, 1, False, 0),      # matrix scratch over the array: vector kernels
 ]
 
 
