@@ -534,9 +534,8 @@ ds_status ds_jit_conv_mul_image(const int32_t *w, const int32_t *bias, int64_t n
  * ds_conv2d_shift where their scratch fits the array (layers of up to about 6
  * million inputs), the vector kernels the others. Every call on a GPU that uses
  * scratch uses that GPU's one array: calls on one stream are ordered, but calls
- * that overlap in time on
- * one GPU (several streams, several host threads) race on it and must be
- * serialised by the caller. */
+ * that overlap in time on one GPU (several streams, several host threads) race on
+ * it and must be serialised by the caller. */
 #define DS_NOALLOC_SCRATCH_BYTES (32u << 20)
 ds_status ds_conv2d_shift_noalloc(const int32_t *x, const uint32_t *w_packed, const int32_t *bias,
                                   int32_t *y, int64_t n, int64_t c, int64_t h, int64_t w,

@@ -433,7 +433,10 @@ static ds_status backward_data(const int32_t *dy, const uint32_t *w_packed, int3
                                   pad_w, frac_bits, flags, g);
     if (st != DS_SUCCESS) return st;
     Workspace ws;
-    st = check_workspace(scratch, scratch_bytes, {{dy, 4 * int64_t(g.n) * g.k * g.oh * g.ow}, {dx, 4 * int64_t(g.n) * g.c * g.h * g.w}}, ws);
+    st = check_workspace(scratch, scratch_bytes,
+                         {{dy, 4 * int64_t(g.n) * g.k * g.oh * g.ow},
+                          {w_packed, 4 * int64_t(g.k) * row_words_bits(g.crs, g.bits)},
+                          {dx, 4 * int64_t(g.n) * g.c * g.h * g.w}}, ws);
     if (st != DS_SUCCESS) return st;
     hipError_t e;
     try {

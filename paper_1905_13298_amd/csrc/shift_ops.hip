@@ -154,7 +154,10 @@ static ds_status conv2d_shift_fused(const int32_t *x, const uint32_t *w_packed,
     epi.res = residual;
     epi.relu = (flags & DS_RELU) != 0;
     Workspace ws;
-    st = check_workspace(scratch, scratch_bytes, {{x, 4 * int64_t(g.n) * g.c * g.h * g.w}, {y, yb}}, ws);
+    st = check_workspace(scratch, scratch_bytes,
+                         {{x, 4 * int64_t(g.n) * g.c * g.h * g.w},
+                          {w_packed, 4 * int64_t(g.k) * row_words_bits(g.crs, g.bits)},
+                          {bias, kb}, {mul, kb}, {add, kb}, {residual, yb}, {y, yb}}, ws);
     if (st != DS_SUCCESS) return st;
     // Scratch that is too small for the call's kernels is not used.
     if (ws.bytes < conv_workspace_bytes(g)) ws = Workspace();

@@ -225,3 +225,58 @@ def test_scratch_entry_points(knob):
                 np.testing.assert_array_equal(y.cpu().numpy(), want)
             else:
                 assert torch.all(y == 7)
+
+
+@pytest.mark.parametrize("variant", [64, 4])
+def test_scratch_over_any_buffer_is_refused(variant, knob):
+    """Scratch that shares memory with any of a call's buffers, by one word at either end,
+    is refused and nothing is written; next to them it is taken."""
+    import ctypes
+    from paper_1905_13298_amd import _native
+    lib = _native.lib()
+    rng = np.random.default_rng(6)
+    n, c, h, k = 2, 40, 12, 70
+    x = inputs(rng, "digit", (n, c, h, h))
+    codes = random_codes(rng, (k, c * 9))
+    bias, mul, add = (rng.integers(-(2 ** 18), 2 ** 18, k).astype(np.int32) for _ in range(3))
+    res = rng.integers(-(2 ** 20), 2 ** 20, (n, k, h, h)).astype(np.int32)
+    knob("DS_FORCE_VARIANT", variant)
+    shape = (n, c, h, h, k, 3, 3, 1, 1, 1, 1)
+    need = max(lib.ds_conv2d_shift_scratch_bytes(*shape), lib.ds_conv2d_shift_backward_data_scratch_bytes(*shape))
+    need = (need + 255) // 256 * 256
+    data = dict(x=x, w=ops.pack_shift_weights(codes).view(np.int32), bias=bias, mul=mul, add=add, res=res, y=res)
+    stream = ctypes.c_void_p(torch.cuda.current_stream(DEV).cuda_stream)
+    # every buffer between two stretches of scratch, all starting on 256-byte boundaries
+    room, at = {}, need
+    for name, a in data.items():
+        room[name] = at
+        at += (a.nbytes + 255) // 256 * 256 + need
+    big = torch.zeros(at, dtype=torch.uint8, device=DEV)
+    base = big.data_ptr()
+    view = {m: big[room[m]:room[m] + a.nbytes].view(torch.int32).view(a.shape) for m, a in data.items()}
+    for m, a in data.items():
+        view[m].copy_(torch.from_numpy(a))
+    view["y"].fill_(7)
+    p = {m: base + room[m] for m in data}
+
+    def forward(scratch):
+        return lib.ds_conv2d_shift_fused_ws(p["x"], p["w"], p["bias"], p["mul"], p["add"], 13, p["res"], p["y"], *shape,
+                                            16, 1, scratch, need, stream)
+
+    def gradient(scratch):
+        return lib.ds_conv2d_shift_backward_data_ws(p["res"], p["w"], p["x"], *shape, 16, 0, scratch, need, stream)
+
+    before = big.clone()
+    for m, a in data.items():
+        ends = [p[m] - need + 256, p[m] + (a.nbytes - 1) // 256 * 256]
+        for scratch in ends:
+            assert forward(scratch) == 3, m
+            if m in ("res", "w", "x"):
+                assert gradient(scratch) == 3, m
+    assert torch.equal(big, before)
+    assert forward(p["w"] - need) == 0
+    v = oracle.conv2d_shift(x, codes, bias, r=3, stride=1, pad=1)
+    np.testing.assert_array_equal(view["y"].cpu().numpy(), oracle.epilogue(v, mul, add, 13, res, True))
+    assert gradient(p["y"] - need) == 0
+    want = oracle.conv2d_shift_backward_data(res, codes, (n, c, h, h), r=3, stride=1, pad=1)
+    np.testing.assert_array_equal(view["x"].cpu().numpy(), want)
