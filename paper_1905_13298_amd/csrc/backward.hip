@@ -266,7 +266,7 @@ size_t vector_phase_bytes(const std::vector<PhasePlan> &phases, size_t words)
 {
     size_t most = 0;
     for (const PhasePlan &p : phases)
-        if (p.ph.g.r > 0 && p.ph.g.s > 0) most = std::max(most, conv_workspace_bytes(p.ph.g, p.ph.map, p.pad));
+        if (p.ph.g.r > 0 && p.ph.g.s > 0) most = std::max(most, conv_scratch_bytes(p.ph.g, p.ph.map, p.pad));
     return packed_code_bytes(words) + most;
 }
 
@@ -291,10 +291,14 @@ hipError_t run_backward_data(const ConvGeom &g, const int32_t *dy, const uint32_
             void *scratch = ws.ptr && ws.bytes >= bytes ? ws.ptr : nullptr;
             const bool own = !scratch;
             hipError_t e = own ? scratch_alloc(&scratch, bytes, st) : hipSuccess;
-            if (e != hipSuccess) return e;
-            e = run_matrix_phases(tasks, zeros, g, dy, wp, dx, static_cast<unsigned char *>(scratch), st);
-            const hipError_t ef = own ? hipFreeAsync(scratch, st) : hipSuccess;
-            return e != hipSuccess ? e : ef;
+            if (e == hipSuccess) {
+                e = run_matrix_phases(tasks, zeros, g, dy, wp, dx, static_cast<unsigned char *>(scratch), st);
+                const hipError_t ef = own ? hipFreeAsync(scratch, st) : hipSuccess;
+                return e != hipSuccess ? e : ef;
+            }
+            // Without room for it the vector kernels run the gradient.
+            if (e != hipErrorOutOfMemory) return e;
+            (void)hipGetLastError();
         }
     }
     std::vector<PhasePlan> phases;

@@ -1495,11 +1495,11 @@ size_t conv_scratch_bytes(const ConvGeom &g0, const OutMap &map, const Padded &p
     return L.direct ? 0 : L.scratch_bytes();
 }
 
-size_t conv_workspace_bytes(const ConvGeom &g, const OutMap &map, const Padded &pad)
+size_t conv_workspace_bytes(const ConvGeom &g)
 {
-    if (rows_path(g, map, pad)) return 0;
+    if (rows_path(g, OutMap(), Padded())) return 0;
     const MfmaLayout l = mfma_layout(g);
-    return use_mfma(g, l) ? l.input_bytes() + l.weight_bytes() : conv_scratch_bytes(g, map, pad);
+    return use_mfma(g, l) ? l.input_bytes() + l.weight_bytes() : conv_scratch_bytes(g);
 }
 
 hipError_t run_conv(const ConvGeom &g0, const int32_t *x, const uint32_t *wp, const int32_t *wi,
@@ -1514,17 +1514,22 @@ hipError_t run_conv(const ConvGeom &g0, const int32_t *x, const uint32_t *wp, co
         if (use_mfma(g0, t.l) && (!ws.ptr || bytes <= ws.bytes)) {
             void *scratch = ws.ptr;
             hipError_t e = scratch ? hipSuccess : scratch_alloc(&scratch, bytes, st);
-            if (e != hipSuccess) return e;
-            unsigned char *input = static_cast<unsigned char *>(scratch);
-            t.g = g0;
-            t.map = map;
-            t.w = mfma_forward_weights(g0);
-            t.weights = input + t.l.input_bytes();
-            e = mfma_prepare(&t, 1, x, 4, wp, input, bias, y, st);
-            if (e == hipSuccess) e = mfma_multiply(&t, 1, input, bias, y, epi, st);
-            if (ws.ptr) return e;
-            const hipError_t ef = hipFreeAsync(scratch, st);
-            return e != hipSuccess ? e : ef;
+            if (e == hipSuccess) {
+                unsigned char *input = static_cast<unsigned char *>(scratch);
+                t.g = g0;
+                t.map = map;
+                t.w = mfma_forward_weights(g0);
+                t.weights = input + t.l.input_bytes();
+                e = mfma_prepare(&t, 1, x, 4, wp, input, bias, y, st);
+                if (e == hipSuccess) e = mfma_multiply(&t, 1, input, bias, y, epi, st);
+                if (ws.ptr) return e;
+                const hipError_t ef = hipFreeAsync(scratch, st);
+                return e != hipSuccess ? e : ef;
+            }
+            // Without room for it the vector kernels run the problem: their scratch is a
+            // small part of this one.
+            if (e != hipErrorOutOfMemory) return e;
+            (void)hipGetLastError();
         }
     }
     const ConvLayout L = conv_layout(g0, map, pad);

@@ -110,7 +110,7 @@ std::vector<GradPhase> grad_phases(const ConvGeom &g);
 // Scratch bytes with which run_conv runs a shift problem as it would without a
 // workspace (conv_scratch_bytes is what the vector kernels need, the least a call
 // can do with).
-size_t conv_workspace_bytes(const ConvGeom &g, const OutMap &map = OutMap(), const Padded &pad = Padded());
+size_t conv_workspace_bytes(const ConvGeom &g);
 
 // Whether run_conv runs g (with `pad`) on the tiled kernel rather than the
 // one-thread-per-output kernel.

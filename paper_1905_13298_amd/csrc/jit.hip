@@ -1020,13 +1020,24 @@ static bool matrix_allowed(int splits)
 
 // Completes a plan on the matrix cores: allocates its weights and the packed copy
 // of its input, and expands the weights (wp: host packed codes, `words` of them).
-static ds_status build_matrix_plan(ds_jit_conv *p, const uint32_t *wp, size_t words, const Spec &spec)
+// `no_room`: they could not be allocated, and generated code, which holds a
+// fraction of that memory, is to be tried; the plan then holds none of it.
+static ds_status build_matrix_plan(ds_jit_conv *p, const uint32_t *wp, size_t words, const Spec &spec, bool &no_room)
 {
+    no_room = false;
     size_t bytes = p->tasks[0].l.input_bytes(), at = bytes;
     for (const MfmaTask &t : p->tasks) bytes += t.l.weight_bytes();
     uint32_t *codes = nullptr;
     hipError_t e = hipMalloc(&p->matrix, bytes);
     if (e == hipSuccess) e = hipMalloc(&codes, words * 4);
+    if (e == hipErrorOutOfMemory) {
+        (void)hipGetLastError();
+        if (p->matrix) (void)hipFree(p->matrix);
+        p->matrix = nullptr;
+        p->tasks.clear();
+        no_room = true;
+        return fail(DS_ERR_HIP, "no memory for the weight matrices");
+    }
     if (e == hipSuccess) e = hipMemcpy(codes, wp, words * 4, hipMemcpyHostToDevice);
     for (MfmaTask &t : p->tasks) {
         t.weights = p->matrix + at;
@@ -1170,16 +1181,17 @@ extern "C" ds_status ds_jit_conv_create(const uint32_t *w_packed, const int32_t 
                 delete p;
                 return fail(DS_ERR_HIP, "no HIP device");
             }
-            st = build_matrix_plan(p, w_packed, size_t(g.k) * size_t(row_words_bits(g.crs, g.bits)), sp);
-            if (st != DS_SUCCESS) {
-                const std::string msg = last_error();
-                destroy_plan(p);
-                return fail(st, "%s", msg.c_str());
+            bool no_room;
+            st = build_matrix_plan(p, w_packed, size_t(g.k) * size_t(row_words_bits(g.crs, g.bits)), sp, no_room);
+            if (st == DS_SUCCESS) {
+                p->sp.bias = p->sp.mul = p->sp.add = nullptr;
+                p->sp.wp = nullptr;
+                *plan = p;
+                return ok();
             }
-            p->sp.bias = p->sp.mul = p->sp.add = nullptr;
-            p->sp.wp = nullptr;
-            *plan = p;
-            return ok();
+            const std::string msg = last_error();
+            destroy_plan(p);
+            if (!no_room) return fail(st, "%s", msg.c_str());
         }
         return build_plan(sp, plan);
     } catch (const std::bad_alloc &) {
@@ -1229,14 +1241,17 @@ extern "C" ds_status ds_jit_conv_backward_data_create(const uint32_t *w_packed, 
         int64_t terms = 0;
         if (matrix_allowed(splits) && mfma_gradient_tasks(g, p->tasks, zeros, terms) &&
             (forced_variant() == 64 || mfma_prefer_plan(p->tasks.data(), p->tasks.size(), int64_t(g.n) * g.k * g.oh * g.ow, terms))) {
-            st = build_matrix_plan(p, w_packed, size_t(g.k) * size_t(rw), Spec());
-            if (st != DS_SUCCESS) {
+            bool no_room;
+            st = build_matrix_plan(p, w_packed, size_t(g.k) * size_t(rw), Spec(), no_room);
+            if (st == DS_SUCCESS) {
+                *plan = p;
+                return ok();
+            }
+            if (!no_room) {
                 const std::string msg = last_error();
                 destroy_plan(p);
                 return fail(st, "%s", msg.c_str());
             }
-            *plan = p;
-            return ok();
         }
         p->tasks.clear();
         // Stride phases fused into one kernel when they can be (no split of the

@@ -151,11 +151,17 @@ def _scratch(entry: str, shape, dev: torch.device):
     """A call's scratch from PyTorch's caching allocator on the current stream (the
     caller holds it until its work is enqueued; the allocator orders its reuse), and
     its size: the library's own stream-ordered allocation costs about 12 us a call, and
-    350 us for 128 MB after a synchronisation."""
+    350 us for 128 MB after a synchronisation. None where there is no room for it: the
+    library then runs kernels that need less (a call being captured has to bring it)."""
     size = getattr(lib(), entry)(*shape)
     if size <= 0:
         return None, 0
-    return torch.empty(size, dtype=torch.uint8, device=dev), size
+    try:
+        return torch.empty(size, dtype=torch.uint8, device=dev), size
+    except torch.OutOfMemoryError:
+        if torch.cuda.is_current_stream_capturing():
+            raise
+        return None, 0
 
 
 def out_size(size: int, pad: int, k: int, stride: int) -> int:

@@ -4,6 +4,8 @@ import pytest
 
 from paper_1905_13298_amd import _native, ops
 
+from .mock_hip import run
+
 
 def test_pixel_counts_near_2_31_keep_off_the_matrix_cores():
     """A tile's pixel range is formed in 32 bits, past its 256 pixels: 8 x 16383 x 16385
@@ -47,3 +49,41 @@ def test_noalloc_reports_the_scratch_it_uses():
     large = (64, 64, 112, 112, 64, 3, 3, 1, 1, 1, 1)
     assert 0 < need(*large) < 32 << 20 < matrix(*large)
     assert need(8, 256, 1, 1, 128, 1, 1, 1, 1, 0, 0) == 0
+
+
+def test_calls_and_plans_without_room_for_the_matrix_cores_run_without_them(tmp_path):
+    """Packed inputs and expanded weights take far more memory than what they replace: where
+    they cannot be allocated, calls run on the vector kernels and plans on generated
+    code, as they did with that little memory before. (Against a stand-in runtime whose
+    allocations fail past a limit.)"""
+    run("""
+wp = np.zeros((256, (256 * 9 + 5) // 6), np.uint32)
+buf = np.zeros(1 << 16, np.uint8).ctypes.data
+shape = (32, 256, 14, 14, 256, 3, 3, 1, 1, 1, 1)
+need = lib.ds_conv2d_shift_scratch_bytes(*shape)
+far = [buf + (i << 36) for i in range(4)]         # never touched: launches run nothing
+call = lambda: lib.ds_conv2d_shift(far[0], far[1], None, far[2], *shape, 16, 0, None)
+grad = lambda: lib.ds_conv2d_shift_backward_data(far[0], far[1], far[2], *shape, 16, 0, None)
+for f in (call, grad):
+    mock.mock_reset(ALL)
+    assert f() == 0 and "mfma_conv_kernel" in kernels(), kernels()
+    matrix = mock.mock_largest()
+    mock.mock_reset(matrix - 1)
+    assert f() == 0, lib.ds_last_error_message()
+    assert "tiled_kernel" in kernels() and "mfma_conv_kernel" not in kernels(), kernels()
+    assert mock.mock_failures() == 1
+    mock.mock_reset(1)                            # nothing can be allocated: an error, as before
+    assert f() == 6 and kernels() == []
+for create in (lambda p: lib.ds_jit_conv_create(wp.ctypes.data, None, None, None, 0, *shape, 0, 0, p),
+               lambda p: lib.ds_jit_conv_backward_data_create(wp.ctypes.data, *shape, 0, 0, p)):
+    mock.mock_reset(ALL)
+    p = ctypes.c_void_p()
+    assert create(ctypes.byref(p)) == 0 and lib.ds_jit_conv_matrix_cores(p) == 1
+    matrix = mock.mock_largest()
+    lib.ds_jit_conv_destroy(p)
+    mock.mock_reset(matrix - 1)
+    assert create(ctypes.byref(p)) == 0, lib.ds_last_error_message()
+    assert lib.ds_jit_conv_matrix_cores(p) == 0 and "module" in kernels()
+    assert lib.ds_jit_conv_run(p, far[0], None, far[2], None) == 0 and "generated" in kernels()
+    lib.ds_jit_conv_destroy(p)
+""", tmp_path)
