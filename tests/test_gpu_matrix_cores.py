@@ -29,6 +29,10 @@ def inputs(rng, mode, shape):
     elif mode == "one":       # a single value beyond it
         x = rng.integers(0, 2 ** 18, shape)
         x[-1, -1, -1, -1] = -(2 ** 31)
+    elif mode == "spots":     # a few, in some tiles' windows only
+        x = rng.integers(0, 2 ** 18, shape)
+        spots = rng.choice(x.size, 6, replace=False)
+        x.flat[spots] = rng.integers(-(2 ** 31), 2 ** 31, 6)
     else:                     # "full": all of int32
         x = rng.integers(-(2 ** 31), 2 ** 31, shape, dtype=np.int64)
     return x.astype(np.int32)
@@ -47,6 +51,13 @@ CASES = [
     (2, 64, 7, 7, 128, 3, 3, 1, 1, "digit"),      # small images: a tile spans several
     (300, 256, 1, 1, 128, 1, 1, 1, 0, "digit"),   # LinearShift: y in rows of channels
     (261, 250, 1, 1, 130, 1, 1, 1, 0, "full"),    # unaligned rows
+    # images of many tiles: values beyond one digit reach the tiles whose rows hold them
+    (1, 32, 70, 90, 64, 3, 3, 1, 1, "spots"),
+    (2, 40, 61, 50, 64, 5, 3, 2, 2, "spots"),
+    (1, 3, 90, 83, 64, 7, 7, 2, 3, "spots"),      # folded
+    (3, 33, 35, 41, 64, 1, 1, 2, 0, "spots"),     # sampled
+    (1, 32, 50, 60, 64, 3, 3, 1, 9, "spots"),     # tiles whose rows lie in the padding
+    (1, 32, 40, 300, 64, 3, 1, 3, 0, "one"),      # rows wider than a tile
 ]
 
 
