@@ -331,7 +331,8 @@ ds_status ds_linear_shift_backward_data(const int32_t *dy, const uint32_t *w_pac
 /* Names, without launching anything, what ds_conv2d_shift_backward_data runs
  * for a forward layer of this shape: "direct" (one thread per dx element), or
  * "phases<P>" followed by each stride phase's window and kernel (a phase whose
- * rows or columns no tap reaches is "zero"). Arguments as for
+ * rows or columns no tap reaches is "zero"); "matrix cores; else ..." where the
+ * phases run there together. Arguments as for
  * ds_conv2d_shift_describe. For profiling and tests. */
 ds_status ds_conv2d_shift_backward_data_describe(int64_t n, int64_t c, int64_t h, int64_t w,
                                                  int64_t k, int64_t r, int64_t s,
@@ -362,7 +363,9 @@ ds_status ds_linear_mul_i32(const int32_t *x, const int32_t *w, const int32_t *b
 /* Names, without launching anything, the kernel ds_conv2d_shift (or
  * ds_linear_shift, as a 1x1 convolution with h = w = 1) runs for a problem
  * of this shape on the current device, e.g. "tiled point tm8 cc8 splits1"
- * or "direct". Writes a NUL-terminated string of at most len bytes into buf.
+ * or "direct", or "matrix cores, parts 2; else tiled ..." (the parts of the
+ * reduction, and the vector kernel that runs it where there is no room for the
+ * matrix cores' scratch). Writes a NUL-terminated string of at most len bytes into buf.
  * Shape arguments are validated as for ds_conv2d_shift; no device memory is
  * touched. For profiling and tests. */
 ds_status ds_conv2d_shift_describe(int64_t n, int64_t c, int64_t h, int64_t w, int64_t k,

@@ -352,10 +352,10 @@ void describe_backward(const ConvGeom &g, char *buf, size_t len)
     bool zeros = false;
     const bool mfma = matrix_phases(g, tasks, zeros);
     if (!plan_phases(g, phases, words) || forced_variant() == 0) {
-        snprintf(buf, len, "direct%s", mfma ? "; matrix cores" : "");
+        snprintf(buf, len, "%sdirect", mfma ? "matrix cores; else " : "");
         return;
     }
-    size_t used = size_t(snprintf(buf, len, "phases%zu", phases.size()));
+    size_t used = size_t(snprintf(buf, len, "%sphases%zu", mfma ? "matrix cores; else " : "", phases.size()));
     for (const PhasePlan &pp : phases) {
         if (used >= len) break;
         const ConvGeom &q = pp.ph.g;
@@ -364,12 +364,11 @@ void describe_backward(const ConvGeom &g, char *buf, size_t len)
             snprintf(sub, sizeof sub, "zero");
         else
             describe_conv(q, sub, sizeof sub);
-        // (the phases are named by their tiled instances)
-        if (char *cut = strstr(sub, "; matrix cores")) *cut = 0;
+        // (by its vector kernel: on the matrix cores the phases run together)
+        const char *cut = strstr(sub, "else "), *name = cut ? cut + 5 : sub;
         used += size_t(snprintf(buf + used, len - used, "%s%dx%d %s", used ? "; " : "", q.r,
-                                q.s, sub));
+                                q.s, name));
     }
-    if (mfma && used < len) snprintf(buf + used, len - used, "; matrix cores");
 }
 
 // Validates the sizes of a backward problem given by its forward geometry.

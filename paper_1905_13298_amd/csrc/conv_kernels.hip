@@ -865,28 +865,28 @@ void describe_conv(const ConvGeom &g0, char *buf, size_t len)
         snprintf(buf, len, "rows");
         return;
     }
+    // The kernel that runs comes first; after the matrix cores the vector kernel that
+    // takes the problem where their scratch has no room.
+    const MfmaLayout l = mfma_layout(g0);
+    char mfma[48] = "";
+    if (use_mfma(g0, l)) snprintf(mfma, sizeof mfma, "matrix cores, parts %d; else ", l.splits);
     bool rowmajor = false;
     const ConvGeom g = tiled_geometry(g0, rowmajor);
     int plane = 0;
     size_t lds = 0;
     const Variant v = choose_variant(g, Padded(), plane, lds);
     if (use_direct(g, v)) {
-        snprintf(buf, len, "direct%s", use_mfma(g0, mfma_layout(g0)) ? "; matrix cores" : "");
+        snprintf(buf, len, "%sdirect", mfma);
         return;
     }
     int tiles_p, tiles_k, nchunks, splits, cps;
     plan_splits(g, v, tiles_p, tiles_k, nchunks, splits, cps);
-    // Problems that the matrix cores run are named by their tiled instance too (the
-    // one that takes them under another variant or a small workspace).
-    const MfmaLayout l = mfma_layout(g0);
-    char mfma[32] = "";
-    if (use_mfma(g0, l)) snprintf(mfma, sizeof mfma, "; matrix cores, parts %d", l.splits);
     if (v.mode == MODE_POINT)
-        snprintf(buf, len, "tiled point%s tm%d cc%d splits%d%s", rowmajor ? " transposed" : "", v.tm,
-                 v.cc, splits, mfma);
+        snprintf(buf, len, "%stiled point%s tm%d cc%d splits%d", mfma, rowmajor ? " transposed" : "", v.tm,
+                 v.cc, splits);
     else
-        snprintf(buf, len, "tiled window tm%d cc%d s%d gw%d splits%d%s", v.tm, v.cc, v.sk, v.gw,
-                 splits, mfma);
+        snprintf(buf, len, "%stiled window tm%d cc%d s%d gw%d splits%d", mfma, v.tm, v.cc, v.sk, v.gw,
+                 splits);
 }
 
 // The epilogue as its own pass over y (see epilogue_kernel).

@@ -145,16 +145,22 @@ def test_host_pointers_rejected_without_gpu_access():
     assert np.all(y == 7)
 
 
-def test_describe_names_a_kernel_without_a_gpu():
-    assert ops.describe_conv2d(128, 64, 56, 56, 256, 1).startswith("tiled point")
-    assert ops.describe_conv2d(128, 64, 56, 56, 64, 3, 1, 1).startswith("tiled window")
-    assert ops.describe_conv2d(2, 3, 224, 224, 64, 7, 2, 3).startswith("tiled window")
+def test_describe_names_a_kernel_without_a_gpu(knob):
+    large = [(128, 64, 56, 56, 256, 1), (128, 64, 56, 56, 64, 3, 1, 1), (2, 3, 224, 224, 64, 7, 2, 3),
+             (256, 4096, 1, 1, 4096, 1)]
+    tiled = ["tiled point", "tiled window", "tiled window", "tiled point transposed"]
+    for shape, name in zip(large, tiled):       # the matrix cores first, then what runs without them
+        d = ops.describe_conv2d(*shape)
+        assert d.startswith("matrix cores, parts ") and d.split("; else ")[1].startswith(name), d
+    knob("DS_FORCE_VARIANT", 4)
+    for shape, name in zip(large, tiled):
+        assert ops.describe_conv2d(*shape).startswith(name)
+    knob("DS_FORCE_VARIANT", -1)
     assert ops.describe_conv2d(1, 3, 9, 9, 5, 4, 1, 1).startswith("tiled window tm4 cc1 s4")
     assert ops.describe_conv2d(1, 3, 12, 12, 5, 6, 1, 1) == "direct"   # no instance for 6 taps per row
     # LinearShift (1 x 1 on 1 x 1 inputs) below 256 rows: the small-batch kernel
     assert ops.describe_conv2d(1, 25088, 1, 1, 4096, 1) == "rows"
     assert ops.describe_conv2d(255, 2048, 1, 1, 1000, 1) == "rows"
-    assert ops.describe_conv2d(256, 4096, 1, 1, 4096, 1).startswith("tiled point transposed")
     assert ops.describe_conv2d(8, 256, 2, 1, 128, 1).startswith("tiled")
     lib = _native.lib()
     import ctypes
@@ -283,8 +289,10 @@ def test_backward_validation_codes():
     assert st in (ARG, HIP) and np.all(dx == 7)
 
 
-def test_backward_describe_plans_phases_without_a_gpu():
+def test_backward_describe_plans_phases_without_a_gpu(knob):
     d = ops.describe_conv2d_backward_data
+    assert d(128, 64, 56, 56, 128, 3, 2, 1).startswith("matrix cores; else phases4; 1x1 tiled point")
+    knob("DS_FORCE_VARIANT", 4)
     s2 = d(128, 64, 56, 56, 128, 3, 2, 1)
     assert s2.startswith("phases4") and s2.count("tiled") == 4
     assert d(128, 64, 56, 56, 64, 3, 1, 1).startswith("phases1; 3x3 tiled window")

@@ -75,17 +75,16 @@ def make(seed, n, c, h, w, k, r, s, st, pd, lim=2 ** 31):
     return dy, codes, (r, s)
 
 
-@pytest.mark.parametrize("direct", [False, True], ids=["auto", "gather"])
+@pytest.mark.parametrize("variant", [-1, 4, 0], ids=["auto", "tiled", "gather"])
 @pytest.mark.parametrize("spec", EDGE, ids=[e[0] for e in EDGE])
-def test_edge_shapes_match_oracle(spec, direct, knob):
+def test_edge_shapes_match_oracle(spec, variant, knob):
     name, n, c, h, w, k, r, s, st, pd = spec
-    if direct:
-        knob("DS_FORCE_VARIANT", 0)
+    knob("DS_FORCE_VARIANT", variant)
     rr = r if np.isscalar(r) else r[0]
     ss = s if np.isscalar(s) else s[1]
     dy, codes, _ = make(zlib.crc32(name.encode()), n, c, h, w, k, rr, ss, st, pd)
     plan = ops.describe_conv2d_backward_data(n, c, h, w, k, (rr, ss), st, pd)
-    say(f"backward {name} direct={direct}: {plan}")
+    say(f"backward {name} variant={variant}: {plan}")
     wp = to_dev(ops.pack_shift_weights(codes).view(np.int32))
     dx = ops.conv2d_shift_backward_data(to_dev(dy), wp, (n, c, h, w), (rr, ss), st, pd).cpu().numpy()
     want = oracle.conv2d_shift_backward_data(dy, codes, (n, c, h, w), r=rr, s=ss, stride=st, pad=pd)
@@ -93,8 +92,9 @@ def test_edge_shapes_match_oracle(spec, direct, knob):
     assert bad.size == 0, f"{bad.size} of {want.size} differ, first at {bad[:5]}"
 
 
-def test_plans_cover_the_expected_paths():
+def test_plans_cover_the_expected_paths(knob):
     d = ops.describe_conv2d_backward_data
+    knob("DS_FORCE_VARIANT", 4)
     assert d(2, 64, 56, 56, 128, 3, 2, 1).startswith("phases4")
     assert d(2, 64, 56, 56, 64, 3, 1, 1).startswith("phases1")
     assert "zero" in d(8, 64, 14, 14, 70, 1, 2, 0)
@@ -104,8 +104,10 @@ def test_plans_cover_the_expected_paths():
 
 
 @pytest.mark.parametrize("shape", [(8, 256, 128), (33, 300, 70), (256, 4096, 4096), (1, 1, 1)])
-def test_linear_matches_oracle(shape):
+@pytest.mark.parametrize("variant", [-1, 4], ids=["auto", "tiled"])
+def test_linear_matches_oracle(shape, variant, knob):
     batch, fin, fout = shape
+    knob("DS_FORCE_VARIANT", variant)
     rng = np.random.default_rng(fin + fout)
     dy = rng.integers(-(2 ** 31), 2 ** 31, (batch, fout), dtype=np.int64).astype(np.int32)
     codes = random_codes(rng, (fout, fin), zero_frac=0.1)
@@ -185,12 +187,16 @@ def test_resnet50_full_batch_against_gather_kernel_and_oracle(knob):
         dyd = to_dev(dy)
         x_shape = L.x_shape
         say(f"backward resnet50 {L.name}: {ops.describe_conv2d_backward_data(*x_shape, L.k, (L.r, L.s), L.stride, L.pad)}")
-        dx = ops.conv2d_shift_backward_data(dyd, wp, x_shape, (L.r, L.s), L.stride, L.pad)
         knob("DS_FORCE_VARIANT", 0)
         ref = ops.conv2d_shift_backward_data(dyd, wp, x_shape, (L.r, L.s), L.stride, L.pad)
-        knob("DS_FORCE_VARIANT", -1)
-        diff = int((dx != ref).sum())
-        assert diff == 0, f"{L.name}: {diff} elements differ from the gather kernel"
+        for variant in (4, -1):      # the tiled phases; as chosen
+            knob("DS_FORCE_VARIANT", variant)
+            if variant == 4:
+                assert ops.describe_conv2d_backward_data(*x_shape, L.k, (L.r, L.s), L.stride,
+                                                         L.pad).startswith("phases")
+            dx = ops.conv2d_shift_backward_data(dyd, wp, x_shape, (L.r, L.s), L.stride, L.pad)
+            diff = int((dx != ref).sum())
+            assert diff == 0, f"{L.name} variant {variant}: {diff} elements differ from the gather kernel"
         total = int(np.prod(x_shape))
         idx = np.unique(np.concatenate([rng.choice(total, 400, replace=False), [0, total - 1]]))
         got = dx.reshape(-1)[torch.from_numpy(idx).to(DEV)].cpu().numpy()
@@ -211,6 +217,7 @@ def test_stem_gradient_on_tiled_phases_full_size(knob):
     codes = W.gen_codes(L, W.CONFIG_SEEDS[4], 0)
     g = np.random.default_rng(17)
     dy = np.rint(g.standard_normal((n, L.k) + tuple(L.y_shape[2:]), dtype=np.float32) * 2 ** 16).astype(np.int32)
+    knob("DS_FORCE_VARIANT", 4)
     path = ops.describe_conv2d_backward_data(*x_shape, L.k, (L.r, L.s), L.stride, L.pad)
     assert path.startswith("phases4") and path.count("tiled") == 4, path
     say(f"backward stem {x_shape}: {path}")
@@ -221,9 +228,12 @@ def test_stem_gradient_on_tiled_phases_full_size(knob):
     ref = ops.conv2d_shift_backward_data(dyd, wp, x_shape, (L.r, L.s), L.stride, L.pad)
     knob("DS_FORCE_VARIANT", -1)
     assert int((dx != ref).sum()) == 0
-    plan = ops.JitConvBackwardData(ops.pack_shift_weights(codes), x_shape, (L.r, L.s), L.stride, L.pad)
-    assert int((plan(dyd) != dx).sum()) == 0
-    plan.close()
+    for variant in (4, 64):      # generated code, the matrix cores
+        knob("DS_FORCE_VARIANT", variant)
+        plan = ops.JitConvBackwardData(ops.pack_shift_weights(codes), x_shape, (L.r, L.s), L.stride, L.pad)
+        assert plan.matrix_cores == (variant == 64)
+        assert int((plan(dyd) != dx).sum()) == 0
+        plan.close()
     total = int(np.prod(x_shape))
     idx = np.unique(np.concatenate([np.random.default_rng(3).choice(total, 400, replace=False), [0, total - 1]]))
     got = dx.reshape(-1)[torch.from_numpy(idx).to(DEV)].cpu().numpy()
@@ -298,7 +308,7 @@ def test_linear_plan_matches_oracle():
     plan.close()
 
 
-def test_resnet50_full_batch_plans_equal_runtime_kernel():
+def test_resnet50_full_batch_plans_equal_runtime_kernel(knob):
     """Every ResNet-50 convolution but the stem at batch 128: the plans' input
     gradient equals ds_conv2d_shift_backward_data's on every element."""
     layers = W.config_layers(4)
@@ -309,15 +319,21 @@ def test_resnet50_full_batch_plans_equal_runtime_kernel():
         g = np.random.default_rng([4, li, 7])
         dy = to_dev(np.rint(g.standard_normal(L.y_shape, dtype=np.float32) * 2 ** 16).astype(np.int32))
         wp = ops.pack_shift_weights(codes)
-        plan = ops.JitConvBackwardData(wp, L.x_shape, (L.r, L.s), L.stride, L.pad)
-        say(f"jit backward resnet50 {L.name}: {plan.segments} segments, {plan.code_bytes / 2 ** 20:.1f} MiB")
-        got = plan(dy)
         ref = ops.conv2d_shift_backward_data(dy, to_dev(wp.view(np.int32)), L.x_shape, (L.r, L.s),
                                              L.stride, L.pad)
-        diff = int((got != ref).sum())
-        assert diff == 0, f"{L.name}: {diff} elements differ"
-        plan.close()
-        del got, ref, dy
+        for variant in (4, -1):      # generated code; as chosen
+            knob("DS_FORCE_VARIANT", variant)
+            plan = ops.JitConvBackwardData(wp, L.x_shape, (L.r, L.s), L.stride, L.pad)
+            assert not (variant == 4 and plan.matrix_cores)
+            say(f"jit backward resnet50 {L.name}: matrix cores {plan.matrix_cores}, {plan.segments} segments, "
+                f"{plan.code_bytes / 2 ** 20:.1f} MiB")
+            got = plan(dy)
+            diff = int((got != ref).sum())
+            assert diff == 0, f"{L.name} variant {variant}: {diff} elements differ"
+            plan.close()
+            del got
+        knob("DS_FORCE_VARIANT", -1)
+        del ref, dy
 
 
 def _random_layers(count, seed):

@@ -39,10 +39,9 @@ CONV = [(2, 13, 9, 11, 37, 3, 1, 1), (3, 20, 15, 15, 33, 1, 2, 0), (1, 300, 6, 6
 
 
 @pytest.mark.parametrize("bits", BITS)
-@pytest.mark.parametrize("direct", [False, True], ids=["tiled", "direct"])
-def test_conv_matches_oracle(bits, direct, knob):
-    if direct:
-        knob("DS_FORCE_VARIANT", 0)
+@pytest.mark.parametrize("variant", [-1, 4, 0], ids=["auto", "tiled", "direct"])
+def test_conv_matches_oracle(bits, variant, knob):
+    knob("DS_FORCE_VARIANT", variant)
     for shape in CONV:
         n, c, h, w, k, r, st, pd = shape
         rng = np.random.default_rng(zlib.crc32(repr((shape, bits)).encode()))
@@ -77,7 +76,9 @@ def test_fused_and_linear_match_oracle(bits):
 
 
 @pytest.mark.parametrize("bits", BITS)
-def test_input_gradients_match_oracle(bits):
+@pytest.mark.parametrize("variant", [-1, 4], ids=["auto", "tiled"])
+def test_input_gradients_match_oracle(bits, variant, knob):
+    knob("DS_FORCE_VARIANT", variant)
     rng = np.random.default_rng(10 + bits)
     for (n, c, h, w, k, r, st, pd) in CONV:
         oh, ow = (h + 2 * pd - r) // st + 1, (w + 2 * pd - r) // st + 1

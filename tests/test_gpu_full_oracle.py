@@ -4,8 +4,9 @@ For each layer of the ResNet-18 (batch 32) and ResNet-50 (batch 128) workloads,
 at the batch the benchmark times, both paths the benchmark runs -- the
 weight-specialised plan made by ``ops.layer_plan`` (the benchmark's default)
 and the runtime kernel (``ds_conv2d_shift`` / ``ds_linear_shift``) -- are
-compared with the oracle on every output, bit for bit. The plan runs twice and
-the two runs must agree as well.
+compared with the oracle on every output, bit for bit: as the library chooses
+(most on the matrix cores), and on the vector kernels and generated code. The plan
+runs twice and the two runs must agree as well.
 
 On sampled outputs the float64 band of the paper's emulation (Section 4: the
 float convolution with weights sign * 2^p) is checked too, in two forms:
@@ -42,6 +43,12 @@ def runtime_call(L, xt, wt, bt):
     if L.kind == "linear":
         return ops.linear_shift(xt, wt, bt)
     return ops.conv2d_shift(xt, wt, bt, (L.r, L.s), L.stride, L.pad)
+
+
+def runtime_kernel(L):
+    if L.kind == "linear":
+        return ops.describe_conv2d(L.n, L.c, 1, 1, L.k, 1)
+    return ops.describe_conv2d(L.n, L.c, L.h, L.w, L.k, (L.r, L.s), L.stride, L.pad)
 
 
 def band_points(L, x, codes, bias, idx):
@@ -96,7 +103,7 @@ def check_band(L, y_flat, x, codes, bias, idx):
 
 
 @pytest.mark.parametrize("cfg,li,name", CASES, ids=[f"{W.CONFIG_NAMES[c]}-{n}" for c, _, n in CASES])
-def test_every_output_at_benchmark_batch(cfg, li, name):
+def test_every_output_at_benchmark_batch(cfg, li, name, knob):
     L = W.config_layers(cfg)[li]
     say(f"{W.CONFIG_NAMES[cfg]} layer {li} {name} batch {L.n}: oracle on {oracle.max_threads()} threads")
     x, codes, bias = W.gen_layer(L, W.CONFIG_SEEDS[cfg], li)
@@ -106,17 +113,23 @@ def test_every_output_at_benchmark_batch(cfg, li, name):
     wt = torch.from_numpy(wp.view(np.int32)).to(DEV)
     bt = None if bias is None else torch.from_numpy(bias).to(DEV)
 
-    plan = ops.layer_plan(L, wp, bias, device=DEV)
-    y1 = ops.run_layer_plan(plan, L, xt).cpu().numpy().reshape(-1)
-    y2 = ops.run_layer_plan(plan, L, xt).cpu().numpy().reshape(-1)
-    plan.close()
-    bad = np.flatnonzero(y1 != want)
-    assert bad.size == 0, f"plan: {bad.size} of {want.size} outputs differ, first at {bad[:5]}"
-    assert np.array_equal(y1, y2), "plan: two runs differ"
+    for variant in (4, -1):      # vector kernels and generated code; as chosen
+        knob("DS_FORCE_VARIANT", variant)
+        plan = ops.layer_plan(L, wp, bias, device=DEV)
+        if variant == 4:
+            assert not plan.matrix_cores
+            assert runtime_kernel(L).startswith("tiled"), runtime_kernel(L)
+        say(f"variant {variant}: {runtime_kernel(L)}; plan on the matrix cores: {plan.matrix_cores}")
+        y1 = ops.run_layer_plan(plan, L, xt).cpu().numpy().reshape(-1)
+        y2 = ops.run_layer_plan(plan, L, xt).cpu().numpy().reshape(-1)
+        plan.close()
+        bad = np.flatnonzero(y1 != want)
+        assert bad.size == 0, f"plan: {bad.size} of {want.size} outputs differ, first at {bad[:5]}"
+        assert np.array_equal(y1, y2), "plan: two runs differ"
 
-    yr = runtime_call(L, xt, wt, bt).cpu().numpy().reshape(-1)
-    bad = np.flatnonzero(yr != want)
-    assert bad.size == 0, f"runtime kernel: {bad.size} of {want.size} outputs differ, first at {bad[:5]}"
+        yr = runtime_call(L, xt, wt, bt).cpu().numpy().reshape(-1)
+        bad = np.flatnonzero(yr != want)
+        assert bad.size == 0, f"runtime kernel: {bad.size} of {want.size} outputs differ, first at {bad[:5]}"
 
     rng = np.random.default_rng([cfg, li, 9])
     idx = np.unique(np.concatenate([rng.choice(want.size, 300, replace=False), [0, want.size - 1]]))

@@ -152,8 +152,10 @@ def test_epilogue_matches_oracle(parts, splits):
     np.testing.assert_array_equal(y, want)
 
 
+@pytest.mark.parametrize("variant", [-1, 4], ids=["auto", "generated"])
 @pytest.mark.parametrize("cfg", [0, 1, 2])
-def test_single_layer_configs_exact(cfg):
+def test_single_layer_configs_exact(cfg, variant, knob):
+    knob("DS_FORCE_VARIANT", variant)
     (layer,) = W.config_layers(cfg)
     x, codes, bias = W.gen_layer(layer, W.CONFIG_SEEDS[cfg], 0)
     lin = layer.kind == "linear"

@@ -69,7 +69,7 @@ def test_matrix_core_convolutions_match_oracle(case, knob):
     codes = random_codes(rng, (k, c * r * s), zero_frac=0.1)
     bias = rng.integers(-(2 ** 31), 2 ** 31, k, dtype=np.int64).astype(np.int32)
     knob("DS_FORCE_VARIANT", 64)
-    assert "matrix cores" in ops.describe_conv2d(n, c, h, w, k, (r, s), stride, pad)
+    assert ops.describe_conv2d(n, c, h, w, k, (r, s), stride, pad).startswith("matrix cores")
     print(case, ops.describe_conv2d(n, c, h, w, k, (r, s), stride, pad), flush=True)
     want = oracle.conv2d_shift(x, codes, bias, r=r, s=s, stride=stride, pad=pad)
     size = want.size
@@ -88,7 +88,7 @@ def test_sums_past_the_accumulators_exact_range(value, shift, knob):
     is large enough that the reduction is not split."""
     n, c, k = 300, 1056, 16
     knob("DS_FORCE_VARIANT", 64)
-    assert ops.describe_conv2d(n, c, 16, 16, k, 1).endswith("parts 1")
+    assert ops.describe_conv2d(n, c, 16, 16, k, 1).startswith("matrix cores, parts 1;")
     x = torch.full((n, c, 16, 16), value, dtype=torch.int32, device=DEV)
     codes = np.full((k, c), shift, dtype=np.uint8)
     codes[1::2] |= 16
@@ -112,7 +112,7 @@ def test_matrix_core_epilogue_matches_oracle(shape, mode, knob):
     # ragged: one launch applies the epilogue to a last wave of 51 pixels and to one
     # channel past a row tile, each lane's parameters being another channel's
     if shape == (3, 40, 9, 65, 1):
-        assert ops.describe_conv2d(n, c, h, h, k, r, 1, r // 2).endswith("parts 1")
+        assert ops.describe_conv2d(n, c, h, h, k, r, 1, r // 2).startswith("matrix cores, parts 1;")
     y = ops.conv2d_shift_fused(to_dev(x), to_dev(ops.pack_shift_weights(codes).view(np.int32)), to_dev(bias), r, 1,
                                r // 2, mul=to_dev(mul), add=to_dev(add), mul_shift=13, residual=to_dev(res), relu=True)
     want = oracle.epilogue(oracle.conv2d_shift(x, codes, bias, r=r, stride=1, pad=r // 2), mul, add, 13, res, True)
@@ -153,7 +153,7 @@ def test_matrix_core_gradients_match_oracle(case, mode, knob):
     dy = inputs(rng, mode, (n, k, oh, ow))
     codes = random_codes(rng, (k, c * r * s), zero_frac=0.1)
     knob("DS_FORCE_VARIANT", 64)
-    assert "matrix cores" in ops.describe_conv2d_backward_data(n, c, h, w, k, (r, s), stride, pad)
+    assert ops.describe_conv2d_backward_data(n, c, h, w, k, (r, s), stride, pad).startswith("matrix cores; else ")
     print(case, mode, flush=True)
     want = oracle.conv2d_shift_backward_data(dy, codes, (n, c, h, w), r=r, s=s, stride=stride, pad=pad)
     wp = ops.pack_shift_weights(codes)

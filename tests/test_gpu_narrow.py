@@ -62,7 +62,9 @@ FULL = [(4, "layer1.0.conv1"), (4, "layer1.1.conv1"), (4, "layer2.0.downsample")
 
 @pytest.mark.parametrize("act_bits", [16, 8])
 @pytest.mark.parametrize("cfg,name", FULL)
-def test_narrow_benchmark_layers_every_output(cfg, name, act_bits):
+@pytest.mark.parametrize("variant", [-1, 4], ids=["auto", "generated"])
+def test_narrow_benchmark_layers_every_output(cfg, name, act_bits, variant, knob):
+    knob("DS_FORCE_VARIANT", variant)
     layers = W.config_layers(cfg)
     li = [L.name for L in layers].index(name)
     L = layers[li]

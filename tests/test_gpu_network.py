@@ -37,8 +37,10 @@ COMBOS = ["relu", "affine", "affine_noadd", "residual", "all"]
 
 @pytest.mark.parametrize("shape", FUSED_SHAPES)
 @pytest.mark.parametrize("combo", COMBOS)
-def test_fused_conv_matches_oracle(shape, combo):
+@pytest.mark.parametrize("variant", [-1, 4], ids=["auto", "tiled"])
+def test_fused_conv_matches_oracle(shape, combo, variant, knob):
     n, c, h, k, r, st, pd = shape
+    knob("DS_FORCE_VARIANT", variant)
     say(f"fused conv {shape} {combo}: {ops.describe_conv2d(n, c, h, h, k, r, st, pd)}")
     rng = np.random.default_rng(zlib.crc32(repr((shape, combo)).encode()))
     x = rng.integers(-(2 ** 22), 2 ** 22, (n, c, h, h)).astype(np.int32)
@@ -111,10 +113,13 @@ def test_avgpool_matches_oracle(shape):
     np.testing.assert_array_equal(y, oracle.avgpool_global(x))
 
 
+@pytest.mark.parametrize("variant", [-1, 4], ids=["auto", "vector"])
 @pytest.mark.parametrize("jit", [False, "all"], ids=["runtime", "jit"])
-def test_resnet18_forward_matches_oracle(jit):
+def test_resnet18_forward_matches_oracle(jit, variant, knob):
     """Every intermediate buffer of a ResNet-18 forward pass (batch 2), bit for bit,
-    with the runtime kernels and with weight-specialised plans."""
+    with the runtime kernels and with weight-specialised plans, as the library chooses
+    and on the vector kernels and generated code."""
+    knob("DS_FORCE_VARIANT", variant)
     n = 2
     graph, params = W.resnet18_graph(n), W.resnet18_params(n)
     x = W.gen_images(n)

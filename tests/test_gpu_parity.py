@@ -147,7 +147,9 @@ def test_edge_shapes_exact(spec, signed):
 @pytest.mark.parametrize("shape", [(1, 1, 1), (1, 7, 5), (3, 100, 33), (300, 70, 65),
                                    (257, 129, 31), (16, 4096, 8)])
 @pytest.mark.parametrize("signed", [False, True])
-def test_linear_shapes_exact(shape, signed):
+@pytest.mark.parametrize("variant", [-1, 4], ids=["auto", "tiled"])
+def test_linear_shapes_exact(shape, signed, variant, knob):
+    knob("DS_FORCE_VARIANT", variant)
     B, I, O = shape
     rng = np.random.default_rng(B * 7 + I + O + signed)
     lo = -(2 ** 20) if signed else 0
@@ -211,7 +213,7 @@ def test_output_canaries_untouched():
 
 
 @pytest.mark.parametrize("offset", [0, 1], ids=["aligned", "offset_4_bytes"])
-def test_split_outputs_ragged_and_unaligned(offset):
+def test_split_outputs_ragged_and_unaligned(offset, knob):
     """Split reductions whose output count is not a multiple of 4, written into a
     buffer on a 16-byte boundary and 4 bytes past one: the fill pass before the
     atomics in its vector form with its tail, and in its element-wise form; the
@@ -219,7 +221,8 @@ def test_split_outputs_ragged_and_unaligned(offset):
     canaries on both sides of y."""
     rng = np.random.default_rng(77 + offset)
     n, c, h, w, k = 1, 256, 7, 7, 255
-    assert int(re.search(r"splits(\d+)", ops.describe_conv2d(n, c, h, w, k, 3, 1, 1)).group(1)) > 1
+    knob("DS_FORCE_VARIANT", 4)
+    assert int(re.match(r"tiled .* splits(\d+)", ops.describe_conv2d(n, c, h, w, k, 3, 1, 1)).group(1)) > 1
     x = rng.integers(0, 2 ** 20, (n, c, h, w)).astype(np.int32)
     codes = random_codes(rng, (k, c * 9), zero_frac=0.2)
     bias = rng.integers(-(2 ** 20), 2 ** 20, k).astype(np.int32)

@@ -7,8 +7,8 @@ random shapes, strides, padding, signs, zero-weight fractions, weight codes of
 layouts (segment width, wave split, pixel groups, block order and its tile
 groups, loads in flight, register map, split-K parts, x^T or x for LinearShift,
 batch rows per workgroup of the small-batch kernel),
-and compares the runtime-weights call and the weight-specialised plan with the
-oracle bit for bit. The layouts are the ones the planner can be forced into
+and compares the runtime-weights call, as the library chooses and on the tiled
+vector kernels, and the weight-specialised plan with the oracle bit for bit. The layouts are the ones the planner can be forced into
 for measurements; every one of them must give the oracle's output.
 """
 import numpy as np
@@ -82,6 +82,13 @@ def assert_equal(name, got, want, info):
     assert bad.size == 0, f"{name} {info}: {bad.size} of {want.size} outputs differ, first at {bad[:5]}"
 
 
+def check_call(call, want, info):
+    """A runtime-weights call as the library chooses, and on the tiled vector kernels."""
+    assert_equal("runtime", call().cpu().numpy(), want, info)
+    with ops.tuning("DS_FORCE_VARIANT", 4):
+        assert_equal("runtime, tiled", call().cpu().numpy(), want, info)
+
+
 def linear_case(rng, info):
     b, c, k = int(rng.integers(1, 300)), int(rng.integers(1, 700)), int(rng.integers(1, 500))
     signed = bool(rng.random() < 0.5)
@@ -98,9 +105,8 @@ def linear_case(rng, info):
     if relu:
         want = np.maximum(want, 0)
     wp = ops.pack_shift_weights(codes, bits=bits)
-    y = ops.linear_shift(to_dev(x32), to_dev(wp.view(np.int32)), to_dev(bias), relu=relu,
-                         code_bits=bits)
-    assert_equal("runtime", y.cpu().numpy(), want, info)
+    xd, wd, bd = to_dev(x32), to_dev(wp.view(np.int32)), to_dev(bias)
+    check_call(lambda: ops.linear_shift(xd, wd, bd, relu=relu, code_bits=bits), want, info)
     plan = ops.JitConv(wp, (b, c, 1, 1), 1, 1, 0, bias=bias, relu=relu, splits=splits,
                        code_bits=bits, act_bits=act_bits)
     try:
@@ -131,9 +137,9 @@ def gradient_case(rng, info):
     say("case", info)
     want = oracle.conv2d_shift_backward_data(dy, codes, (n, c, h, w), r=r, s=s, stride=st, pad=pd)
     wp = ops.pack_shift_weights(codes, bits=bits)
-    y = ops.conv2d_shift_backward_data(to_dev(dy), to_dev(wp.view(np.int32)), (n, c, h, w), (r, s),
-                                       st, pd, code_bits=bits)
-    assert_equal("runtime", y.cpu().numpy(), want, info)
+    dyd, wd = to_dev(dy), to_dev(wp.view(np.int32))
+    check_call(lambda: ops.conv2d_shift_backward_data(dyd, wd, (n, c, h, w), (r, s), st, pd, code_bits=bits),
+               want, info)
     plan = ops.JitConvBackwardData(wp, (n, c, h, w), (r, s), st, pd, splits=splits, code_bits=bits)
     try:
         assert_equal("plan", plan(to_dev(dy)).cpu().numpy(), want,
@@ -168,12 +174,13 @@ def conv_case(rng, info):
     xd, wd = to_dev(x), to_dev(wp.view(np.int32))
     # The runtime-weights calls read int32 inputs: the narrow values widened, whose
     # terms equal the narrow plan's (an arithmetic shift of a sign-extended value).
+    x32d, bd = to_dev(x32), to_dev(bias)
     if ep:
-        y = ops.conv2d_shift_fused(to_dev(x32), wd, to_dev(bias), (r, s), st, pd, to_dev(mul), to_dev(add),
-                                   16, to_dev(res), relu, code_bits=bits)
+        md, ad, rd = to_dev(mul), to_dev(add), to_dev(res)
+        check_call(lambda: ops.conv2d_shift_fused(x32d, wd, bd, (r, s), st, pd, md, ad, 16, rd, relu,
+                                                  code_bits=bits), want, info)
     else:
-        y = ops.conv2d_shift(to_dev(x32), wd, to_dev(bias), (r, s), st, pd, code_bits=bits)
-    assert_equal("runtime", y.cpu().numpy(), want, info)
+        check_call(lambda: ops.conv2d_shift(x32d, wd, bd, (r, s), st, pd, code_bits=bits), want, info)
     plan = ops.JitConv(wp, x.shape, (r, s), st, pd, bias=bias, mul=mul, add=add,
                        residual=res is not None, relu=relu, splits=splits, code_bits=bits,
                        act_bits=act_bits)
