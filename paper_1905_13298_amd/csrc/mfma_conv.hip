@@ -25,7 +25,7 @@
 // hold the sum: C0 in units of 1 and C1, the part of the shifts 0..5 above bit
 // 11, in units of 2^7. H outside -16 .. 15 is split into four signed base-32
 // digits h0 .. h3; h0 takes H's place and the three others get passes of their
-// own, which a tile runs only when its images need them.
+// own, which a tile runs only as far as the inputs that it reads need them.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -55,6 +55,9 @@ constexpr int kStageBytes = 2 * kTileBytes;            // a workgroup's 64 rows
 constexpr int kXpBytes = 88;         // per pixel and 32 channels: 4 nibble planes, h0
 constexpr int kDigBytes = 72;        // the same for h1, h2, h3
 constexpr int kOutPitch = 68;         // LDS words per pixel of the output tile: 16-byte rows, no bank conflicts
+constexpr int kParked = 4 * 64 * kOutPitch * 4;   // bytes of the output tile
+constexpr int kDigitStage = 4 * 1536;  // P_14 and W of 64 rows, one after the other in a stage
+static_assert(kParked + 2 * kDigitStage <= 2 * kStageBytes, "the parked sums and two chunks of the digit passes");
 constexpr uint32_t kOOB = 0x80000000u;
 constexpr int kRsrcWord3 = 0x00020000;
 constexpr int kLimit = (1 << 24) - 1;  // a float sum of integers stays exact up to 2^24
@@ -278,8 +281,8 @@ __device__ __forceinline__ uint32_t e2m3(int h) { return h < 0 ? uint32_t(-h) | 
 
 // The packed copy of 32 channels of 256 pixels, one pixel per lane: four planes of
 // nibbles (bits 4p .. 4p+3 of the 32 channels, channel e in nibble e) and h0; h1
-// .. h3 where some H of the block needs them. hmax[cb][block]: the largest |H|, or
-// 255 when one lies outside -16 .. 15.
+// .. h3 as far as some H of the block needs them. hmax[cb][block]: the largest |H|, or
+// 252 and the last digit that an H outside -16 .. 15 needs.
 template <typename T>
 __device__ void pack_x(const T *__restrict__ x, const PackParams &p, int block, unsigned char *__restrict__ xp,
                        unsigned char *__restrict__ dig, unsigned char *__restrict__ hmax)
@@ -332,7 +335,8 @@ __device__ void pack_x(const T *__restrict__ x, const PackParams &p, int block, 
 #pragma unroll
     for (int e = 0; e < kBlockK; ++e) {
         const int h = v[e] >> 16;
-        const int a = h < -16 || h > 15 ? 255 : h < 0 ? -h : h;
+        // (two digits hold -528 .. 495, three -16912 .. 15855)
+        const int a = h >= -16 && h <= 15 ? abs(h) : h >= -528 && h <= 495 ? 253 : h >= -16912 && h <= 15855 ? 254 : 255;
         most = max(most, a);
         put6(h6, e, e2m3(((h + 16) & 31) - 16));
     }
@@ -368,9 +372,9 @@ __device__ void pack_x(const T *__restrict__ x, const PackParams &p, int block, 
     __syncthreads();
     most = max(max(red[0], red[1]), max(red[2], red[3]));
     if (threadIdx.x == 0) hmax[block] = (unsigned char)most;
-    if (most < 255 || !in) return;
+    if (most < 253 || !in) return;
 #pragma unroll 1
-    for (int d = 1; d < 4; ++d) {
+    for (int d = 1; d <= most - 252; ++d) {
         uint32_t q6[6] = {};
 #pragma unroll
         for (int e = 0; e < kBlockK; ++e) {
@@ -518,7 +522,7 @@ mfma_conv_kernel(const ProductArgs a)
     if (place >= share || at >= tiles) return;
     const int tp = at / p.tiles_k, mblk = at - tp * p.tiles_k;
     const int ch0 = int(blockIdx.y) * p.cps, ch1 = min(p.d.nchunks, ch0 + p.cps);
-    const int CB = p.d.CB, R = p.d.R, S = p.d.S;
+    const int CB = p.d.CB, R = p.d.R, S = p.d.S, PH = p.PH, PW = p.PW;
 
     // Where the windows of this lane's two pixels start in the packed copy: the pixel
     // and its row and column (16 bits each; a row no tap can bring inside for a pixel
@@ -537,7 +541,7 @@ mfma_conv_kernel(const ProductArgs a)
     // Pixel of tap (r, s) in the packed copy, or -1 outside it.
     auto pixel = [&](int t, int r, int s) {
         const int ih = (at0[t] >> 16) + r, iw = int(int16_t(at0[t])) + s;
-        return unsigned(ih) < unsigned(p.PH) && unsigned(iw) < unsigned(p.PW) ? pb[t] + r * p.PW + s : -1;
+        return (unsigned(ih) < unsigned(PH)) & (unsigned(iw) < unsigned(PW)) ? pb[t] + r * PW + s : -1;
     };
     const __amdgpu_buffer_rsrc_t xr = rsrc(a.xp, p.xp_bytes);
     const unsigned char *wrow = p.wa + int64_t(mblk) * p.d.nchunks * kStageBytes;
@@ -547,16 +551,12 @@ mfma_conv_kernel(const ProductArgs a)
     // The lane half's block of the next chunk to load, advanced block by block.
     int cb, r, s;
     auto seek = [&](int ch) { block_at(p.d, ch, half, cb, r, s); };
+    const int stride = p.d.even ? 2 : 1;
     auto step = [&]() {
-        ++s;
-        if (s == S) {
-            s = 0;
-            ++r;
-            if (r == R) {
-                r = 0;
-                cb += p.d.even ? 2 : 1;
-            }
-        }
+        const bool row = s + 1 == S, block = row & (r + 1 == R);
+        s = row ? 0 : s + 1;
+        r = block ? 0 : row ? r + 1 : r;
+        cb += block ? stride : 0;
     };
     uint32_t off[2], base;   // byte of the pixel in a plane of 16-byte entries; of the block
     auto locate = [&]() {
@@ -599,29 +599,39 @@ mfma_conv_kernel(const ProductArgs a)
 #pragma unroll
                 for (int i = 0; i < 16; ++i) c0[m][t][i] = c1[m][t][i] = 0.0f;
     };
-    // The sums so far into y, `shift` bits up: stored, or added to what an earlier
-    // call of the same lane stored (`more`); `last` adds the bias and the epilogue.
-    // They pass through the wave's own part of the LDS, so that a store takes 64
-    // consecutive pixels of one channel and the channel's parameters are scalars.
-    auto flush = [&](bool more, bool last, int shift) {
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        __syncthreads();   // nobody reads or fills the staged weights any more
-        int32_t *out = reinterpret_cast<int32_t *>(lds) + wave * 64 * kOutPitch;
+    // The sums so far as integers in the wave's own part of the LDS, `shift` bits up:
+    // written, or added to what is there (`add`). The products of the digits h1 .. h3
+    // meet those of the rest here: y, read and written again by each pass, took as long
+    // as the products (64 -> 64 channels 3 x 3 on 56 x 56 at batch 128, four passes: 514 us
+    // so, 309 us here, with nothing else changed; one pass takes 156).
+    int32_t *const out = reinterpret_cast<int32_t *>(lds) + wave * 64 * kOutPitch;
+    auto park = [&](bool add, int shift) {
 #pragma unroll
         for (int t = 0; t < 2; ++t)
 #pragma unroll
             for (int m = 0; m < 2; ++m)
 #pragma unroll
                 for (int g = 0; g < 4; ++g) {
+                    v4i *const at = reinterpret_cast<v4i *>(out + (t * 32 + (lane & 31)) * kOutPitch + m * 32 + g * 8 + half * 4);
                     v4i v;
 #pragma unroll
                     for (int i = 0; i < 4; ++i)
-                        v[i] = int(uint32_t(int(c0[m][t][g * 4 + i] * 32.0f)) +
-                                   (uint32_t(int(c1[m][t][g * 4 + i] * 16.0f)) << 7));
-                    *reinterpret_cast<v4i *>(out + (t * 32 + (lane & 31)) * kOutPitch + m * 32 + g * 8 + half * 4) = v;
+                        v[i] = int((uint32_t(int(c0[m][t][g * 4 + i] * 32.0f)) +
+                                    (uint32_t(int(c1[m][t][g * 4 + i] * 16.0f)) << 7)) << shift);
+                    if (add) {
+                        const v4i o = *at;
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) v[i] = int(uint32_t(v[i]) + uint32_t(o[i]));
+                    }
+                    *at = v;
                 }
         // Written and read back by the same wave, whose LDS accesses run in order.
         __builtin_amdgcn_wave_barrier();
+    };
+    // They go to y: stored, or added to what an earlier call of the same lane stored
+    // (`more`); `last` adds the bias and the epilogue. Through the LDS a store takes 64
+    // consecutive pixels of one channel and the channel's parameters are scalars.
+    auto emit = [&](bool more, bool last) {
         // Sixteen outputs a lane at a time: the channels of one pixel (64 consecutive
         // pixels a store), or, where y holds a pixel's channels in a row (LinearShift),
         // the pixels of one channel.
@@ -652,13 +662,13 @@ mfma_conv_kernel(const ProductArgs a)
             uint32_t v[16];
             if (byrow) {
 #pragma unroll
-                for (int j = 0; j < 16; ++j) v[j] = uint32_t(src[j * kOutPitch]) << shift;
+                for (int j = 0; j < 16; ++j) v[j] = uint32_t(src[j * kOutPitch]);
             } else {
 #pragma unroll
                 for (int j = 0; j < 16; j += 4) {
                     const v4i q = *reinterpret_cast<const v4i *>(src + j);
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) v[j + i] = uint32_t(q[i]) << shift;
+                    for (int i = 0; i < 4; ++i) v[j + i] = uint32_t(q[i]);
                 }
             }
             const int left = count - j0;
@@ -726,8 +736,8 @@ mfma_conv_kernel(const ProductArgs a)
     const int lane8x = (lane ^ 1) * 8;
     const int sc = kScales;
     if (ch0 >= ch1) return;   // a task with fewer parts than the launch
-    // Largest |H| of the blocks of packed rows this tile reads (255: their h1 .. h3 are
-    // needed), from its first output's first row to its last one's last. The first
+    // Largest |H| of the blocks of packed rows this tile reads (253 .. 255: their digits up
+    // to h1 .. h3 are needed), from its first output's first row to its last one's last. The first
     // entries are fetched before everything else, so that their maximum is formed
     // while the first chunk is on its way. (Over whole images the entries grow with the
     // image: 64 -> 64 channels 3 x 3 on one of 1024 x 1024 took 620 us so, 401 here; 3 -> 16
@@ -754,240 +764,325 @@ mfma_conv_kernel(const ProductArgs a)
     const __amdgpu_buffer_rsrc_t dr = rsrc(a.dig, uint32_t(CB) * uint32_t(p.NP) * uint32_t(kDigBytes));
     const Bounds *bd = p.bounds + 2 * mblk * p.d.nchunks;
     // Pass 0 forms the products of the nibble planes and h0; passes 1 .. 3, for
-    // inputs beyond 20 bits, those of h1, h2, h3, 5 bits further up each.
+    // inputs beyond 20, 25 and 30 bits, those of h1, h2, h3, 5 bits further up each.
     for (int i = lane + 64; i - lane < hnb * CB; i += 64) hm = max(hm, hload(i));
     for (int off = 32; off > 0; off >>= 1) hm = max(hm, __shfl_xor(hm, off));
     hm = __builtin_amdgcn_readfirstlane(hm);
-    const int passes = hm == 255 ? 4 : 1;
+    const int passes = hm < 253 ? 1 : hm - 251;
     hm = min(hm, 16);
-    int pass = 0, ch = ch0;
+    int hleast = 255;   // the least of them, where it matters
+    if (passes > 1) {
+        for (int i = lane; i < hnb * CB; i += 64) hleast = min(hleast, hload(i));
+        for (int off = 32; off > 0; off >>= 1) hleast = min(hleast, __shfl_xor(hleast, off));
+        hleast = __builtin_amdgcn_readfirstlane(hleast);
+    }
+    int ch = ch0, b0 = 0, b1 = 0;
     bool more = false;
+    // Whether chunk c can be added before a sum could leave the exact range.
+    const auto fits = [&](int c) {
+        const Bounds u = bd[2 * c], v = bd[2 * c + 1];
+        b0 += max(u.p0, v.p0) + (hm + 1) * max(u.q0, v.q0);
+        b1 += max(u.r1, v.r1) * (15 + 16 * hm);
+        return b0 <= kLimit && b1 <= kLimit;
+    };
     for (;;) {
         clear();
-        int b0 = 0, b1 = 0;
-        // Chunks until the reduction ends or a sum could leave the exact range.
-        const auto fits = [&](int c) {
-            const Bounds u = bd[2 * c], v = bd[2 * c + 1];
-            const int q0 = max(u.q0, v.q0);
-            b0 += pass ? 17 * q0 : max(u.p0, v.p0) + (hm + 1) * q0;
-            b1 += max(u.r1, v.r1) * (pass ? 271 : 15 + 16 * hm);
-            return b0 <= kLimit && b1 <= kLimit;
-        };
-        if (pass == 0) {
-            (void)fits(ch);
-            do {
-                // This wave's share of the chunk's weights has landed: only the twelve loads
-                // of its inputs, issued later, may be outstanding. Behind the barrier every
-                // share has, and nobody reads the other buffer any more.
-                asm volatile("s_waitcnt vmcnt(12) lgkmcnt(0)" ::: "memory");
-                __builtin_amdgcn_s_barrier();
-                asm volatile("" ::: "memory");
-                stage(ch + 1, (ch + 1 - ch0) & 1);
-                asm volatile("" ::: "memory");
-                const unsigned char *buf = lds + ((ch - ch0) & 1) * kStageBytes;
-                auto a6 = [&](v8i (&a)[2], int i) {
-#pragma unroll
-                    for (int m = 0; m < 2; ++m)
-                        a[m] = wide(*reinterpret_cast<const v4i *>(buf + fp6_lo(i, m) + lane * 16),
-                                    *reinterpret_cast<const v2i *>(buf + fp6_hi(i, m) + (m ? lane8x : lane * 8)));
-                };
-                auto a4 = [&](v8i (&a)[2], int i) {
-#pragma unroll
-                    for (int m = 0; m < 2; ++m)
-                        a[m] = wide(*reinterpret_cast<const v4i *>(buf + fp4_at(i, m) + lane * 16));
-                };
-                // Where the next chunk's inputs are.
-                if (ch + 1 < ch1) {
-                    step();
-                    if (!p.d.even) step();
-                    locate();
-                } else {
-                    off[0] = off[1] = kOOB;
-                }
-                constexpr int kDig = 0x33333333, kBit = 0x22222222;
-                // A step: the products of one matrix, the reads of the next one's share, and
-                // the next digits, cut out while the products run. `region` ends it (the
-                // scheduler keeps a step's instructions together: four products, with
-                // vector instructions between them).
-                v8i aa[2], ab[2];
-                v4i d0[2], d1[2], u[2];
-                auto cut = [&](v4i (&d)[2], const v4i &x0, const v4i &x1, int mask) {
-                    d[0] = x0 & mask;
-                    d[1] = x1 & mask;
-                };
-                auto up = [&](int pl) {
-#pragma unroll
-                    for (int t = 0; t < 2; ++t)
-#pragma unroll
-                        for (int g = 0; g < 4; ++g) u[t][g] = int(uint32_t(xw[t][pl][g]) >> 2);
-                };
-                auto region = [&](auto products) {
-                    // (a count of the products the step holds, in twos of two and three
-                    // vector instructions)
-                    constexpr int n = decltype(products)::value;
-                    __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);
-#pragma unroll
-                    for (int i = 0; i < n; ++i) {
-                        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                        __builtin_amdgcn_sched_group_barrier(0x002, 5, 0);
-                    }
-                    __builtin_amdgcn_sched_barrier(0);
-                };
-                using Four = std::integral_constant<int, 4>;
-                using Eight = std::integral_constant<int, 8>;
-                auto bits = [&](const v8i (&a)[2], const v4i (&d)[2]) {     // S_b, P_0
-#pragma unroll
-                    for (int m = 0; m < 2; ++m)
-#pragma unroll
-                        for (int t = 0; t < 2; ++t) c0[m][t] = mms<kE2M1, kE2M1, kM4>(a[m], wide(d[t]), c0[m][t], sc);
-                };
-                auto powers = [&](const v8i (&a)[2], const v4i (&d)[2]) {   // P_2 ..
-#pragma unroll
-                    for (int m = 0; m < 2; ++m)
-#pragma unroll
-                        for (int t = 0; t < 2; ++t) c0[m][t] = mm<kE3M2, kE2M1>(a[m], wide(d[t]), c0[m][t]);
-                };
-                a4(aa, 0);
-                cut(d0, xw[0][0], xw[1][0], kDig);
-                __builtin_amdgcn_sched_barrier(0);
-                // A plane's registers take the next chunk's plane as soon as its last digit is
-                // cut out.
-                auto plane = [&](auto pl_, auto first, auto last) {
-                    constexpr int pl = decltype(pl_)::value;
-                    a4(ab, 2 * pl + 1);
-                    if constexpr (pl == 0) bits(aa, d0);
-                    else powers(aa, d0);                               // P of the low digit
-                    cut(d1, xw[0][pl], xw[1][pl], kBit);
-                    region(Four());
-                    a6(aa, 2 * pl);
-                    bits(ab, d1);                                      // S of its upper bit
-                    up(pl);
-                    cut(d0, u[0], u[1], kDig);
-                    region(Four());
-                    load_plane(pl);
-                    first();
-                    powers(aa, d0);                                    // P of the high digit
-                    cut(d1, u[0], u[1], kBit);
-                    region(Four());
-                    last();
-                };
-                plane(std::integral_constant<int, 0>(), [&] { a4(ab, 2); }, [&] {
-                    a6(aa, kP4);
-                    bits(ab, d1);                                      // S_3
-                    cut(d0, xw[0][1], xw[1][1], kDig);
-                    region(Four());
-                });
-                plane(std::integral_constant<int, 1>(), [&] { a4(ab, 4); }, [&] {
-                    a6(aa, kP8);
-                    bits(ab, d1);                                      // S_7
-                    cut(d0, xw[0][2], xw[1][2], kDig);
-                    region(Four());
-                });
-                a4(ab, 5);
-                powers(aa, d0);                                        // P_8
-                cut(d1, xw[0][2], xw[1][2], kBit);
-                region(Four());
-                a6(aa, kP10);
-                bits(ab, d1);                                          // S_9
-                up(2);
-                cut(d0, u[0], u[1], kDig);
-                region(Four());
-                load_plane(2);
-                a4(ab, 6);
-                powers(aa, d0);                                        // P_10
-                cut(d1, u[0], u[1], kBit);
-                region(Four());
-                a6(aa, kW);
-                bits(ab, d1);                                          // S_11
-                cut(d1, xw[0][3], xw[1][3], kDig);
-                region(Four());
-                a6(ab, kP12);
+        b0 = b1 = 0;
+        (void)fits(ch);
+        do {
+            // This wave's share of the chunk's weights has landed: only the twelve loads
+            // of its inputs, issued later, may be outstanding. Behind the barrier every
+            // share has, and nobody reads the other buffer any more.
+            asm volatile("s_waitcnt vmcnt(12) lgkmcnt(0)" ::: "memory");
+            __builtin_amdgcn_s_barrier();
+            asm volatile("" ::: "memory");
+            stage(ch + 1, (ch + 1 - ch0) & 1);
+            asm volatile("" ::: "memory");
+            const unsigned char *buf = lds + ((ch - ch0) & 1) * kStageBytes;
+            auto a6 = [&](v8i (&a)[2], int i) {
 #pragma unroll
                 for (int m = 0; m < 2; ++m)
-#pragma unroll
-                    for (int t = 0; t < 2; ++t) {                      // W x d(10), d(12)
-                        c0[m][t] = mms<kE3M2, kE2M1, kP4x>(aa[m], wide(d0[t]), c0[m][t], sc);
-                        c1[m][t] = mm<kE3M2, kE2M1>(aa[m], wide(d1[t]), c1[m][t]);
-                    }
-                region(Eight());
-                cut(d0, xw[0][3], xw[1][3], kBit);
-                powers(ab, d1);                                        // P_12
-                up(3);
-                region(Four());
-                load_plane(3);
-                a4(ab, 7);
-                cut(d1, u[0], u[1], kDig);
+                    a[m] = wide(*reinterpret_cast<const v4i *>(buf + fp6_lo(i, m) + lane * 16),
+                                *reinterpret_cast<const v2i *>(buf + fp6_hi(i, m) + (m ? lane8x : lane * 8)));
+            };
+            auto a4 = [&](v8i (&a)[2], int i) {
 #pragma unroll
                 for (int m = 0; m < 2; ++m)
-#pragma unroll
-                    for (int t = 0; t < 2; ++t)                        // W x H
-                        c1[m][t] = mms<kE3M2, kE2M3, kP2x, kP4x>(aa[m], wide(xl[t], xh[t]), c1[m][t], sc);
-                region(Four());
-#pragma unroll
-                for (int m = 0; m < 2; ++m)
-#pragma unroll
-                    for (int t = 0; t < 2; ++t)                        // W x d(14)
-                        c1[m][t] = mms<kE3M2, kE2M1, kP2x>(aa[m], wide(d1[t]), c1[m][t], sc);
-                __builtin_amdgcn_sched_barrier(0);
-                a6(aa, kP14);
-                bits(ab, d0);                                          // S_13
-                region(Four());
-#pragma unroll
-                for (int m = 0; m < 2; ++m)
-#pragma unroll
-                    for (int t = 0; t < 2; ++t)                        // P_14 x H
-                        c0[m][t] = mms<kE3M2, kE2M3, kP4x>(aa[m], wide(xl[t], xh[t]), c0[m][t], sc);
-                load_h();
-                __builtin_amdgcn_sched_barrier(0);
-                powers(aa, d1);                                        // P_14
-                __builtin_amdgcn_sched_barrier(0);
-                ++ch;
-            } while (ch < ch1 && fits(ch));
-        } else {
-            (void)fits(ch);
-            do {
-                v8i h[2];
-#pragma unroll
-                for (int t = 0; t < 2; ++t) {
-                    const int px = cb < CB ? pixel(t, r, s) : -1, pix = max(px, 0);
-                    const bool some = px >= 0 && hmax[(px >= 0 ? cb : 0) * p.nblk + (pix >> 8)] == 255;
-                    const uint32_t dbase = (uint32_t(cb) * 3u + uint32_t(pass - 1)) * uint32_t(p.NP) * 24u;
-                    const v4i lo = __builtin_amdgcn_raw_buffer_load_b128(dr, some ? dbase + uint32_t(pix) * 16u : kOOB, 0, 0);
-                    const v2i hi = __builtin_amdgcn_raw_buffer_load_b64(
-                        dr, some ? dbase + uint32_t(np16) + uint32_t(pix) * 8u : kOOB, 0, 0);
-                    h[t] = wide(lo, hi);
-                }
-                const unsigned char *st = wrow + int64_t(ch) * kStageBytes;
-#pragma unroll
-                for (int m = 0; m < 2; ++m) {
-                    const v8i a = wide(*reinterpret_cast<const v4i *>(st + fp6_lo(kP14, m) + lane * 16),
-                                       *reinterpret_cast<const v2i *>(st + fp6_hi(kP14, m) + (lane ^ m) * 8));
-                    const v8i w = wide(*reinterpret_cast<const v4i *>(st + fp6_lo(kW, m) + lane * 16),
-                                       *reinterpret_cast<const v2i *>(st + fp6_hi(kW, m) + (lane ^ m) * 8));
-#pragma unroll
-                    for (int t = 0; t < 2; ++t) {
-                        c0[m][t] = mms<kE3M2, kE2M3, kP4x>(a, h[t], c0[m][t], sc);
-                        c1[m][t] = mms<kE3M2, kE2M3, kP2x, kP4x>(w, h[t], c1[m][t], sc);
-                    }
-                }
+                    a[m] = wide(*reinterpret_cast<const v4i *>(buf + fp4_at(i, m) + lane * 16));
+            };
+            // Where the next chunk's inputs are.
+            if (ch + 1 < ch1) {
                 step();
                 if (!p.d.even) step();
-                ++ch;
-            } while (ch < ch1 && fits(ch));
-        }
-        const bool end = ch == ch1;
-        flush(more, end && pass + 1 == passes, 5 * pass);
+                locate();
+            } else {
+                off[0] = off[1] = kOOB;
+            }
+            constexpr int kDig = 0x33333333, kBit = 0x22222222;
+            // A step: the products of one matrix, the reads of the next one's share, and
+            // the next digits, cut out while the products run. `region` ends it (the
+            // scheduler keeps a step's instructions together: four products, with
+            // vector instructions between them).
+            v8i aa[2], ab[2];
+            v4i d0[2], d1[2], u[2];
+            auto cut = [&](v4i (&d)[2], const v4i &x0, const v4i &x1, int mask) {
+                d[0] = x0 & mask;
+                d[1] = x1 & mask;
+            };
+            auto up = [&](int pl) {
+#pragma unroll
+                for (int t = 0; t < 2; ++t)
+#pragma unroll
+                    for (int g = 0; g < 4; ++g) u[t][g] = int(uint32_t(xw[t][pl][g]) >> 2);
+            };
+            auto region = [&](auto products) {
+                // (a count of the products the step holds, in twos of two and three
+                // vector instructions)
+                constexpr int n = decltype(products)::value;
+                __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);
+#pragma unroll
+                for (int i = 0; i < n; ++i) {
+                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                    __builtin_amdgcn_sched_group_barrier(0x002, 5, 0);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            };
+            using Four = std::integral_constant<int, 4>;
+            using Eight = std::integral_constant<int, 8>;
+            auto bits = [&](const v8i (&a)[2], const v4i (&d)[2]) {     // S_b, P_0
+#pragma unroll
+                for (int m = 0; m < 2; ++m)
+#pragma unroll
+                    for (int t = 0; t < 2; ++t) c0[m][t] = mms<kE2M1, kE2M1, kM4>(a[m], wide(d[t]), c0[m][t], sc);
+            };
+            auto powers = [&](const v8i (&a)[2], const v4i (&d)[2]) {   // P_2 ..
+#pragma unroll
+                for (int m = 0; m < 2; ++m)
+#pragma unroll
+                    for (int t = 0; t < 2; ++t) c0[m][t] = mm<kE3M2, kE2M1>(a[m], wide(d[t]), c0[m][t]);
+            };
+            a4(aa, 0);
+            cut(d0, xw[0][0], xw[1][0], kDig);
+            __builtin_amdgcn_sched_barrier(0);
+            // A plane's registers take the next chunk's plane as soon as its last digit is
+            // cut out.
+            auto plane = [&](auto pl_, auto first, auto last) {
+                constexpr int pl = decltype(pl_)::value;
+                a4(ab, 2 * pl + 1);
+                if constexpr (pl == 0) bits(aa, d0);
+                else powers(aa, d0);                               // P of the low digit
+                cut(d1, xw[0][pl], xw[1][pl], kBit);
+                region(Four());
+                a6(aa, 2 * pl);
+                bits(ab, d1);                                      // S of its upper bit
+                up(pl);
+                cut(d0, u[0], u[1], kDig);
+                region(Four());
+                load_plane(pl);
+                first();
+                powers(aa, d0);                                    // P of the high digit
+                cut(d1, u[0], u[1], kBit);
+                region(Four());
+                last();
+            };
+            plane(std::integral_constant<int, 0>(), [&] { a4(ab, 2); }, [&] {
+                a6(aa, kP4);
+                bits(ab, d1);                                      // S_3
+                cut(d0, xw[0][1], xw[1][1], kDig);
+                region(Four());
+            });
+            plane(std::integral_constant<int, 1>(), [&] { a4(ab, 4); }, [&] {
+                a6(aa, kP8);
+                bits(ab, d1);                                      // S_7
+                cut(d0, xw[0][2], xw[1][2], kDig);
+                region(Four());
+            });
+            a4(ab, 5);
+            powers(aa, d0);                                        // P_8
+            cut(d1, xw[0][2], xw[1][2], kBit);
+            region(Four());
+            a6(aa, kP10);
+            bits(ab, d1);                                          // S_9
+            up(2);
+            cut(d0, u[0], u[1], kDig);
+            region(Four());
+            load_plane(2);
+            a4(ab, 6);
+            powers(aa, d0);                                        // P_10
+            cut(d1, u[0], u[1], kBit);
+            region(Four());
+            a6(aa, kW);
+            bits(ab, d1);                                          // S_11
+            cut(d1, xw[0][3], xw[1][3], kDig);
+            region(Four());
+            a6(ab, kP12);
+#pragma unroll
+            for (int m = 0; m < 2; ++m)
+#pragma unroll
+                for (int t = 0; t < 2; ++t) {                      // W x d(10), d(12)
+                    c0[m][t] = mms<kE3M2, kE2M1, kP4x>(aa[m], wide(d0[t]), c0[m][t], sc);
+                    c1[m][t] = mm<kE3M2, kE2M1>(aa[m], wide(d1[t]), c1[m][t]);
+                }
+            region(Eight());
+            cut(d0, xw[0][3], xw[1][3], kBit);
+            powers(ab, d1);                                        // P_12
+            up(3);
+            region(Four());
+            load_plane(3);
+            a4(ab, 7);
+            cut(d1, u[0], u[1], kDig);
+#pragma unroll
+            for (int m = 0; m < 2; ++m)
+#pragma unroll
+                for (int t = 0; t < 2; ++t)                        // W x H
+                    c1[m][t] = mms<kE3M2, kE2M3, kP2x, kP4x>(aa[m], wide(xl[t], xh[t]), c1[m][t], sc);
+            region(Four());
+#pragma unroll
+            for (int m = 0; m < 2; ++m)
+#pragma unroll
+                for (int t = 0; t < 2; ++t)                        // W x d(14)
+                    c1[m][t] = mms<kE3M2, kE2M1, kP2x>(aa[m], wide(d1[t]), c1[m][t], sc);
+            __builtin_amdgcn_sched_barrier(0);
+            a6(aa, kP14);
+            bits(ab, d0);                                          // S_13
+            region(Four());
+#pragma unroll
+            for (int m = 0; m < 2; ++m)
+#pragma unroll
+                for (int t = 0; t < 2; ++t)                        // P_14 x H
+                    c0[m][t] = mms<kE3M2, kE2M3, kP4x>(aa[m], wide(xl[t], xh[t]), c0[m][t], sc);
+            load_h();
+            __builtin_amdgcn_sched_barrier(0);
+            powers(aa, d1);                                        // P_14
+            __builtin_amdgcn_sched_barrier(0);
+            ++ch;
+        } while (ch < ch1 && fits(ch));
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();   // nobody reads or fills the staged weights any more
+        park(false, 0);
+        if (ch == ch1) break;
+        // A sum would leave the exact range: y takes what there is, the staging goes on.
+        emit(more, false);
         more = true;
-        if (end) {
-            if (++pass == passes) break;
+        __syncthreads();   // every wave has read its sums back
+        stage(ch, (ch - ch0) & 1);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    }
+    ch = ch0;
+    // Whether all of the part's chunks fit a digit pass's sums; if not, 15 do, whatever
+    // their weights (a chunk's q0 is at most 64 * 2^16 / 2^6, its r1 64 * 32).
+    int most = 15;
+    if (passes > 1) {
+        int sum0 = 0, sum1 = 0;
+        for (int i = ch0 + lane; i < ch1; i += 64) {
+            const Bounds u = bd[2 * i], v = bd[2 * i + 1];
+            sum0 = min(sum0 + 17 * max(u.q0, v.q0), kLimit + 1);
+            sum1 = min(sum1 + 271 * max(u.r1, v.r1), kLimit + 1);
+        }
+        for (int off = 32; off > 0; off >>= 1) {
+            sum0 = min(sum0 + __shfl_xor(sum0, off), kLimit + 1);
+            sum1 = min(sum1 + __shfl_xor(sum1, off), kLimit + 1);
+        }
+        if (__builtin_amdgcn_readfirstlane(max(sum0, sum1)) <= kLimit) most = ch1 - ch0;
+    }
+    static_assert(15 * 17 * 64 * 1024 <= kLimit && 15 * 271 * 64 * 32 <= kLimit, "15 chunks of a digit pass");
+    for (int pass = 1; pass < passes;) {
+        const int stop = min(ch1, ch + most);
+        clear();
+        // A chunk's two matrices are staged beside the parked sums during the chunk before,
+        // its digits loaded kAhead chunks before: a pass touches them once, and what comes
+        // from beyond L2 takes as long as several chunks. Where only some blocks have
+        // digits of this pass, an entry of hmax for each pixel tells. (256 -> 256 channels
+        // 3 x 3 on 14 x 14 at batch 128 over all of int32, four passes: 276 us with a
+        // chunk's loads issued during the one before, 243 four ahead, 219 without a load
+        // of the bounds between them, which waits for all that is on its way; with inputs
+        // to 2^23, two passes, 166; one pass 135.)
+        auto stage2 = [&](int c, int buf) {
+            const uint32_t from = uint32_t(c) * uint32_t(kStageBytes) + uint32_t(fp6_lo(kP14, 0));
+#pragma unroll
+            for (int i = 0; i < kDigitStage / 1024; i += 4)
+                if (i + wave < kDigitStage / 1024)
+                    __builtin_amdgcn_raw_ptr_buffer_load_lds(
+                        wr, (lds_ptr_t)(lds + kParked + buf * kDigitStage + (i + wave) * 1024), 16, uint32_t(lane * 16),
+                        from + uint32_t(i + wave) * 1024u, 0, 0);
+            asm volatile("" ::: "memory");   // the digits' loads come after it: it is waited for by count
+        };
+        auto run = [&](auto all_) {
+            constexpr bool all = decltype(all_)::value;
+            constexpr int kAhead = 4;
+            auto fetch = [&](v8i &a0, v8i &a1, bool &some) {
+                const uint32_t dbase = (uint32_t(cb) * 3u + uint32_t(pass - 1)) * uint32_t(p.NP) * 24u;
+                bool in[2];
+                v8i v[2];
+#pragma unroll
+                for (int t = 0; t < 2; ++t) {
+                    const int px = cb < CB ? pixel(t, r, s) : -1;
+                    in[t] = px >= 0;
+                    if constexpr (!all) in[t] = in[t] & (hmax[in[t] ? cb * p.nblk + (px >> 8) : 0] >= 252 + pass);
+                    const v4i lo = __builtin_amdgcn_raw_buffer_load_b128(dr, in[t] ? dbase + uint32_t(px) * 16u : kOOB, 0, 0);
+                    const v2i hi = __builtin_amdgcn_raw_buffer_load_b64(
+                        dr, in[t] ? dbase + uint32_t(np16) + uint32_t(px) * 8u : kOOB, 0, 0);
+                    v[t] = wide(lo, hi);
+                }
+                a0 = v[0];
+                a1 = v[1];
+                some = all || __ballot(in[0] | in[1]) != 0;
+                step();
+                if (!p.d.even) step();
+            };
+            v8i q[kAhead][2];
+            bool some[kAhead];
+            seek(ch);
+            stage2(ch, 0);
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u) fetch(q[u][0], q[u][1], some[u]);
+            asm volatile("s_waitcnt vmcnt(16)" ::: "memory");
+            __builtin_amdgcn_s_barrier();
+            asm volatile("" ::: "memory");
+            int buf = 0;
+            for (;;) {
+#pragma unroll
+                for (int u = 0; u < kAhead; ++u) {
+                    const v8i h[2] = {q[u][0], q[u][1]};
+                    const bool now = some[u];
+                    if (ch + 1 < ch1) stage2(ch + 1, buf ^ 1);
+                    fetch(q[u][0], q[u][1], some[u]);
+                    if (now) {
+                        const unsigned char *st = lds + kParked + buf * kDigitStage - fp6_lo(kP14, 0);
+#pragma unroll
+                        for (int m = 0; m < 2; ++m) {
+                            const int l8 = m ? lane8x : lane * 8;
+                            const v8i a = wide(*reinterpret_cast<const v4i *>(st + fp6_lo(kP14, m) + lane * 16),
+                                               *reinterpret_cast<const v2i *>(st + fp6_hi(kP14, m) + l8));
+                            const v8i w = wide(*reinterpret_cast<const v4i *>(st + fp6_lo(kW, m) + lane * 16),
+                                               *reinterpret_cast<const v2i *>(st + fp6_hi(kW, m) + l8));
+#pragma unroll
+                            for (int t = 0; t < 2; ++t) {
+                                c0[m][t] = mms<kE3M2, kE2M3, kP4x>(a, h[t], c0[m][t], sc);
+                                c1[m][t] = mms<kE3M2, kE2M3, kP2x, kP4x>(w, h[t], c1[m][t], sc);
+                            }
+                        }
+                    }
+                    // The next chunk's share has landed (only this chunk's four loads of digits
+                    // came later), every wave's behind the barrier; this one's have been read.
+                    asm volatile("s_waitcnt vmcnt(4) lgkmcnt(0)" ::: "memory");
+                    __builtin_amdgcn_s_barrier();
+                    asm volatile("" ::: "memory");
+                    buf ^= 1;
+                    ++ch;
+                    if (ch == stop) return;
+                }
+            }
+        };
+        if (hleast >= 252 + pass) run(std::true_type());
+        else run(std::false_type());
+        park(true, 5 * pass);
+        if (ch == ch1) {
+            ++pass;
             ch = ch0;
-            seek(ch0);
-        } else if (pass == 0) {
-            __syncthreads();   // every wave has read its sums back
-            stage(ch, (ch - ch0) & 1);
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         }
     }
+    emit(more, true);
 }
 
 constexpr int64_t round256(int64_t v) { return (v + 255) & ~int64_t(255); }

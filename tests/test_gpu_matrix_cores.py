@@ -33,6 +33,13 @@ def inputs(rng, mode, shape):
         x = rng.integers(0, 2 ** 18, shape)
         spots = rng.choice(x.size, 6, replace=False)
         x.flat[spots] = rng.integers(-(2 ** 31), 2 ** 31, 6)
+    elif mode in ("two", "three", "four"):   # what is above bit 15 at the ends of two or three digits, or past them
+        ends = {"two": [-528, -17, 16, 495], "three": [-16912, -529, 496, 15855], "four": [-32768, -16913, 15856, 32767]}
+        x = rng.choice(ends[mode] + [0], shape) * 65536 + rng.integers(0, 65536, shape)
+    elif mode == "mixed":     # values of one to four digits, few enough that some tiles and blocks have none
+        x = rng.integers(0, 2 ** 18, shape)
+        spots = rng.choice(x.size, 8, replace=False)
+        x.flat[spots] = rng.choice([-1, 1], 8) * 2 ** np.array([19, 21, 24, 26, 29, 30, 22, 27])
     else:                     # "full": all of int32
         x = rng.integers(-(2 ** 31), 2 ** 31, shape, dtype=np.int64)
     return x.astype(np.int32)
@@ -58,6 +65,14 @@ CASES = [
     (3, 33, 35, 41, 64, 1, 1, 2, 0, "spots"),     # sampled
     (1, 32, 50, 60, 64, 3, 3, 1, 9, "spots"),     # tiles whose rows lie in the padding
     (1, 32, 40, 300, 64, 3, 1, 3, 0, "one"),      # rows wider than a tile
+    # every number of digits, whole and split, odd and even block counts, past a tile's edges
+    (2, 40, 13, 21, 70, 3, 3, 1, 1, "two"),
+    (2, 72, 13, 21, 70, 3, 3, 1, 1, "three"),
+    (2, 40, 13, 21, 70, 1, 1, 1, 0, "three"),
+    (2, 64, 13, 21, 70, 3, 3, 1, 1, "four"),
+    (1, 96, 60, 50, 65, 3, 3, 1, 1, "mixed"),
+    (2, 3, 61, 50, 64, 7, 7, 2, 3, "mixed"),      # folded
+    (300, 130, 1, 1, 130, 1, 1, 1, 0, "mixed"),
 ]
 
 
@@ -81,7 +96,8 @@ def test_matrix_core_convolutions_match_oracle(case, knob):
     assert np.all(edge[:256] == 0x5A5A5A5A) and np.all(edge[256 + size:] == 0x5A5A5A5A)
 
 
-@pytest.mark.parametrize("value,shift", [(2 ** 20 - 1, 6), (-(2 ** 20), 6), (2 ** 20 - 1, 0), (2 ** 31 - 1, 0)])
+@pytest.mark.parametrize("value,shift", [(2 ** 20 - 1, 6), (-(2 ** 20), 6), (2 ** 20 - 1, 0), (2 ** 31 - 1, 0),
+                                         (15855 * 2 ** 16 + 65535, 6), (-16912 * 2 ** 16, 0), (-(2 ** 31), 6)])
 def test_sums_past_the_accumulators_exact_range(value, shift, knob):
     """1056 equal terms of the largest size an accumulator meets (shift 6 in one, shift
     0 in the other): a tile that walked them in one go would pass 2^24 units. The grid
