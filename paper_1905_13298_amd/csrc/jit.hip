@@ -1018,6 +1018,49 @@ static bool matrix_allowed(int splits)
     return splits == 0 && (forced_variant() < 0 || forced_variant() == 64);
 }
 
+// Non-zero codes among `rows` packed rows of `cols` codes.
+static int64_t nonzero_codes(const uint32_t *wp, int64_t rows, int64_t cols, int bits)
+{
+    const int per = 32 / bits;
+    uint32_t ones = 0;   // bit 0 of every code in a word
+    for (int j = 0; j < per; ++j) ones |= 1u << (bits * j);
+    const int64_t full = cols / per, rw = row_words_bits(cols, bits);
+    const uint32_t rest = ones & ((1u << (bits * int(cols % per))) - 1u);
+    int64_t zeros = 0;
+    for (int64_t k = 0; k < rows; ++k) {
+        const uint32_t *row = wp + k * rw;
+        // A zero code is one whose bits below the sign are all ones.
+        auto count = [&](uint32_t w, uint32_t mask) {
+            uint32_t z = w;
+            for (int b = 1; b < bits - 1; ++b) z &= w >> b;
+            return __builtin_popcount(z & mask);
+        };
+        for (int64_t i = 0; i < full; ++i) zeros += count(row[i], ones);
+        if (rest) zeros += count(row[full], rest);
+    }
+    return rows * cols - zeros;
+}
+
+// Expected duration (us) of a plan of generated code on MI355X: `terms` products of
+// which `share` have non-zero weights, in groups of 64 channels that each read `taps`
+// times an input of x_elems elements. A launch, and 50 T instructions/s: one a non-zero
+// term and about twelve an input element and group (load, wait, offset, the distinct
+// shifts), which at the ResNets' 20 % of zeros are as many as the terms, so that denser
+// weights are rated alike. Sparser ones are bound by reading x: 14 TB/s over groups and
+// taps, 1.8 TB/s for the first time, partly overlapped; they have to be a tenth ahead.
+// Measured in generated code and on the matrix cores, by share of zeros: 256 -> 256 3 x 3
+// on 14 x 14 at batch 128 20 % 244 and 133, 70 % 127 and 129, 90 % 99 and 127; 64 -> 64 on
+// 56 x 56 50 % 172 and 154, 70 % 124 and 152; 256 -> 1024 on 14 x 14 50 % 86 and 80, 70 % 65
+// and 80; 1024 -> 256 50 % 100 and 92, 90 % 95 and 90; 512 -> 512 3 x 3 on 7 x 7 at batch 32
+// 20 % 74 and 62, 50 % 55 and 61; 4096 -> 4096 at batch 256 50 % 63 and 58, 70 % 51 and 58.
+static double generated_us(int64_t terms, double share, int64_t channels, double taps, int64_t x_elems)
+{
+    const double dense = double(terms) / 50e6, groups = double((channels + kTN - 1) / kTN);
+    const double issue = dense * (share + 12.0 * groups / double(channels));
+    const double reads = 4.0 * double(x_elems) * (groups * taps / 14e6 + 1.0 / 1.8e6);
+    return 3.0 + std::min(dense, 1.1 * (std::max(issue, reads) + 0.15 * std::min(issue, reads)));
+}
+
 // Completes a plan on the matrix cores: allocates its weights and the packed copy
 // of its input, and expands the weights (wp: host packed codes, `words` of them).
 // `no_room`: they could not be allocated, and generated code, which holds a
@@ -1171,8 +1214,12 @@ extern "C" ds_status ds_jit_conv_create(const uint32_t *w_packed, const int32_t 
         t.g = g;
         t.w = mfma_forward_weights(g);
         if (matrix_allowed(splits)) t.l = mfma_layout(g);
-        if (t.l.fits && (forced_variant() == 64 ||
-                         mfma_prefer_plan(&t, 1, int64_t(g.n) * g.c * g.h * g.w, int64_t(g.n) * g.oh * g.ow * g.k * g.crs))) {
+        const int64_t xe = int64_t(g.n) * g.c * g.h * g.w;
+        auto generated = [&]() {
+            return generated_us(int64_t(g.n) * g.oh * g.ow * g.k * g.crs,
+                                double(nonzero_codes(w_packed, g.k, g.crs, g.bits)) / (double(g.k) * g.crs), g.k, g.r * g.s, xe);
+        };
+        if (t.l.fits && (forced_variant() == 64 || mfma_plan_us(&t, 1, xe) < generated())) {
             if (sp.act_bytes < 4) t.l.dig_bytes = 0;   // no input leaves the range of one digit
             ds_jit_conv *p = new ds_jit_conv;
             p->sp = sp;
@@ -1239,8 +1286,13 @@ extern "C" ds_status ds_jit_conv_backward_data_create(const uint32_t *w_packed, 
             if (ph.g.r == 0 || ph.g.s == 0) p->zeros.push_back(ph);
         bool zeros = false;
         int64_t terms = 0;
+        const int64_t ye = int64_t(g.n) * g.k * g.oh * g.ow;
+        auto generated = [&]() {
+            return generated_us(terms, double(nonzero_codes(w_packed, g.k, g.crs, g.bits)) / (double(g.k) * g.crs), g.c,
+                                g.r * g.s, ye);
+        };
         if (matrix_allowed(splits) && mfma_gradient_tasks(g, p->tasks, zeros, terms) &&
-            (forced_variant() == 64 || mfma_prefer_plan(p->tasks.data(), p->tasks.size(), int64_t(g.n) * g.k * g.oh * g.ow, terms))) {
+            (forced_variant() == 64 || mfma_plan_us(p->tasks.data(), p->tasks.size(), ye) < generated())) {
             bool no_room;
             st = build_matrix_plan(p, w_packed, size_t(g.k) * size_t(rw), Spec(), no_room);
             if (st == DS_SUCCESS) {

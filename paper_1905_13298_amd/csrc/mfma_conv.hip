@@ -1162,18 +1162,15 @@ bool mfma_prefer(const ConvGeom &g, int64_t terms)
     return linear || (g.k > 16 && terms >= 4000000) || terms >= 50000000;
 }
 
-// A plan's two paths, in microseconds on MI355X (graph replays). Here: two launches
-// and what a tile does besides its products (10), the packed copy of x written and
-// read at 5.5 TB/s, the products of whole tiles at 130 T terms/s (2.2 a chunk at
-// least), y at 4 TB/s, 15 for a split reduction. Generated code: 50 T terms/s at the ResNets' share of zero
-// weights, and a launch. Measured (estimated) here against generated code: 256 ->
-// 256 3x3 on 14x14 at batch 128 138 (138) against 280 (299), 64 -> 64 3x3 on 56x56
-// 177 (181) against 278 (299), 1024 -> 256 on 14x14 95 (98) against 134 (135), 512
-// -> 512 3x3 on 7x7 at batch 32 63 (55) against 86 (77), 4096 -> 4096 at batch 256
-// 64 (60) against 102 (89); the other way 512 -> 128 on 28x28 135 (136) against 124
-// (135), 64 -> 256 on 56x56 196 (195) against 157 (135), the 7x7 stem 376 (355)
-// against 313 (305), 128 -> 128 3x3 on 28x28 at batch 8 32 (35) against 28 (21).
-bool mfma_prefer_plan(const MfmaTask *tasks, size_t ntasks, int64_t x_elems, int64_t terms)
+// In microseconds on MI355X (graph replays): two launches and what a tile does
+// besides its products (10), the packed copy of x written and read at 5.5 TB/s, the
+// products of whole tiles at 130 T terms/s (2.2 a chunk at least), y at 4 TB/s, 15 for
+// a split reduction. Measured (estimated): 256 -> 256 3x3 on 14x14 at batch 128 138
+// (138), 64 -> 64 3x3 on 56x56 177 (181), 1024 -> 256 on 14x14 95 (98), 512 -> 512 3x3
+// on 7x7 at batch 32 63 (55), 4096 -> 4096 at batch 256 64 (60), 512 -> 128 on 28x28
+// 135 (136), 64 -> 256 on 56x56 196 (195), the 7x7 stem 376 (355), 128 -> 128 3x3 on
+// 28x28 at batch 8 32 (35).
+double mfma_plan_us(const MfmaTask *tasks, size_t ntasks, int64_t x_elems)
 {
     const MfmaLayout &l = tasks[0].l;
     double us = 10.0 + (4.0 * x_elems + 2.75 * 32.0 * l.CB * l.NP) / 5.5e6;
@@ -1186,7 +1183,7 @@ bool mfma_prefer_plan(const MfmaTask *tasks, size_t ntasks, int64_t x_elems, int
         split = split || t.l.splits > 1;
     }
     if (split) us += 15.0;
-    return us < 3.0 + double(terms) / 50e6;
+    return us;
 }
 
 MfmaWeights mfma_forward_weights(const ConvGeom &g)

@@ -68,9 +68,8 @@ hipError_t mfma_multiply(const MfmaTask *tasks, int ntasks, const unsigned char 
 // false when a phase has no layout. `terms`: of all phases.
 bool mfma_gradient_tasks(const ConvGeom &g, std::vector<MfmaTask> &tasks, bool &zeros, int64_t &terms);
 
-// Whether tasks on an input of x_elems elements, `terms` in all, are expected to run
-// faster here (the weights expanded when the plan is made) than as a plan's
-// generated code.
-bool mfma_prefer_plan(const MfmaTask *tasks, size_t ntasks, int64_t x_elems, int64_t terms);
+// Expected duration (us) of a plan's tasks on an input of x_elems elements, the
+// weights expanded when the plan is made.
+double mfma_plan_us(const MfmaTask *tasks, size_t ntasks, int64_t x_elems);
 
 }  // namespace ds

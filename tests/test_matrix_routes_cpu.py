@@ -87,3 +87,36 @@ for create in (lambda p: lib.ds_jit_conv_create(wp.ctypes.data, None, None, None
     assert lib.ds_jit_conv_run(p, far[0], None, far[2], None) == 0 and "generated" in kernels()
     lib.ds_jit_conv_destroy(p)
 """, tmp_path)
+
+
+def test_plans_of_sparse_weights_are_generated_code(tmp_path):
+    """Generated code has an instruction a non-zero weight, the matrix cores' time does not
+    depend on them: plans of the same layer take the one or the other by the share of
+    zero codes, of any width and with a last word that is not full. (Against a stand-in
+    runtime.)"""
+    run("""
+from paper_1905_13298_amd import ops
+shape = (128, 256, 14, 14, 256, 3, 3, 1, 1, 1, 1)
+def plan(codes, bits, gradient):
+    wp = ops.pack_shift_weights(codes, bits=bits)
+    p = ctypes.c_void_p()
+    flags = 0 if bits == 5 else ops.code_bits_flag(bits)
+    if gradient:
+        st = lib.ds_jit_conv_backward_data_create(wp.ctypes.data, *shape, flags, 0, ctypes.byref(p))
+    else:
+        st = lib.ds_jit_conv_create(wp.ctypes.data, None, None, None, 0, *shape, flags, 0, ctypes.byref(p))
+    assert st == 0, lib.ds_last_error_message()
+    matrix = lib.ds_jit_conv_matrix_cores(p)
+    lib.ds_jit_conv_destroy(p)
+    return matrix
+mock.mock_reset(ALL)
+rng = np.random.default_rng(0)
+for bits in (5, 4, 3, 2):
+    top = (1 << (bits - 1)) - 1                # its shifts are 0 .. top - 1
+    for zeros, matrix in ((0.0, 1), (0.2, 1), (0.5, 1), (0.9, 0), (1.0, 0)):
+        sign, shift = rng.integers(0, 2, (256, 2304)), rng.integers(0, top, (256, 2304))
+        shift[rng.random(shift.shape) < zeros] = 15
+        codes = (sign << 4 | shift).astype(np.uint8)
+        for gradient in (False, True):
+            assert plan(codes, bits, gradient) == matrix, (bits, zeros, gradient)
+""", tmp_path)
