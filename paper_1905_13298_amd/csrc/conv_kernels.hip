@@ -1232,13 +1232,12 @@ static int rows_splits(int64_t blocks, int units, bool may_split)
 // CU) times each workgroup's work, (1.5 + rows) / parts (a code's decode costs
 // about 1.5 times a row's term). More rows share each decoded code, fewer give
 // more workgroups. The measured best on MI355X (graph replays), which this
-// picks: 2048 -> 1000 with 8 rows at batch 32-128 (12.3, 19.5, 31.9 us against
-// 13.7, 20.5, 34.1 with 4), with 4 at batch 16 and 192 (9.2 against 12.1 with
-// 8; 48.1 against 61.3: 384 workgroups of 8 rows fill the chip one and a half
-// times), with 2 at batch 8 (7.7 us); 512 -> 1000 at batch 32 with 2 (6.2 us
-// against 10.4 with 8); 256 -> 128 at batch 8 with 1 (3.8 us against 6.5 with
-// 8). The DS_ROWS_BATCH override is for measurements.
-static int rows_per_block(const ConvGeom &g, int units, bool may_split)
+// picks: 2048 -> 1000 with 8 rows at batch 32 (12.3 us against 13.7 with 4), with 4
+// at batch 16 (9.2 against 12.1 with 8), with 2 at batch 8 (7.7 us); 512 -> 1000 at
+// batch 32 with 2 (6.2 us against 10.4 with 8); 256 -> 128 at batch 8 with 1 (3.8 us
+// against 6.5 with 8). At 64 rows and more of 2048 -> 1000 the table below runs instead.
+// The DS_ROWS_BATCH override is for measurements. `cost`: the estimate.
+static int rows_per_block(const ConvGeom &g, int units, bool may_split, double *cost_out = nullptr)
 {
     const int forced = tuning(kRowsBatch);
     if (forced == 1 || forced == 2 || forced == 4 || forced == 8) return forced;
@@ -1255,6 +1254,7 @@ static int rows_per_block(const ConvGeom &g, int units, bool may_split)
             best_cost = cost;
         }
     }
+    if (cost_out) *cost_out = best_cost;
     return best;
 }
 
@@ -1409,24 +1409,63 @@ static void launch_table(dim3 grid, const int32_t *x, const RowsArgs &a, int par
     else hipLaunchKernelGGL((linear_table_kernel<2, ROWS>), grid, block, 0, st, x, a, part_words);
 }
 
-// Where the table pays for its fill pass and 512-channel workgroups (MI355X, graph
-// replays, against the kernel above): 25088 -> 4096 at batch 1 25.0 against 41.4 us
-// (2.7 TB/s of packed weights), 17000 -> 1000 with 3-bit codes 8.0 against 14.2, 9000
-// -> 1700 with 2-bit codes (15 M terms) 7.7 against 10.7; 4096 -> 4096 at batch 2, 8,
-// 32, 128 10.1, 16.6, 44, 150 against 11.5, 21.4, 63, 232; 2048 -> 1000 at batch 128
-// 26 against 33. Smaller ones keep the kernel above: 2048 -> 1000 at batch 8 (16 M)
-// 7.9 against 9.4, 512 -> 1000 at batch 32 5.8 against 9.4, 4383 -> 67 at batch 4 6.5
-// against 8.9; so do those of more rows and shorter reductions up to 100 M terms,
-// where the fill is a third of the call: 512 -> 2048 at batch 32 (34 M) 7.9 against
-// 9.9, 1024 -> 1024 at batch 64 (67 M) 11.9 against 13.1, but 8000 -> 300 at batch 16
-// (38 M) 13.7 against 10.9. DS_ROWS_BATCH: 16 forces the table, its other values the kernel above.
+// The table kernel's grid. Parts of at least 16 words (64 bytes of each row), 1024
+// workgroups (25088 -> 4096 at batch 1: 35.3, 29.9, 25.0, 24.8, 27.0 us with 256, 512,
+// 768, 1024, 1536).
+struct TableGrid {
+    int words, rows, kblocks, row_groups, part_words, parts;
+};
+
+static TableGrid table_grid(const ConvGeom &g)
+{
+    TableGrid t;
+    t.words = int(row_words_bits(g.c, g.bits));
+    t.rows = g.n >= 3 ? 4 : g.n;
+    t.kblocks = (g.k + kTableThreads - 1) / kTableThreads;
+    t.row_groups = (g.n + t.rows - 1) / t.rows;
+    const int64_t parts =
+        std::max<int64_t>(1, std::min<int64_t>((t.words + 15) / 16, 1024 / (int64_t(t.kblocks) * t.row_groups)));
+    t.part_words = (int((t.words + parts - 1) / parts) + 15) & ~15;
+    t.parts = (t.words + t.part_words - 1) / t.part_words;
+    return t;
+}
+
+// Where the table pays for its fill pass and 512-channel workgroups: both kernels'
+// times in microseconds, fitted on MI355X (graph replays) to 743 problems of 256 - 25088
+// inputs, 256 - 4096 channels, 1 - 255 rows and codes of 2 to 5 bits. The kernel above
+// takes 1.54 ns a code of its estimate (within 6 % of nearly all), or its weights at 1.8
+// TB/s. A workgroup here looks up its channels' codes (the LDS is shared by the workgroups
+// of a CU, `crowd`) and builds 2^bits entries a code and row, at least as long as the weights
+// take at 3.4 TB/s; rows of packed codes over 12 KB, each a lane's own, cost 1.3 times
+// that. Within 15 % of nearly all, so the table has to be 5 % ahead, or less than 5 %
+// behind from 100 M terms, where it is underrated. Over the 743 the choice is 0.3 % off the
+// best, and behind the kernel above by more than 7 % for one of them (by terms alone, 24 M
+// or 100 M: 4 %, and up to 1.6 times). Measured (above, here): 25088 -> 4096 at batch 1 39.0,
+// 24.5 us, 25088 -> 256 at batch 96 95.6, 113; 4096 -> 4096 at batch 2, 8, 32, 128 10.6, 9.8;
+// 19.4, 16.2; 60.6, 50.9; 233, 157; 512 -> 1000 at batch 32 5.8, 9.1; 2048 -> 1000 at batch 8,
+// 32, 128 7.7, 9.2; 12.3, 12.1; 31.6, 25.9; 8000 -> 256 at batch 4 8.6, 9.2 with 5 bits, 14.1, 8.9
+// with 2. DS_ROWS_BATCH: 16 forces the table, its other values the kernel above.
 static bool table_path(const ConvGeom &g)
 {
     const int forced = tuning(kRowsBatch);
     if (forced == 16) return true;
-    const int64_t terms = int64_t(g.n) * g.c * g.k;
-    return forced < 0 && g.k >= 256 &&
-           (terms >= 100000000 || (terms >= 24000000 && (g.n <= 4 || g.c >= 8000)) || (terms >= 14000000 && g.n == 1));
+    if (forced >= 0 || g.k < 256) return false;
+    const TableGrid t = table_grid(g);
+    const int per = 32 / g.bits;
+    const double bytes = 4.0 * g.k * t.words, codes = double(t.words) * per;
+    double cost = 0.0;
+    const int rows = rows_per_block(g, t.words, true, &cost);
+    const int64_t blocks = int64_t((g.k + 63) / 64) * ((g.n + rows - 1) / rows);
+    const double above = 3.0 + (rows_splits(blocks, t.words, true) > 1 ? 1.8 : 0.0) +
+                         std::max(codes * cost * 1.54e-3, bytes / 1.8e6);
+    static const double crowd[] = {0.0, 1.0, 1.7, 2.4, 3.5};
+    const int64_t share = (int64_t(t.kblocks) * t.row_groups * t.parts + 255) / 256;   // workgroups of a CU
+    const double used = double(g.k) / (double(kTableThreads) * t.kblocks);
+    const double code_ns = (6.5 + 3.25 * t.rows) * used + 100.0 / kTableThreads * t.rows * (1 << g.bits);
+    const double work = (share <= 4 ? crowd[share] : 3.5 / 4 * double(share)) * codes / t.parts * code_ns * 1e-3 *
+                        (t.words > 3000 ? 1.3 : 1.0);
+    const double here = 5.0 + (t.rows > 1 ? 0.2 : 0.0) + std::max(work, bytes / 3.4e6);
+    return above > (int64_t(g.n) * g.c * g.k >= 100000000 ? 0.95 : 1.05) * here;
 }
 
 static hipError_t run_table(const ConvGeom &g, const int32_t *x, const uint32_t *wp, const int32_t *bias, int32_t *y,
@@ -1442,18 +1481,12 @@ static hipError_t run_table(const ConvGeom &g, const int32_t *x, const uint32_t 
     a.B = g.n;
     a.C = g.c;
     a.K = g.k;
-    a.wpr = int(row_words_bits(g.c, g.bits));
-    const int rows = g.n >= 3 ? 4 : g.n;
-    const int64_t blocks = int64_t((g.k + kTableThreads - 1) / kTableThreads) * ((g.n + rows - 1) / rows);
-    // Parts of at least 16 words (64 bytes of each row), 1024 workgroups (25088 -> 4096
-    // at batch 1: 35.3, 29.9, 25.0, 24.8, 27.0 us with 256, 512, 768, 1024, 1536).
-    const int64_t parts = std::max<int64_t>(1, std::min<int64_t>((a.wpr + 15) / 16, 1024 / blocks));
-    const int part_words = (int((a.wpr + parts - 1) / parts) + 15) & ~15;
-    const dim3 grid(unsigned((g.k + kTableThreads - 1) / kTableThreads), unsigned((g.n + rows - 1) / rows),
-                    unsigned((a.wpr + part_words - 1) / part_words));
-    if (rows == 4) launch_table<4>(grid, x, a, part_words, g.bits, st);
-    else if (rows == 2) launch_table<2>(grid, x, a, part_words, g.bits, st);
-    else launch_table<1>(grid, x, a, part_words, g.bits, st);
+    const TableGrid t = table_grid(g);
+    a.wpr = t.words;
+    const dim3 grid(unsigned(t.kblocks), unsigned(t.row_groups), unsigned(t.parts));
+    if (t.rows == 4) launch_table<4>(grid, x, a, t.part_words, g.bits, st);
+    else if (t.rows == 2) launch_table<2>(grid, x, a, t.part_words, g.bits, st);
+    else launch_table<1>(grid, x, a, t.part_words, g.bits, st);
     e = hipGetLastError();
     return e == hipSuccess && epi.any() ? run_epilogue(g, y, epi, st) : e;
 }

@@ -120,3 +120,28 @@ for bits in (5, 4, 3, 2):
         for gradient in (False, True):
             assert plan(codes, bits, gradient) == matrix, (bits, zeros, gradient)
 """, tmp_path)
+
+
+def test_small_batch_linear_takes_the_faster_kernel(tmp_path):
+    """The choice between the table and the kernel that decodes each code, where they are
+    furthest apart (measured on MI355X, us: decoding, table): by codes' width, by long rows
+    of few channels and by terms."""
+    run("""
+x, w, y = (np.zeros(64, np.int32).ctypes.data + (i << 36) for i in range(3))   # never touched
+def table(n, c, k, bits):
+    mock.mock_reset(ALL)
+    flags = 0 if bits == 5 else bits << 8
+    assert lib.ds_linear_shift(x, w, None, y, n, c, k, 16, flags, None) == 0, lib.ds_last_error_message()
+    names = kernels()
+    assert ("linear_table_kernel" in names) != ("linear_rows_kernel" in names), names
+    return "linear_table_kernel" in names
+for n, c, k, bits in [(1, 25088, 4096, 5), (1, 25088, 512, 5),      # 39.0, 24.5; 17.3, 11.6
+                      (128, 4096, 4096, 5), (200, 2048, 2048, 5),   # 233, 157; 121, 78
+                      (64, 2048, 1000, 5), (200, 2048, 256, 5),     # 19.5, 14.9; 21.3, 16.2
+                      (4, 8000, 256, 2), (1, 8000, 1000, 3), (128, 512, 4096, 4)]:   # 14.1, 8.9; 8.9, 7.1; 37.3, 18.7
+    assert table(n, c, k, bits), (n, c, k, bits)
+for n, c, k, bits in [(96, 25088, 256, 5), (200, 25088, 256, 5),    # 95.6, 113; 181, 227
+                      (32, 512, 1000, 5), (8, 256, 128, 2),         # 5.8, 9.1; fewer than 256 channels
+                      (16, 1024, 512, 5), (4, 2048, 1000, 4), (64, 512, 256, 2)]:    # 6.9, 9.2; 6.9, 9.1; 5.4, 9.1
+    assert not table(n, c, k, bits), (n, c, k, bits)
+""", tmp_path)
