@@ -48,19 +48,22 @@ maxpool_kernel(const int32_t *__restrict__ x, int32_t *__restrict__ y, int64_t t
     }
 }
 
-// Sixteen lanes per (n, c) plane: floor of the int64 sum over the plane / HW.
-// A thread per plane read it at one load's latency after another: 16 x 64 planes of
-// 56 x 56 take 394 us so and 19.5 us here.
+// LANES lanes per (n, c) plane: floor of the int64 sum over the plane / HW. A thread per
+// plane reads it at one load's latency after another, sixteen divide by HW sixteen times:
+// 16 x 64 planes of 56 x 56 take 394 us with one and 19.5 with sixteen, 2^20 planes of 5 x
+// 5 152 and 60, of 4 x 4 38 and 55, of one element 7.5 and 53.
+template <int LANES>
 __global__ void __launch_bounds__(256)
 avgpool_global_kernel(const int32_t *__restrict__ x, int32_t *__restrict__ y, int64_t planes,
                       int HW)
 {
-    const int part = threadIdx.x & 15;
-    for (int64_t i = int64_t(blockIdx.x) * 16 + (threadIdx.x >> 4); i < planes; i += int64_t(gridDim.x) * 16) {
+    const int part = threadIdx.x % LANES;
+    for (int64_t i = int64_t(blockIdx.x) * (256 / LANES) + threadIdx.x / LANES; i < planes;
+         i += int64_t(gridDim.x) * (256 / LANES)) {
         const int32_t *xp = x + i * HW;
         int64_t sum = 0;
-        for (int64_t p = part; p < HW; p += 16) sum += xp[p];
-        for (int off = 8; off > 0; off >>= 1) sum += __shfl_xor(sum, off, 16);
+        for (int64_t p = part; p < HW; p += LANES) sum += xp[p];
+        for (int off = LANES / 2; off > 0; off >>= 1) sum += __shfl_xor(sum, off, LANES);
         int64_t q = sum / HW;
         if (sum % HW != 0 && sum < 0) q -= 1;  // division truncates; floor it
         if (part == 0) y[i] = int32_t(q);
@@ -124,7 +127,8 @@ extern "C" ds_status ds_avgpool2d_global(const int32_t *x, int32_t *y, int64_t n
     if (overlap(x, 4 * xe, y, 4 * ye)) return fail(DS_ERR_INVALID_ARG, "y overlaps x");
     if (!device_range_ok(x, 4 * xe)) return fail(DS_ERR_INVALID_ARG, "x is not a device buffer of %lld bytes", (long long)(4 * xe));
     if (!device_range_ok(y, 4 * ye)) return fail(DS_ERR_INVALID_ARG, "y is not a device buffer of %lld bytes", (long long)(4 * ye));
-    hipLaunchKernelGGL(avgpool_global_kernel, dim3(grid_for(16 * ye)), dim3(256), 0,
-                       static_cast<hipStream_t>(stream), x, y, ye, int(h * w));
+    const int lanes = h * w <= 16 ? 1 : 16;
+    hipLaunchKernelGGL(lanes == 1 ? avgpool_global_kernel<1> : avgpool_global_kernel<16>, dim3(grid_for(lanes * ye)),
+                       dim3(256), 0, static_cast<hipStream_t>(stream), x, y, ye, int(h * w));
     return status_of(hipGetLastError(), "ds_avgpool2d_global");
 }

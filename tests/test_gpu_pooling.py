@@ -26,7 +26,8 @@ def test_maxpool_edges(shape):
     np.testing.assert_array_equal(y, oracle.maxpool2d(x, r=r, stride=st, pad=pd))
 
 
-@pytest.mark.parametrize("shape", [(1, 1, 3, 5), (1, 17, 4, 4), (5, 33, 1, 17), (1, 16, 31, 1), (2, 1, 56, 57)])
+@pytest.mark.parametrize("shape", [(1, 1, 3, 5), (1, 17, 4, 4), (5, 33, 1, 17), (1, 16, 31, 1), (2, 1, 56, 57),
+                                   (3, 300, 2, 2), (2, 1000, 1, 1)])
 def test_avgpool_edges(shape):
     x = np.random.default_rng(sum(shape)).integers(-(2 ** 31), 2 ** 31 - 1, shape, dtype=np.int64).astype(np.int32)
     x[0, 0] = -(2 ** 31)
