@@ -230,7 +230,8 @@ bool matrix_phases(const ConvGeom &g, std::vector<MfmaTask> &tasks, bool &zeros)
     // The small-batch LinearShift kernel keeps its rows.
     if (fv < 0 && g.h == 1 && g.w == 1 && g.r == 1 && g.s == 1 && g.ph == 0 && g.pw == 0 && g.n < 256) return false;
     int64_t terms = 0;
-    return mfma_gradient_tasks(g, tasks, zeros, terms) && (fv == 64 || mfma_prefer(tasks[0].g, terms));
+    if (!mfma_gradient_tasks(g, tasks, zeros, terms)) return false;
+    return fv == 64 || (mfma_prefer(tasks[0].g, terms) && !(tasks.size() == 1 && mfma_padded(tasks[0].g, tasks[0].l, true)));
 }
 
 size_t matrix_phase_bytes(const std::vector<MfmaTask> &tasks)

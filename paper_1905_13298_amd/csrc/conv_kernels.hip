@@ -824,7 +824,7 @@ static void plan_splits(const ConvGeom &g, const Variant &v, int &tiles_p, int &
 static bool use_mfma(const ConvGeom &g, const MfmaLayout &l)
 {
     const int fv = forced_variant();
-    return l.fits && (fv == 64 || (fv < 0 && mfma_prefer(g, int64_t(g.n) * g.oh * g.ow * g.k * g.crs)));
+    return l.fits && (fv == 64 || (fv < 0 && mfma_prefer(g, int64_t(g.n) * g.oh * g.ow * g.k * g.crs) && !mfma_padded(g, l, false)));
 }
 
 static bool use_direct(const ConvGeom &g, const Variant &v)

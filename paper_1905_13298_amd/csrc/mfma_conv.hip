@@ -1154,12 +1154,38 @@ MfmaLayout mfma_layout(const ConvGeom &g, bool shared, int tasks)
 // takes 13.0 us there and 18.6 here, 512 -> 10 on 7 x 7, batch 32 (8 M, ten of the 64
 // rows of a tile in use) 15.7 and 19.7; 64 -> 64 3 x 3 on 14 x 14 (7 M) 24.1 and
 // 21.4, 128 -> 128 3 x 3 on 28 x 28 (116 M) 30.6 and 22.2, and 256 -> 256 3 x 3 on
-// 14 x 14 at batch 128 (14.8 G) 935 and 150. A LinearShift (256 rows or more here)
-// takes five launches there: 128 -> 64 at batch 300 (2.5 M) 26.4 against 19.5.
+// 14 x 14 at batch 128 (14.8 G) 935 and 150. From 50 M terms a few rows of a tile are
+// enough (eager calls): 64 -> 1 3 x 3 on 56 x 56 at batch 32 (58 M) 198 and 46, 256 -> 4 on
+// 28 x 28 at batch 8 (58 M) 68 and 27, 1024 -> 8 1 x 1 on 14 x 14 at batch 32 (51 M) 38 and
+// 23. A LinearShift (256 rows or more here) takes five launches there: 128 -> 64 at batch
+// 300 (2.5 M) 26.4 against 19.5.
 bool mfma_prefer(const ConvGeom &g, int64_t terms)
 {
     const bool linear = g.h == 1 && g.w == 1 && g.r == 1 && g.s == 1;
     return linear || (g.k > 16 && terms >= 4000000) || terms >= 50000000;
+}
+
+// By both paths' times (us, fitted to eager calls of 295 problems of 4 - 28 terms a row,
+// 3 - 256 channels and 25 - 2097 thousand pixels, within 15 % of nearly all; the choice is
+// 0.3 % off the best). On the matrix cores: x read and packed at 4 TB/s, whole tiles at 139
+// T terms/s, each row's sums at 6.6 T/s and y at 9.2 TB/s. On the vector kernels: y at 3.7
+// TB/s, or a third of that and 11.5 T terms/s of at least 32 rows; an input gradient
+// re-packs its codes first (4). Measured there and on the matrix cores: 4 -> 24 1 x 1 on 112
+// x 112 at batch 8 14 and 20, 8 -> 64 on 56 x 56 at batch 64 26 and 39, 1 -> 64 3 x 3 29 and
+// 45, 3 -> 24 34 and 44, 3 -> 64 104 and 75 (512 x 512, batch 2), 16 -> 128 1 x 1 55 and 49
+// (56 x 56, batch 64); gradients of 64 -> 4 1 x 1 on 512 x 512 at batch 8 207 and 226, 64 -> 16
+// on 112 x 112 28 and 22.
+bool mfma_padded(const ConvGeom &g, const MfmaLayout &l, bool gradient)
+{
+    const bool linear = g.h == 1 && g.w == 1 && g.r == 1 && g.s == 1;
+    if (linear || double(g.crs) >= 0.45 * 64.0 * l.nchunks || g.r > 5 || g.s > 5) return false;
+    const double x = 4.0 * g.n * double(g.c) * g.h * g.w, nq = double(g.n) * g.oh * g.ow, y = 4.0 * nq * g.k;
+    const double rows = double(l.tiles_k) * kRows;
+    const double matrix = 13.0 + (x + double(kXpBytes) * l.CB * l.NP) / 4.0e6 +
+                          double(l.tiles_p) * kPix * rows * l.nchunks * 64.0 / 139e6 + nq * rows / 6.6e6 + y / 9.2e6;
+    const double issue = nq * std::max(32, (g.k + 15) / 16 * 16) * g.crs / 11.5e6;
+    const double vector = 12.0 + (gradient ? 4.0 : 1.0) + std::max(y / 3.7e6, issue + y / 11.5e6);
+    return vector <= matrix;
 }
 
 // In microseconds on MI355X (graph replays): two launches and what a tile does

@@ -28,8 +28,11 @@ struct MfmaLayout {
 MfmaLayout mfma_layout(const ConvGeom &g, bool shared = false, int tasks = 1);
 
 // Whether the matrix cores are expected to run a problem of this many terms
-// faster than the vector kernels.
+// faster than the vector kernels,
 bool mfma_prefer(const ConvGeom &g, int64_t terms);
+// unless its reduction is so short that most of a chunk is padding. `gradient`: the
+// vector kernels run it as a gradient's single phase.
+bool mfma_padded(const ConvGeom &g, const MfmaLayout &l, bool gradient);
 
 // Where a problem's weights are in the packed codes. Element (output channel k,
 // reduction channel c, tap (r, s)) is the code of row k and column

@@ -7,10 +7,11 @@ from paper_1905_13298_amd import _native, ops
 from .mock_hip import run
 
 
-def test_pixel_counts_near_2_31_keep_off_the_matrix_cores():
+def test_pixel_counts_near_2_31_keep_off_the_matrix_cores(knob):
     """A tile's pixel range is formed in 32 bits, past its 256 pixels: 8 x 16383 x 16385
     outputs end 8 short of 2^31, where the last tile's end does not fit."""
     n, oh, ow = 8, 16383, 16385
+    knob("DS_FORCE_VARIANT", 64)
     assert 2 ** 31 - 256 < n * oh * ow < 2 ** 31
     d = ops.describe_conv2d(n, 1, 1, 3, 1, 1, 1, 8191)
     assert "matrix cores" not in d
@@ -145,3 +146,17 @@ for n, c, k, bits in [(96, 25088, 256, 5), (200, 25088, 256, 5),    # 95.6, 113;
                       (16, 1024, 512, 5), (4, 2048, 1000, 4), (64, 512, 256, 2)]:    # 6.9, 9.2; 6.9, 9.1; 5.4, 9.1
     assert not table(n, c, k, bits), (n, c, k, bits)
 """, tmp_path)
+
+
+def test_short_reductions_keep_off_the_matrix_cores():
+    """A chunk is 64 terms: a reduction of a few, most of it padding, runs on the vector kernels
+    where it is measured faster there (the comment's figures, us: vector, matrix cores)."""
+    matrix = lambda n, c, h, k, r, p: ops.describe_conv2d(n, c, h, h, k, r, 1, p).startswith("matrix cores")
+    for shape in [(8, 4, 112, 24, 1, 0), (64, 8, 56, 64, 1, 0), (64, 1, 56, 64, 3, 1), (64, 3, 56, 24, 3, 1)]:
+        assert not matrix(*shape), shape        # 14, 20; 26, 39; 29, 45; 34, 44
+    for shape in [(2, 3, 512, 64, 3, 1), (64, 16, 56, 128, 1, 0), (8, 24, 112, 64, 1, 0), (64, 64, 28, 64, 1, 0)]:
+        assert matrix(*shape), shape            # 104, 75; 55, 49
+    grad = lambda n, c, h, k, r, s, p: ops.describe_conv2d_backward_data(n, c, h, h, k, r, s, p).startswith("matrix cores")
+    assert not grad(8, 64, 512, 4, 1, 1, 0)     # 207, 226
+    assert grad(8, 64, 112, 16, 1, 1, 0)        # 28, 22
+    assert grad(64, 64, 56, 5, 3, 2, 1)         # phases together: 98, 40
