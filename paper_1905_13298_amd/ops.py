@@ -447,7 +447,8 @@ def _np_ptr(a):
 def jit_conv_image(w_packed, x_shape, kernel_size, stride=1, padding=0, bias=None, mul=None,
                    add=None, mul_shift: int = 16, residual: bool = False, relu: bool = False,
                    splits: int = 0, code_bits: int = 5, act_bits: int = 32) -> bytes:
-    """The code object a JitConv with these arguments would load (host only)."""
+    """The code object that generated code for a JitConv with these arguments makes: what
+    it loads, unless it takes the matrix cores (host only)."""
     k = int(w_packed.shape[0])
     wp, b, m, a = _jit_args(w_packed, k, bias, mul, add)
     n, c, h, w = x_shape
@@ -516,9 +517,10 @@ class JitConv:
         # Whether the plan runs on the matrix cores rather than generated code.
         self.matrix_cores = bool(lib().ds_jit_conv_matrix_cores(self._h))
 
-    # Cost model of generated code and the vector kernels on MI355X (microseconds),
-    # fitted to calls timed back to back. (A call or plan on the matrix cores is the
-    # faster of its kind already: the plan holds the weights the call expands.) A plan's waves each stream their share of the straight-line
+    # Cost model of generated code and the runtime calls on MI355X (microseconds),
+    # fitted to calls timed back to back. (A plan on the matrix cores is the runtime
+    # call's kernels with the weights expanded already.) Otherwise a plan's waves each
+    # stream their share of the straight-line
     # code at about 1.6 GB/s when few waves share it (instruction fetch: a 64-byte
     # line per L2 round trip with a few in flight; the 4096 -> 4096 LinearShift
     # at batch 256, 290 KB per wave, 174 us), and the chip issues at most 0.355
@@ -527,19 +529,24 @@ class JitConv:
     # instruction; each share's code runs once per group of 64 pixels (a pixel
     # tile holds 1, 2 or 4 of them).
     # Launch and set-up add about 3 us, a split reduction (fill pass, atomics) 3
-    # us more. The runtime kernel decodes its weights and launches 2-5 kernels per
-    # call (about 25 us for a convolution, 40 us for a LinearShift at 256 rows or
-    # more, whose operands it transposes), then runs at up to 15 T dense SACs/s
-    # on full tiles of 256 output pixels (a ragged last tile wastes its lanes),
-    # reading its packed weights at 4 TB/s. A LinearShift of fewer than 256 rows
-    # takes the small-batch kernel instead (lanes own output channels): about 6
-    # us plus 9.6 T dense SACs/s, or its packed weights at 1.75 TB/s when they
-    # dominate (batch 1: each code decoded for one row). A LinearShift plan on x^T adds its
-    # two transposing passes and runs its kernel about 15 % slower than modelled
-    # (2.5 us + 1.16 x the plan's own estimate fits batches 64-256 within 15 %).
+    # us more. A runtime call on the matrix cores (a LinearShift from 256 rows, convolutions
+    # from 4 M SACs) expands its weights (10 bytes each at 3.6 TB/s), packs x (4 bytes
+    # read and 2.75 written an element), forms the products of whole tiles of 256
+    # pixels, 64 channels and 64 terms at 130 T SACs/s and writes y at 4 TB/s, over 16
+    # us, or 20.5 with the split reduction of a convolution: 22 modelled and 17 measured
+    # for 128 -> 128 3 x 3 on 28 x 28 at batch 1, 97 and 95 for 4096 -> 4096 at batch 256,
+    # 105 and 96 for 1024 -> 256 on 14 x 14 at batch 128. Smaller convolutions run on the
+    # vector kernels, about 13 us plus 15 T dense SACs/s. A LinearShift of fewer than 256
+    # rows takes a small-batch kernel: about 5.5 us plus 9.6 T dense SACs/s, or its packed
+    # weights at 1.75 TB/s when they dominate (batch 1: each code decoded for one row), or
+    # from 256 channels, where that is less, a table: 7.5 us, 13.5 T and 3.2 TB/s. A
+    # LinearShift plan on x^T adds its two transposing passes and runs its kernel about 15
+    # % slower than modelled (2.5 us + 1.16 x the plan's own estimate fits batches 64-256
+    # within 15 %).
     PLAN_STREAM_BPUS = 1.6e3        # code bytes per us per wave
     PLAN_ISSUE_PER_US = 872e3       # wave-instructions per us, whole chip
-    RUNTIME_SAC_PER_US = 15e6       # dense SACs per us on full tiles
+    RUNTIME_SAC_PER_US = 15e6       # dense SACs per us, vector kernels
+    MATRIX_SAC_PER_US = 130e6       # SACs per us of whole tiles on the matrix cores
     ROWS_SAC_PER_US = 9.6e6         # dense SACs per us, small-batch LinearShift kernel
 
     def estimate_us(self) -> float:
@@ -559,27 +566,34 @@ class JitConv:
     def runtime_estimate_us(self) -> float:
         """Modelled duration of the same layer on the runtime kernel
         (ds_conv2d_shift / ds_linear_shift)."""
-        nq = max(1, self.out_pixels)
-        weight_bytes = self.out_channels * packed_row_words(self.crs) * 4
+        nq, k = max(1, self.out_pixels), self.out_channels
+        weight_bytes = k * packed_row_words(self.crs) * 4
         if self.linear and nq < 256:
-            return 5.5 + max(self.sac / self.ROWS_SAC_PER_US, weight_bytes / 1.75e6)
-        fill = nq / (-(-nq // 256) * 256)
-        return ((40.0 if self.linear else 25.0) + self.sac / (self.RUNTIME_SAC_PER_US * fill)
-                + weight_bytes / 4e6)
+            rows = 5.5 + max(self.sac / self.ROWS_SAC_PER_US, weight_bytes / 1.75e6)
+            table = 7.5 + max(self.sac / 13.5e6, weight_bytes / 3.2e6)
+            return min(rows, table) if k >= 256 else rows
+        if not (self.linear or (k > 16 and self.sac >= 4e6) or self.sac >= 5e7):
+            return 13.0 + self.sac / self.RUNTIME_SAC_PER_US
+        tiles, chunks = -(-nq // 256) * -(-k // 64), -(-self.crs // 64)
+        x_elems = math.prod(getattr(self, "x_shape", (0,)))
+        taps = self.sac / (nq * k * self.crs)    # an input gradient's stride phases have a share of them each
+        return ((20.5 if tiles < 9 * chunks and not self.linear else 16.0)
+                + taps * tiles * chunks * 256 * 64 * 64 / self.MATRIX_SAC_PER_US
+                + 10.0 * k * self.crs / 3.6e6 + 6.75 * x_elems / 5.5e6 + 4.0 * nq * k / 4e6)
 
     @property
     def preferred(self) -> bool:
         """Whether this plan is expected to beat the runtime kernel, by the cost
         model above. Measured on MI355X as graph replays (model in brackets),
         plan against runtime call: 4096 -> 4096 at batch 256, both on the matrix
-        cores, 64 us against 94; generated code against the vector kernels: 2048 -> 1000 at batch 128 on x^T 17.0 us
-        (17.5) against 32.5-36 us (33); 1024 -> 1024 at batch 64 on x^T 11.9 us
-        (12.0) against 13.7 us (12.5); 512 -> 512 at batch 128 on x^T 10.3 us
-        (12.0) against 8.4 us (9.0); 256 -> 128 at batch 8 4.2 us (5.5)
-        against 4.5 us (5.5); 512 -> 1000 at batch 32 10.2 us (11) against 6.5
-        us (7.2); 25088 -> 4096 at batch 1 344 us (282) against 24 us (42).
-        Over the layers of ResNet-18 (batch 32) and ResNet-50 (batch 128) in generated
-        code, measured / modelled plan durations have medians 1.16 and 1.04."""
+        cores, 64 us against 94; generated code against the small-batch kernels: 2048 -> 1000 at
+        batch 128 on x^T 17.0 us (17.5) against 25.9 (27); 1024 -> 1024 at batch 64 on x^T
+        11.9 (12.0) against 12.7 (12.5); 512 -> 512 at batch 128 on x^T 10.3
+        (12.0) against 8.4 (9.0); 256 -> 128 at batch 8 4.2 (5.5) against 4.5
+        (5.5); 512 -> 1000 at batch 32 10.2 (11) against 6.5 (7.2); 25088 -> 4096 at batch 1
+        344 (282) against 24 (29). Over the layers of ResNet-18 (batch 32) and ResNet-50
+        (batch 128) in generated code, measured / modelled plan durations have medians 1.16
+        and 1.04."""
         if getattr(self, "matrix_cores", False):
             return True     # the runtime call's kernels, with the weights expanded already
         return self.estimate_us() < self.runtime_estimate_us()
@@ -746,3 +760,13 @@ class JitConvMul(JitConv):
         self.out_pixels, self.out_channels = n * self.y_shape[2] * self.y_shape[3], self.k
         self.sac = self.out_pixels * self.k * self.crs
         self.linear = h == wd == r == s == 1 and ph == pw == 0
+
+    def runtime_estimate_us(self) -> float:
+        """Modelled duration of the same layer on the runtime kernel (the vector kernels:
+        ds_conv2d_mul_i32 / ds_linear_mul_i32)."""
+        nq = max(1, self.out_pixels)
+        weight_bytes = self.out_channels * packed_row_words(self.crs) * 4
+        if self.linear and nq < 256:
+            return 5.5 + max(self.sac / self.ROWS_SAC_PER_US, weight_bytes / 1.75e6)
+        fill = nq / (-(-nq // 256) * 256)
+        return (40.0 if self.linear else 25.0) + self.sac / (self.RUNTIME_SAC_PER_US * fill) + weight_bytes / 4e6
