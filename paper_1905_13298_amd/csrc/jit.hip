@@ -1018,25 +1018,33 @@ static bool matrix_allowed(int splits)
     return splits == 0 && (forced_variant() < 0 || forced_variant() == 64);
 }
 
-// Non-zero codes among `rows` packed rows of `cols` codes.
+// Non-zero codes among `rows` packed rows of `cols` codes. Zero codes are counted in
+// the codes' own places, all of a word's at once.
 static int64_t nonzero_codes(const uint32_t *wp, int64_t rows, int64_t cols, int bits)
 {
-    const int per = 32 / bits;
-    uint32_t ones = 0;   // bit 0 of every code in a word
+    const int per = 32 / bits, most = (1 << bits) - 1;   // words before a count could leave its place
+    uint32_t ones = 0;                                   // bit 0 of every code in a word
     for (int j = 0; j < per; ++j) ones |= 1u << (bits * j);
     const int64_t full = cols / per, rw = row_words_bits(cols, bits);
     const uint32_t rest = ones & ((1u << (bits * int(cols % per))) - 1u);
+    // A zero code is one whose bits below the sign are all ones.
+    auto zero = [bits](uint32_t w) {
+        if (bits >= 4) w &= w >> 1;
+        return w & (bits == 5 ? w >> 2 : bits == 4 ? w >> 1 : bits == 3 ? w >> 1 : w);
+    };
     int64_t zeros = 0;
+    auto add = [&](uint32_t counts) {
+        for (int j = 0; j < per; ++j) zeros += counts >> (bits * j) & uint32_t(most);
+    };
     for (int64_t k = 0; k < rows; ++k) {
         const uint32_t *row = wp + k * rw;
-        // A zero code is one whose bits below the sign are all ones.
-        auto count = [&](uint32_t w, uint32_t mask) {
-            uint32_t z = w;
-            for (int b = 1; b < bits - 1; ++b) z &= w >> b;
-            return __builtin_popcount(z & mask);
-        };
-        for (int64_t i = 0; i < full; ++i) zeros += count(row[i], ones);
-        if (rest) zeros += count(row[full], rest);
+        for (int64_t i = 0; i < full; i += most) {
+            const int64_t end = std::min(full, i + most);
+            uint32_t counts = 0;
+            for (int64_t q = i; q < end; ++q) counts += zero(row[q]) & ones;
+            add(counts);
+        }
+        if (rest) add(zero(row[full]) & rest);
     }
     return rows * cols - zeros;
 }

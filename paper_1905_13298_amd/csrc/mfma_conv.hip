@@ -330,16 +330,19 @@ __device__ void pack_x(const T *__restrict__ x, const PackParams &p, int block, 
             }
         }
     }
-    int most = 0;
+    int32_t low = 0, high = 0;
     uint32_t h6[6] = {};
 #pragma unroll
     for (int e = 0; e < kBlockK; ++e) {
         const int h = v[e] >> 16;
-        // (two digits hold -528 .. 495, three -16912 .. 15855)
-        const int a = h >= -16 && h <= 15 ? abs(h) : h >= -528 && h <= 495 ? 253 : h >= -16912 && h <= 15855 ? 254 : 255;
-        most = max(most, a);
+        low = min(low, v[e]);
+        high = max(high, v[e]);
         put6(h6, e, e2m3(((h + 16) & 31) - 16));
     }
+    low >>= 16;
+    high >>= 16;
+    // (two digits hold -528 .. 495, three -16912 .. 15855)
+    int most = low >= -16 && high <= 15 ? max(-low, high) : low >= -528 && high <= 495 ? 253 : low >= -16912 && high <= 15855 ? 254 : 255;
     const int64_t np = p.NP;
     unsigned char *o = xp + int64_t(cb) * np * kXpBytes;
     if (in) {
@@ -422,7 +425,6 @@ struct PrepArgs {
     unsigned char *xp, *dig, *hmax;
     PackParams p;
     int wblocks, pblocks;            // of all tasks together; blocks past both fill
-    int ntasks;
     WeightTask w[kMfmaTasks];
     FillParams f[kMfmaTasks];
 };
@@ -1121,7 +1123,6 @@ MfmaLayout mfma_layout(const ConvGeom &g, bool shared, int tasks)
              std::max(std::abs(g.ph), std::abs(g.pw)) < 8192;
     if (!l.fits) return l;
     l.CB = int(cb);
-    l.T = int(t);
     l.even = l.CB % 2 == 0;
     l.xp_bytes = size_t(round256(cb * np * kXpBytes));
     l.dig_bytes = size_t(round256(cb * np * kDigBytes));
@@ -1267,7 +1268,6 @@ hipError_t mfma_prepare(const MfmaTask *tasks, int ntasks, const void *x, int ac
     PrepArgs a{};
     a.x = x;
     a.wp = wp;
-    a.ntasks = ntasks;
     if (x) {
         const MfmaTask &t = tasks[0];
         const ConvGeom &g = t.g;

@@ -15,7 +15,7 @@ struct MfmaLayout {
     bool fits = false;
     bool sampled = false;        // a 1 x 1 window: the packed copy holds the sampled pixels only
     int US = 1;                  // tap columns folded into the channels of the packed copy
-    int CB = 0, T = 0, even = 0; // 32-channel blocks, taps, whether CB is even
+    int CB = 0, even = 0;        // 32-channel blocks, whether their number is even
     int nchunks = 0, tiles_p = 0, tiles_k = 0, splits = 1, cps = 0;
     int PH = 0, PW = 0, NP = 0, nblk = 0;
     size_t xp_bytes = 0, dig_bytes = 0, hm_bytes = 0, wa_bytes = 0, bd_bytes = 0;
