@@ -1269,8 +1269,13 @@ static void launch_rows_op(const ConvGeom &g, const int32_t *x, const RowsArgs &
     else launch_rows<OP, 1>(grid, x, a, g.bits, st);
 }
 
-// Whether a problem takes the small-batch LinearShift kernel: 1 x 1 taps on
-// 1 x 1 inputs, dense output, fewer than 256 rows, no forced variant.
+// Whether a problem takes the small-batch LinearShift kernels: 1 x 1 taps on
+// 1 x 1 inputs, dense output, fewer than 256 rows, no forced variant. 256 is where the
+// tiled vector kernels overtook them; the matrix cores, which have taken their place
+// from there, are ahead below it too where the layer is large (us, eager calls, here and
+// there: 4096 -> 4096 at batch 32, 64, 128, 255 49, 78; 91, 79; 155, 85; 410, 101; 25088 ->
+// 4096 at batch 64 588, 558; 2048 -> 1000 at batch 200, 255 36, 36; 49, 38) and behind where
+// it is not (1024 -> 1024 at batch 200 22, 24; 256 -> 128 at batch 255 7, 16).
 static bool rows_path(const ConvGeom &g, const OutMap &map, const Padded &pad)
 {
     return g.h == 1 && g.w == 1 && g.r == 1 && g.s == 1 && g.ph == 0 && g.pw == 0 && map.dense() &&
